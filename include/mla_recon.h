@@ -257,13 +257,15 @@ int mla_recon_decode_noalloc(const mla_recon_cfg *cfg, const void *q, const void
                              int32_t max_len, const int32_t *lengths, const void *Wuk,
                              const void *Wuv, void *o, void *hip_stream);
 
-/* Prefill in absorbed form: every token of cfg->batch sequences of cfg->seq tokens attends,
- * causally, to the latent cache of its own sequence (Eq. 5's rows [c^KV_j | R_j k^PE_j],
- * j <= t) with the absorbed query [W_UK^T q^nope ; q^rope]; the output is the block's
- * per-head attention output o = W_UV[g] (weighted latent) and/or its post-W_O output A
- * (the student side of Eq. 11), computed either as o W_O^T or, given the folded weights of
- * mla_recon_fold_uv_into_o, as (weighted latent) W_O'^T.  Same shape requirements as
- * mla_recon_decode, and at most 65535 tokens (batch * seq) per call.
+/* Prefill over the latent cache: every token of cfg->batch sequences of cfg->seq tokens
+ * attends, causally, to the latent cache of its own sequence (Eq. 5's rows
+ * [c^KV_j | R_j k^PE_j], j <= t); the output is the block's per-head attention output
+ * o = W_UV[g] (weighted latent) and/or its post-W_O output A (the student side of Eq. 11),
+ * computed either as o W_O^T or, given the folded weights of mla_recon_fold_uv_into_o, as
+ * (weighted latent) W_O'^T.  The keys W_UK c_j (and, without folded weights, the values
+ * W_UV c_j) are expanded into ws once per call, bf16.  A cache row that is not finite makes
+ * the outputs of the tokens that see it NaN and leaves all others as they are.  Same shape
+ * requirements as mla_recon_decode, and at most 65535 tokens (batch * seq) per call.
  *   q     [B, T, H, d_nope + d_rope] bf16 (q^rope rotated by R_t)
  *   cache [B, T, r_kv + d_rope] bf16
  *   Wuk [G_kv d_nope, r_kv], Wuv [G_kv d_k, r_kv], Wo [D, H d_k] bf16; Wo_folded

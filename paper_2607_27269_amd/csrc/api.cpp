@@ -880,18 +880,54 @@ int mla_recon_prefill(const mla_recon_cfg* cfg, const void* q, const void* cache
   const int rows = cfg->batch * cfg->seq, H = cfg->n_heads, D = cfg->hidden;
   const int dv = cfg->head_dim, rkv = cfg->kv_rank;
   const bool folded = A && Wo_folded;
-  // rows b T + t: token t of sequence b, against the first t + 1 rows of its cache
-  Decode d = decode_of(cfg, q, cache, cfg->seq, nullptr, Wuk, Wuv, nullptr, ws);
-  d.B = rows;
-  d.tps = cfg->seq;
-  void* obuf = o ? o : (A && !folded ? (void*)at(ws, off_o) : nullptr);
-  d.o = obuf;
-  if (folded) d.lat_out = at(ws, off_lat);
-  HIP_TRY(decode_attention(d, s));
+  // The absorbed query against the cache equals q^nope . (W_UK c_j) + q^rope . k^PE_j, and
+  // W_UV applied to the weighted latent equals the weighted W_UV c_j.  With T queries per
+  // cache row the expanded form costs 2 (d_nope + d_rope + d_k) flops per (query, key, head)
+  // instead of the absorbed 2 (2 r_kv + d_rope) and runs on the causal attention kernel, so
+  // the keys and values are expanded once per call (decoding, with one query per sequence,
+  // stays absorbed: there the expansion would cost more than the attention).  Measured at
+  // 2 x 2048 tokens, H = 32, r_kv = 512, d_k = 128 (o and A): 256 us
+  // against 1770 us absorbed (one workgroup per token over the cache); folded at
+  // 3 x 999, H = 14, r_kv = 256, d_k = 64: 173 us against 483 us.
+  const int T = cfg->seq, Gkv = cfg->s_kv_groups, dn = cfg->nope_dim, dr = cfg->rope_dim;
+  const int hpg = H / Gkv, dqk = dn + dr;
+  // ws: keys, then the values (or, folded, the guarded latents); both smaller than the
+  // absorbed-query region that prefill_layout reserves
+  const int nk = dn > 0 ? Gkv * dn : dr, nv = Gkv * dv;
+  void* keys = ws;
+  void* vals = at(ws, al((size_t)rows * nk * 2));
+  // (an o that the vector stores cannot take is filled from ws at the end)
+  const bool o_direct = o && (uintptr_t)o % 16 == 0;
+  void* obuf = o_direct ? o : (void*)at(ws, off_o);
+  void* lat = at(ws, off_lat);
+  if (dn > 0)
+    HIP_TRY(gemm(mk(rows, nk, rkv, cache, rkv + dr, true, Wuk, rkv, true, keys, nk, DT_BF16, DT_BF16), nullptr, 0, s));
+  if (!folded)
+    HIP_TRY(gemm(mk(rows, nv, rkv, cache, rkv + dr, true, Wuv, rkv, true, vals, nv, DT_BF16, DT_BF16), nullptr, 0, s));
+  HIP_TRY(prefill_guard(cache, rows, rkv, dr, keys, nk, dn == 0, folded ? nullptr : vals, nv,
+                        folded ? vals : nullptr, s));
+  Attn p;
+  p.B = cfg->batch; p.T = T; p.H = H; p.dqk = dqk; p.dv = dv;
+  p.dnope = dn > 0 ? dn : dqk;  // (no non-positional keys: the guarded copy of k^PE)
+  p.Q = HeadView{q, (int64_t)H * dqk, dqk, 1};
+  p.Ka = HeadView{keys, nk, dn > 0 ? dn : 0, dn > 0 ? hpg : H};
+  p.Kb = HeadView{(const uint16_t*)cache + rkv, rkv + dr, 0, H};
+  p.lse = nullptr; p.scale = cfg->softmax_scale; p.t = DT_BF16;
+  if (folded) {  // the weighted latent of every head, d_k columns at a time
+    p.V = HeadView{vals, rkv, 0, H};
+    p.O = lat; p.o_tok = (int64_t)H * rkv; p.o_head = rkv; p.n_vchunk = rkv / dv;
+  } else {
+    p.V = HeadView{vals, nv, dv, hpg};
+    p.O = obuf; p.o_tok = (int64_t)H * dv;
+  }
+  HIP_TRY(attn_fwd(p, s));
+  if (folded && o) HIP_TRY(uv_project(lat, Wuv, obuf, rows, H, rkv, hpg, dv, s));
+  if (o && !o_direct)
+    HIP_TRY(hipMemcpyAsync(o, obuf, (size_t)rows * H * dv * 2, hipMemcpyDeviceToDevice, s));
   if (A) {
     // A = o W_O^T, or with the folded weights A = latent W_O'^T (K = H r_kv)
     const int K = folded ? H * rkv : H * dv;
-    HIP_TRY(gemm(mk(rows, D, K, folded ? d.lat_out : obuf, K, true, folded ? Wo_folded : Wo, K, true,
+    HIP_TRY(gemm(mk(rows, D, K, folded ? lat : obuf, K, true, folded ? Wo_folded : Wo, K, true,
                     A, D, DT_BF16, DT_F32), nullptr, 0, s));
   }
   return MLA_OK;

@@ -32,7 +32,8 @@ struct AttnDev {
   const bf16_t* Ka; int64_t ka_tok; int ka_head; int ka_div;
   const bf16_t* Kb; int64_t kb_tok; int kb_head; int kb_div;
   const bf16_t* V; int64_t v_tok; int v_head; int v_div;
-  bf16_t* O; int64_t o_tok;
+  bf16_t* O; int64_t o_tok; int o_head;
+  int nvc;  // chunks of dv value columns (forward)
   float* lse;
   const bf16_t* Oref; bf16_t* Odiff;  // optional: Odiff = O - Oref (rounded O), layout of O
   const float* qcos; const float* qsin; int qroff, qnp;  // optional: Q rotated on load
@@ -47,7 +48,8 @@ inline AttnDev to_dev(const Attn& a) {
   d.Ka = (const bf16_t*)a.Ka.p; d.ka_tok = a.Ka.tok; d.ka_head = (int)a.Ka.head; d.ka_div = a.Ka.div;
   d.Kb = (const bf16_t*)a.Kb.p; d.kb_tok = a.Kb.tok; d.kb_head = (int)a.Kb.head; d.kb_div = a.Kb.div;
   d.V = (const bf16_t*)a.V.p; d.v_tok = a.V.tok; d.v_head = (int)a.V.head; d.v_div = a.V.div;
-  d.O = (bf16_t*)a.O; d.o_tok = a.o_tok; d.lse = a.lse;
+  d.O = (bf16_t*)a.O; d.o_tok = a.o_tok; d.o_head = a.o_head ? (int)a.o_head : a.dv;
+  d.nvc = a.n_vchunk; d.lse = a.lse;
   d.Oref = (const bf16_t*)a.o_ref; d.Odiff = (bf16_t*)a.o_diff;
   d.qcos = a.q_cos; d.qsin = a.q_sin; d.qroff = a.q_roff; d.qnp = a.q_np;
   d.nqb = 0;
@@ -73,13 +75,14 @@ struct KVStage {
   int64_t ka_tok, kb_tok, v_tok;
   int dnope, T;
 
-  __device__ __forceinline__ void init(const AttnDev& a, int b, int i) {
+  // (voff: first value column)
+  __device__ __forceinline__ void init(const AttnDev& a, int b, int i, int voff) {
     kt.init();
     vt.init();
     const int64_t n0 = (int64_t)b * a.T;
     ka = a.Ka + n0 * a.ka_tok + (int64_t)(i / a.ka_div) * a.ka_head;
     kb = a.Kb + n0 * a.kb_tok + (int64_t)(i / a.kb_div) * a.kb_head - a.dnope;
-    vb = a.V + n0 * a.v_tok + (int64_t)(i / a.v_div) * a.v_head;
+    vb = a.V + n0 * a.v_tok + (int64_t)(i / a.v_div) * a.v_head + voff;
     ka_tok = a.ka_tok; kb_tok = a.kb_tok; v_tok = a.v_tok;
     dnope = a.dnope; T = a.T;
   }

@@ -47,7 +47,8 @@ __device__ __forceinline__ void fwd_tile(const AttnDev& a, int pid, bf16_t* smem
   // share K/V, run on one XCD); heavy (late) query blocks first inside each head group
   constexpr int BQH = FWD_BQ / HG;  // queries per head
   const int ngr = a.H / HG;
-  const int bh = pid / a.nqb;
+  const int bhc = pid / a.nqb;
+  const int vc = bhc / (a.B * ngr), bh = bhc % (a.B * ngr);  // value chunk; 0 unless nvc > 1
   const int qb = a.nqb - 1 - pid % a.nqb;
   const int b = bh / ngr, i0 = (bh % ngr) * HG;
   const int q0 = qb * BQH;
@@ -113,7 +114,7 @@ __device__ __forceinline__ void fwd_tile(const AttnDev& a, int pid, bf16_t* smem
   // tiles this wavefront sees (a prefix: the causal diagonal cuts its queries last)
   const int nvis = min(nkb, (qw0 + 31) / BKV + 1);
   Stage st;
-  st.init(a, b, i0);  // the group's keys and values
+  st.init(a, b, i0, vc * DV);  // the group's keys and values
   st.issue(0, smem, smem + KS);
   if (nkb > 1) st.issue(BKV, smem + (KS + VS), smem + (KS + VS) + KS);
   wait_all();
@@ -223,7 +224,7 @@ __device__ __forceinline__ void fwd_tile(const AttnDev& a, int pid, bf16_t* smem
   const float l = pair_sum32(l_run);
   if (my_q >= a.T) return;
   const float inv = 1.f / l;
-  const int64_t ooff = ((int64_t)b * a.T + my_q) * a.o_tok + (int64_t)i * DV + 4 * half;
+  const int64_t ooff = ((int64_t)b * a.T + my_q) * a.o_tok + (int64_t)i * a.o_head + vc * DV + 4 * half;
   bf16_t* op = a.O + ooff;
   // the reference rows first, all loads before any store: interleaved, each load would
   // wait (one in-order memory counter) for every store issued before it
@@ -258,7 +259,7 @@ template <int DQK, int DV, bool LSE, int HG>
 __global__ __launch_bounds__(64 * FWD_WAVES) void attn_fwd_mfma_kernel(AttnDev a) {
   using Stage = KVStage<DQK, DV, FWD_WAVES>;
   __shared__ __attribute__((aligned(1024))) bf16_t smem[3 * (Stage::KS + Stage::VS)];
-  const int nwork = a.B * (a.H / HG) * a.nqb;
+  const int nwork = a.nvc * a.B * (a.H / HG) * a.nqb;
   fwd_tile<DQK, DV, LSE, HG>(a, xcd_remap(blockIdx.x, nwork), smem);
 }
 
@@ -270,7 +271,7 @@ template <int DQK, int DV, bool LSE, int HG>
 __global__ __launch_bounds__(64 * FWD_WAVES) void attn_fwd_persist_kernel(AttnDev a) {
   using Stage = KVStage<DQK, DV, FWD_WAVES>;
   __shared__ __attribute__((aligned(1024))) bf16_t smem[3 * (Stage::KS + Stage::VS)];
-  const int per = a.B * (a.H / HG) * a.nqb / 8;  // items of one XCD
+  const int per = a.nvc * a.B * (a.H / HG) * a.nqb / 8;  // items of one XCD
   const int x = blockIdx.x % 8, j = blockIdx.x / 8;
   for (int r = 0;; ++r) {
     const int local = r * FWD_PCU + ((r & 1) ? FWD_PCU - 1 - j : j);
@@ -285,7 +286,7 @@ hipError_t fwd_launch_hg(const Attn& at, hipStream_t s, const char** kernel) {
   AttnDev d = to_dev(at);
   constexpr int BQH = FWD_BQ / HG;
   d.nqb = (at.T + BQH - 1) / BQH;
-  const int nwork = d.B * (d.H / HG) * d.nqb;
+  const int nwork = d.nvc * d.B * (d.H / HG) * d.nqb;
   // the persistent walk needs whole XCD shares of several rounds
   if (nwork % 8 == 0 && nwork / 8 >= 2 * FWD_PCU) {
     if (at.lse) {

@@ -76,8 +76,6 @@ struct DecodeDev {
   int64_t seq_stride;   // Lmax * ldc
   int ldc;              // row stride of the cache (elements)
   const int32_t* len;   // [B]
-  int tps;              // prefill: query row b is token b % tps of sequence b / tps and
-                        // attends to that sequence's first b % tps + 1 rows (0: decoding)
   int Lmax, HP, nsplit, chunk;
   float sl2;            // softmax scale * log2(e)
   float* part_o;        // [B][nsplit][HP][DVL]
@@ -185,14 +183,14 @@ __global__ __launch_bounds__(64 * DEC_WAVES) void decode_attn_kernel(DecodeDev a
   const int split = blockIdx.x, b = blockIdx.y, h0 = 32 * blockIdx.z;
   const int lane = threadIdx.x & 63, wave = wave_id();
   const int half = lane >> 5, col = lane & 31;
-  const int len = a.tps ? b % a.tps + 1 : min(max(a.len[b], 0), a.Lmax);
+  const int len = min(max(a.len[b], 0), a.Lmax);
   const int kbeg = split * a.chunk;
   const int kend = min(len, kbeg + a.chunk);
   const int64_t pbase = ((int64_t)b * a.nsplit + split) * a.HP + h0;
   // this wave's share of the K steps
   const int kk0 = wave * NKK / DEC_WAVES, kk1 = (wave + 1) * NKK / DEC_WAVES;
 
-  const bf16_t* cs = a.cache + (int64_t)(a.tps ? b / a.tps : b) * a.seq_stride;
+  const bf16_t* cs = a.cache + (int64_t)b * a.seq_stride;
   KT kt_copy;
   kt_copy.init();
   // key tile t into stage t % NST; rows past the chunk end repeat its last row (finite,
@@ -426,32 +424,16 @@ hipError_t decode_attention(const Decode& d, hipStream_t s) {
   w += al((size_t)d.B * nsplit * HP * DVL * 4);
   float* part_ml = (float*)w;
   w += al((size_t)d.B * nsplit * HP * 2 * 4);
-  bf16_t* lat = d.lat_out ? (bf16_t*)d.lat_out : (bf16_t*)w;
+  bf16_t* lat = (bf16_t*)w;
 
   prof_begin(KC_ELEM, s);
   const int64_t nq = (int64_t)d.B * HP * DK;
   const int G = d.H / d.hpg;
   const int grow = (d.B * d.hpg + 31) / 32;
   // latent part: q_abs[b][i][:rkv] = q^nope[b][i] W_UK[g]
-  if (d.tps == 0 || d.dn % 8 || d.rkv % 32) {
-    group_gemm_kernel<bf16_t><<<dim3((d.rkv + 31) / 32, grow, G), 256, 0, s>>>(
-        (const bf16_t*)d.q, d.dn + d.dr, (const bf16_t*)d.Wuk, qabs, DK, HP, d.B, d.H, d.hpg, d.dn,
-        d.rkv);
-  } else {
-    // many query rows (prefill): one matrix-core product per head, [rows, d_nope] x
-    // W_UK[g] ([d_nope, r_kv], N-contiguous)
-    for (int i = 0; i < d.H; ++i) {
-      Gemm g;
-      g.M = d.B; g.N = d.rkv; g.K = d.dn;
-      g.A = (const bf16_t*)d.q + (int64_t)i * (d.dn + d.dr); g.lda = (int64_t)d.H * (d.dn + d.dr);
-      g.a_kmajor = true;
-      g.B = (const bf16_t*)d.Wuk + (int64_t)(i / d.hpg) * d.dn * d.rkv; g.ldb = d.rkv; g.b_kmajor = false;
-      g.C = qabs + (int64_t)i * DK; g.ldc = (int64_t)HP * DK;
-      g.in_t = DT_BF16; g.c_t = DT_BF16; g.alpha = 1.f; g.beta = 0.f;
-      hipError_t e = gemm(g, nullptr, 0, s);
-      if (e != hipSuccess) return e;
-    }
-  }
+  group_gemm_kernel<bf16_t><<<dim3((d.rkv + 31) / 32, grow, G), 256, 0, s>>>(
+      (const bf16_t*)d.q, d.dn + d.dr, (const bf16_t*)d.Wuk, qabs, DK, HP, d.B, d.H, d.hpg, d.dn,
+      d.rkv);
   {
     const int64_t nrest = (int64_t)d.B * d.H * d.dr + (int64_t)d.B * (HP - d.H) * DK;
     absorb_rest_kernel<<<(unsigned)((nrest + 255) / 256), 256, 0, s>>>(
@@ -461,7 +443,7 @@ hipError_t decode_attention(const Decode& d, hipStream_t s) {
 
   DecodeDev a;
   a.qabs = qabs; a.cache = (const bf16_t*)d.cache; a.ldc = d.ldc;
-  a.seq_stride = (int64_t)d.Lmax * d.ldc; a.len = d.len; a.tps = d.tps; a.Lmax = d.Lmax; a.HP = HP;
+  a.seq_stride = (int64_t)d.Lmax * d.ldc; a.len = d.len; a.Lmax = d.Lmax; a.HP = HP;
   a.nsplit = nsplit; a.chunk = chunk; a.sl2 = d.scale * attn::LOG2E;
   a.part_o = part_o; a.part_ml = part_ml;
   const dim3 grid(nsplit, d.B, HP / 32);
@@ -479,20 +461,65 @@ hipError_t decode_attention(const Decode& d, hipStream_t s) {
   prof_end(KC_ELEM, s, 0.0, (double)d.B * nsplit * HP * (DVL + 2) * 4 + (double)d.B * d.H * DVL * 2,
            KLABEL("decode_combine_kernel"));
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || d.o == nullptr) return e;
+  if (e != hipSuccess) return e;
+  return uv_project(lat, d.Wuv, d.o, d.B, d.H, d.rkv, d.hpg, d.dv, s);
+}
+
+hipError_t uv_project(const void* lat, const void* Wuv, void* o, int rows, int H, int rkv, int hpg,
+                      int dv, hipStream_t s) {
   // o = W_UV[g] lat per head (matrix cores)
   prof_begin(KC_ELEM, s);
-  if (d.dv == 128)
-    uv_mfma_kernel<128><<<dim3((d.B + 31) / 32, d.H), 256, 0, s>>>(lat, (const bf16_t*)d.Wuv,
-                                                                   (bf16_t*)d.o, d.B, d.H, d.rkv, d.hpg);
-  else if (d.dv == 64)
-    uv_mfma_kernel<64><<<dim3((d.B + 31) / 32, d.H), 128, 0, s>>>(lat, (const bf16_t*)d.Wuv,
-                                                                  (bf16_t*)d.o, d.B, d.H, d.rkv, d.hpg);
+  const dim3 grid((rows + 31) / 32, H);
+  if (dv == 128)
+    uv_mfma_kernel<128><<<grid, 256, 0, s>>>((const bf16_t*)lat, (const bf16_t*)Wuv, (bf16_t*)o, rows,
+                                             H, rkv, hpg);
+  else if (dv == 64)
+    uv_mfma_kernel<64><<<grid, 128, 0, s>>>((const bf16_t*)lat, (const bf16_t*)Wuv, (bf16_t*)o, rows,
+                                            H, rkv, hpg);
   else
     return hipErrorInvalidValue;
-  prof_end(KC_ELEM, s, 2.0 * d.B * d.H * d.dv * d.rkv,
-           (double)d.B * d.H * (d.dv + DVL) * 2 + (double)d.H / d.hpg * d.dv * d.rkv * 2,
-           KLABEL("uv_mfma_kernel"));
+  prof_end(KC_ELEM, s, 2.0 * rows * H * dv * rkv,
+           (double)rows * H * (dv + rkv) * 2 + (double)H / hpg * dv * rkv * 2, KLABEL("uv_mfma_kernel"));
+  return hipGetLastError();
+}
+
+// One wavefront per cache row: 16 bytes of the latent per lane (rkv <= 512).  Reads the
+// latents once; rows are rewritten only where they are not finite.
+__global__ __launch_bounds__(256) void prefill_guard_kernel(const bf16_t* __restrict__ cache,
+                                                            int64_t rows, int rkv, int dr,
+                                                            bf16_t* __restrict__ keys, int nk,
+                                                            int copy_pe, bf16_t* __restrict__ v,
+                                                            int nv, bf16_t* __restrict__ lat_copy) {
+  const int64_t row = (int64_t)blockIdx.x * 4 + wave_id();
+  if (row >= rows) return;
+  const int lane = threadIdx.x & 63;
+  const bf16_t* src = cache + row * (rkv + dr);
+  const bool in = 8 * lane < rkv;
+  u32x4 w = {0u, 0u, 0u, 0u};
+  if (in) w = *(const u32x4*)(src + 8 * lane);
+  bool bad = false;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    bad |= (w[q] & 0x7f80u) == 0x7f80u || (w[q] & 0x7f800000u) == 0x7f800000u;
+  const bool any = __ballot(bad) != 0;  // wave-uniform
+  if (lat_copy && in) *(u32x4*)(lat_copy + row * rkv + 8 * lane) = any ? u32x4{0u, 0u, 0u, 0u} : w;
+  if (copy_pe)
+    for (int c = lane; c < nk; c += 64) keys[row * nk + c] = any ? (bf16_t)0x7fc0 : src[rkv + c];
+  if (!any) return;
+  if (!copy_pe)
+    for (int c = lane; c < nk; c += 64) keys[row * nk + c] = (bf16_t)0x7fc0;
+  if (v)
+    for (int c = lane; c < nv; c += 64) v[row * nv + c] = (bf16_t)0;
+}
+
+hipError_t prefill_guard(const void* cache, int64_t rows, int rkv, int dr, void* keys, int nk,
+                         bool copy_pe, void* v, int nv, void* lat_copy, hipStream_t s) {
+  if (rkv > 512 || rkv % 8 || (copy_pe && nk != dr)) return hipErrorInvalidValue;
+  prof_begin(KC_ELEM, s);
+  prefill_guard_kernel<<<(unsigned)((rows + 3) / 4), 256, 0, s>>>(
+      (const bf16_t*)cache, rows, rkv, dr, (bf16_t*)keys, nk, copy_pe ? 1 : 0, (bf16_t*)v, nv,
+      (bf16_t*)lat_copy);
+  prof_end(KC_ELEM, s, 0.0, (double)rows * rkv * 2.0 * (lat_copy ? 2.0 : 1.0), KLABEL("prefill_guard_kernel"));
   return hipGetLastError();
 }
 

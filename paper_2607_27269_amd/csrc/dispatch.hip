@@ -60,13 +60,16 @@ static double causal_pairs(const Attn& a) {
 }
 
 hipError_t attn_fwd(const Attn& a, hipStream_t s) {
-  double flops = 2.0 * causal_pairs(a) * (a.dqk + a.dv);
+  double flops = 2.0 * causal_pairs(a) * (a.dqk + (double)a.n_vchunk * a.dv);
   double N = (double)a.B * a.T;
-  double bytes = N * a.H * (a.dqk + a.dv) * dsize(a.t) + N * a.H * (a.lse ? 4.0 : 0.0);
+  double bytes = N * a.H * (a.dqk + (double)a.n_vchunk * a.dv) * dsize(a.t) + N * a.H * (a.lse ? 4.0 : 0.0);
   if (a.o_diff) bytes += 2.0 * N * a.H * a.dv * dsize(a.t);
   const bool mfma = a.t == DT_BF16 && attn_mfma_supported(a.dqk, a.dv);
   // the query rotation on load exists on the matrix-core path only
   if (a.q_cos && (!mfma || a.q_roff != 0 || 2 * a.q_np != a.dqk || a.dqk % 32))
+    return hipErrorInvalidValue;
+  // chunked values: the matrix-core path, without lse and o_diff
+  if (a.n_vchunk < 1 || (a.n_vchunk > 1 && (!mfma || a.lse || a.o_diff)))
     return hipErrorInvalidValue;
   prof_begin(KC_ATTN_FWD, s);
   const char* kname = nullptr;

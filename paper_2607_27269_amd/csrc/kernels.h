@@ -85,6 +85,11 @@ struct Attn {
   const float* q_cos = nullptr;
   const float* q_sin = nullptr;
   int q_roff = 0, q_np = 0;
+  // forward only, optional (bf16 matrix-core path, lse and o_diff null): values of width
+  // n_vchunk * dv that all heads share, taken dv columns at a time: O[n*o_tok + i*o_head +
+  // c*dv + d] from V column c*dv + d (o_head = 0: dv)
+  int n_vchunk = 1;
+  int64_t o_head = 0;
 };
 hipError_t attn_fwd(const Attn& a, hipStream_t s);
 
@@ -211,12 +216,8 @@ struct Decode {
   const void* Wuk;                 // [G_kv dn][rkv]
   const void* Wuv;                 // [G_kv dv][rkv]
   float scale;
-  void* o;                         // [B][H][dv] bf16, or null (no W_UV product)
+  void* o;                         // [B][H][dv] bf16
   void* ws;                        // decode_ws_bytes
-  // prefill: B counts query rows, row b is token b % tps of sequence b / tps and attends to
-  // that sequence's first b % tps + 1 cache rows (len unused); 0 = decoding
-  int tps = 0;
-  void* lat_out = nullptr;         // optional [B][H][rkv] bf16: the attention-weighted latent
 };
 bool decode_supported(int DK, int DVL);
 size_t decode_ws_bytes(int B, int H, int DK, int DVL, int Lmax);
@@ -225,6 +226,18 @@ size_t decode_ws_bytes(int B, int H, int DK, int DVL, int Lmax);
 size_t decode_scratch_bytes();
 hipError_t decode_scratch(void** out);
 hipError_t decode_attention(const Decode& d, hipStream_t s);
+// o[r][i] = W_UV[i / hpg] lat[r][i] for `rows` rows of H heads (lat [rows][H][rkv] and o
+// [rows][H][dv] bf16, dv 64 or 128, rkv a multiple of 16)
+hipError_t uv_project(const void* lat, const void* Wuv, void* o, int rows, int H, int rkv, int hpg,
+                      int dv, hipStream_t s);
+// Prefill's guard against non-finite cache rows.  Attention multiplies masked values by
+// P = 0, which keeps a masked row out of earlier outputs only where it is finite.  For every
+// cache row whose latent has a NaN or an infinity: its values (v [rows][nv], or null) become
+// 0 and its keys (keys [rows][nk]) NaN, so that exactly the queries that see the row get NaN.
+// lat_copy (or null) receives the latents [rows][rkv], such rows as 0; copy_pe: the keys are
+// the cache's positional columns, copied (nk = dr; no non-positional keys).
+hipError_t prefill_guard(const void* cache, int64_t rows, int rkv, int dr, void* keys, int nk,
+                         bool copy_pe, void* v, int nv, void* lat_copy, hipStream_t s);
 
 // out = a - b elementwise over n elements of dtype t (fp32 arithmetic)
 hipError_t sub_elementwise(const void* a, const void* b, void* out, int64_t n, DType t,
