@@ -239,6 +239,30 @@ static int check_ws(const mla_recon_cfg* cfg, void* ws, size_t ws_bytes, Layout*
 
 static inline char* at(void* ws, size_t off) { return (char*)ws + off; }
 
+// Scratch for the split-K partials of products.  Every region here has the same size whatever
+// the workspace (the chunked dS^T region counts one sequence), so that a product's split, and
+// with it its rounding, does not depend on how much workspace the caller gave.
+struct Scratch {
+  float* p;
+  size_t elems;
+};
+// forward products: the backward's regions, none of which is live before the backward
+static Scratch fwd_scratch(const Layout& L, void* ws) {
+  return {(float*)at(ws, L.b_do), (L.l_scr - L.b_do) / 4};
+}
+// backward products once the attention's backward is done: the largest of the reserved
+// partials, the teacher's projections, dO and delta, and one sequence's dS^T
+static Scratch bwd_scratch(const Dims& d, const Layout& L, void* ws) {
+  Scratch s{(float*)at(ws, L.b_split), L.b_split_elems};
+  auto better = [&](size_t off, size_t bytes) {
+    if (bytes / 4 > s.elems) s = {(float*)at(ws, off), bytes / 4};
+  };
+  better(L.t_qkv, L.t_o - L.t_qkv);
+  better(L.b_do, L.b_dqacc - L.b_do);
+  if (L.chunk) better(L.b_ds, attn_ds_bytes(1, (int)d.H, (int)d.T));
+  return s;
+}
+
 static Gemm mk(int M, int N, int K, const void* A, int64_t lda, bool ak, const void* B,
                int64_t ldb, bool bk, void* C, int64_t ldc, DType in_t, DType c_t,
                float beta) {
@@ -300,12 +324,13 @@ static int teacher_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h
   char* qkv = at(ws, L.t_qkv);
   char* o = at(ws, L.t_o);
   const size_t ts = d.ts;
+  const Scratch sk = fwd_scratch(L, ws);
 
   HIP_TRY(rope_tables(w->inv_freq, 1, (int)d.T, dk / 2, cs, sn, s));
   // Eq. 1: q = W^Q h, k = W^K h, v = W^V h  (columns [Q | K | V] of one buffer)
-  HIP_TRY(gemm(mk(N, H * dk, D, h, D, true, w->Wq, D, true, qkv, ld_qkv, d.t, d.t), nullptr, 0, s));
-  HIP_TRY(gemm(mk(N, G * dk, D, h, D, true, w->Wk, D, true, qkv + (size_t)H * dk * ts, ld_qkv, d.t, d.t), nullptr, 0, s));
-  HIP_TRY(gemm(mk(N, G * dk, D, h, D, true, w->Wv, D, true, qkv + (size_t)(H + G) * dk * ts, ld_qkv, d.t, d.t), nullptr, 0, s));
+  HIP_TRY(gemm(mk(N, H * dk, D, h, D, true, w->Wq, D, true, qkv, ld_qkv, d.t, d.t), sk.p, sk.elems, s));
+  HIP_TRY(gemm(mk(N, G * dk, D, h, D, true, w->Wk, D, true, qkv + (size_t)H * dk * ts, ld_qkv, d.t, d.t), sk.p, sk.elems, s));
+  HIP_TRY(gemm(mk(N, G * dk, D, h, D, true, w->Wv, D, true, qkv + (size_t)(H + G) * dk * ts, ld_qkv, d.t, d.t), sk.p, sk.elems, s));
   // R_t on queries and keys (Sec. 3.1); on the matrix-core path the attention kernel rotates
   // the queries as it loads them (the teacher's rotated queries are not needed elsewhere)
   const bool q_on_load = d.t == DT_BF16 && attn_mfma_supported(dk, dk) && dk % 32 == 0;
@@ -326,7 +351,7 @@ static int teacher_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h
   HIP_TRY(attn_fwd(a, s));
   // the fixed output projection: A = concat_i o_i W_O^T
   if (A_t)
-    HIP_TRY(gemm(mk(N, D, H * dk, o, (int64_t)H * dk, true, w->Wo, (int64_t)H * dk, true, A_t, D, d.t, DT_F32), nullptr, 0, s));
+    HIP_TRY(gemm(mk(N, D, H * dk, o, (int64_t)H * dk, true, w->Wo, (int64_t)H * dk, true, A_t, D, d.t, DT_F32), sk.p, sk.elems, s));
   return MLA_OK;
 }
 
@@ -367,22 +392,23 @@ static int student_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h
   char* v = at(ws, L.s_v);
   char* o = at(ws, L.s_o);
   float* lse = (float*)at(ws, L.s_lse);
+  const Scratch sk = fwd_scratch(L, ws);
 
   HIP_TRY(rope_tables(w->inv_freq, Gr, T, dr / 2, cs, sn, s));
   // low-rank query: c^Q = W_DQ h, q = W_UQ c^Q  (q = W_UQ h when r_q = 0)
   const void* qin = h;
   int qk = D;
   if (rq > 0) {
-    HIP_TRY(gemm(mk(N, rq, D, h, D, true, w->Wdq, D, true, cq, rq, d.t, d.t), nullptr, 0, s));
+    HIP_TRY(gemm(mk(N, rq, D, h, D, true, w->Wdq, D, true, cq, rq, d.t, d.t), sk.p, sk.elems, s));
     qin = cq;
     qk = rq;
   }
-  HIP_TRY(gemm(mk(N, H * dqk, qk, qin, qk, true, w->Wuq, qk, true, q, (int64_t)H * dqk, d.t, d.t), nullptr, 0, s));
+  HIP_TRY(gemm(mk(N, H * dqk, qk, qin, qk, true, w->Wuq, qk, true, q, (int64_t)H * dqk, d.t, d.t), sk.p, sk.elems, s));
   // Eq. 5: [c^KV | k^PE] = [W^DKV; W^KR] h, [k^nope; v] = W^UKV c^KV
-  HIP_TRY(gemm(mk(N, kv_out, D, h, D, true, w->Wdkv_kr, D, true, ckv, kv_out, d.t, d.t), nullptr, 0, s));
+  HIP_TRY(gemm(mk(N, kv_out, D, h, D, true, w->Wdkv_kr, D, true, ckv, kv_out, d.t, d.t), sk.p, sk.elems, s));
   if (dn > 0)
-    HIP_TRY(gemm(mk(N, Gkv * dn, rkv, ckv, kv_out, true, w->Wuk, rkv, true, knope, (int64_t)Gkv * dn, d.t, d.t), nullptr, 0, s));
-  HIP_TRY(gemm(mk(N, Gkv * dv, rkv, ckv, kv_out, true, w->Wuv, rkv, true, v, (int64_t)Gkv * dv, d.t, d.t), nullptr, 0, s));
+    HIP_TRY(gemm(mk(N, Gkv * dn, rkv, ckv, kv_out, true, w->Wuk, rkv, true, knope, (int64_t)Gkv * dn, d.t, d.t), sk.p, sk.elems, s));
+  HIP_TRY(gemm(mk(N, Gkv * dv, rkv, ckv, kv_out, true, w->Wuv, rkv, true, v, (int64_t)Gkv * dv, d.t, d.t), sk.p, sk.elems, s));
   // decoupled RoPE on q^rope (rope group i / (H/G_r)) and on k^PE
   HIP_TRY(rope_apply(q, d.t, N, T, H, (int64_t)H * dqk, dqk, dn, dr / 2, H / Gr, cs, sn, s));
   HIP_TRY(rope_apply(ckv, d.t, N, T, Gr, kv_out, dr, rkv, dr / 2, 1, cs, sn, s));
@@ -398,7 +424,7 @@ static int student_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h
   HIP_TRY(attn_fwd(a, s));
   // the teacher's frozen W_O
   if (A_s)
-    HIP_TRY(gemm(mk(N, D, H * dv, o, (int64_t)H * dv, true, Wo, (int64_t)H * dv, true, A_s, D, d.t, DT_F32), nullptr, 0, s));
+    HIP_TRY(gemm(mk(N, D, H * dv, o, (int64_t)H * dv, true, Wo, (int64_t)H * dv, true, A_s, D, d.t, DT_F32), sk.p, sk.elems, s));
   return MLA_OK;
 }
 
@@ -470,13 +496,13 @@ static int bwd_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
   float* dkpe = (float*)at(ws, L.b_dkpe);
   char* dckv = at(ws, L.b_dckv);
   char* dcq = at(ws, L.b_dcq);
-  float* split = (float*)at(ws, L.b_split);
-  const size_t se = L.b_split_elems;
   const int64_t ld_dkv = (int64_t)Gkv * (dn + dv);
 
-  // dO = dA W_O  (W_O frozen: no dW_O); without dA, dO is already in place
+  // dO = dA W_O  (W_O frozen: no dW_O); without dA, dO is already in place (its partials: the
+  // gradient regions that follow dO and delta, not yet written)
+  const Scratch sk_do = {(float*)at(ws, L.b_dqacc), (L.l_scr - L.b_dqacc) / 4};
   if (dA)
-    HIP_TRY(gemm(mk(N, H * dv, D, dA, D, true, Wo, (int64_t)H * dv, false, dO, (int64_t)H * dv, t, t), nullptr, 0, s));
+    HIP_TRY(gemm(mk(N, H * dv, D, dA, D, true, Wo, (int64_t)H * dv, false, dO, (int64_t)H * dv, t, t), sk_do.p, sk_do.elems, s));
   // softmax-attention backward -> dq (rotary block rotated back), dk^nope, dv, dk^PE partials
   AttnBwd ab;
   Attn& a = ab.f;
@@ -498,17 +524,18 @@ static int bwd_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
   ab.loss_ref = loss_ref;
   ab.loss_part = loss_part;
   HIP_TRY(attn_bwd(ab, s));
+  const Scratch sk = bwd_scratch(d, L, ws);
 
   if (need_q) {
     const void* qin = rq > 0 ? (const void*)cq : h;
     const int qk = rq > 0 ? rq : D;
     // dW_UQ = dq^T c^Q
     if (gr->dWuq)
-      HIP_TRY(gemm(mk(H * dqk, qk, N, dq, (int64_t)H * dqk, false, qin, qk, false, gr->dWuq, qk, t, DT_F32), split, se, s));
+      HIP_TRY(gemm(mk(H * dqk, qk, N, dq, (int64_t)H * dqk, false, qin, qk, false, gr->dWuq, qk, t, DT_F32), sk.p, sk.elems, s));
     if (gr->dWdq) {
       // dc^Q = dq W_UQ, dW_DQ = dc^Q^T h
-      HIP_TRY(gemm(mk(N, rq, H * dqk, dq, (int64_t)H * dqk, true, w->Wuq, rq, false, dcq, rq, t, t), nullptr, 0, s));
-      HIP_TRY(gemm(mk(rq, D, N, dcq, rq, false, h, D, false, gr->dWdq, D, t, DT_F32), split, se, s));
+      HIP_TRY(gemm(mk(N, rq, H * dqk, dq, (int64_t)H * dqk, true, w->Wuq, rq, false, dcq, rq, t, t), sk.p, sk.elems, s));
+      HIP_TRY(gemm(mk(rq, D, N, dcq, rq, false, h, D, false, gr->dWdq, D, t, DT_F32), sk.p, sk.elems, s));
     }
   }
   if (need_kv) {
@@ -520,22 +547,22 @@ static int bwd_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
     both.m2 = Gkv * dn;
     if (t == DT_BF16 && gr->dWuk && gr->dWuv && dn > 0 && rkv % 4 == 0 &&
         (uintptr_t)gr->dWuk % 16 == 0 && (uintptr_t)gr->dWuv % 16 == 0 &&
-        gemm_scratch_elems(both) <= se) {
-      HIP_TRY(gemm(both, split, se, s));
+        sk.elems >= (size_t)both.M * both.N) {
+      HIP_TRY(gemm(both, sk.p, sk.elems, s));
     } else {
       if (gr->dWuk && dn > 0)
-        HIP_TRY(gemm(mk(Gkv * dn, rkv, N, dkv, ld_dkv, false, ckv, kv_out, false, gr->dWuk, rkv, t, DT_F32), split, se, s));
+        HIP_TRY(gemm(mk(Gkv * dn, rkv, N, dkv, ld_dkv, false, ckv, kv_out, false, gr->dWuk, rkv, t, DT_F32), sk.p, sk.elems, s));
       if (gr->dWuv)
-        HIP_TRY(gemm(mk(Gkv * dv, rkv, N, dkv + (size_t)Gkv * dn * ts, ld_dkv, false, ckv, kv_out, false, gr->dWuv, rkv, t, DT_F32), split, se, s));
+        HIP_TRY(gemm(mk(Gkv * dv, rkv, N, dkv + (size_t)Gkv * dn * ts, ld_dkv, false, ckv, kv_out, false, gr->dWuv, rkv, t, DT_F32), sk.p, sk.elems, s));
     }
     if (gr->dWdkv_kr) {
       // dc^KV = dk^nope W_UK + dv W_UV; dk^PE = R^T sum of the head partials
       if (dn > 0)
-        HIP_TRY(gemm(mk(N, rkv, Gkv * dn, dkv, ld_dkv, true, w->Wuk, rkv, false, dckv, kv_out, t, t), nullptr, 0, s));
-      HIP_TRY(gemm(mk(N, rkv, Gkv * dv, dkv + (size_t)Gkv * dn * ts, ld_dkv, true, w->Wuv, rkv, false, dckv, kv_out, t, t, dn > 0 ? 1.f : 0.f), nullptr, 0, s));
+        HIP_TRY(gemm(mk(N, rkv, Gkv * dn, dkv, ld_dkv, true, w->Wuk, rkv, false, dckv, kv_out, t, t), sk.p, sk.elems, s));
+      HIP_TRY(gemm(mk(N, rkv, Gkv * dv, dkv + (size_t)Gkv * dn * ts, ld_dkv, true, w->Wuv, rkv, false, dckv, kv_out, t, t, dn > 0 ? 1.f : 0.f), sk.p, sk.elems, s));
       HIP_TRY(dkpe_finish(dkpe, dckv + (size_t)rkv * ts, t, kv_out, N, T, Gr, Gkv / Gr, dr, cs, sn, s));
       // d[W_DKV; W_KR] = [dc^KV | dk^PE]^T h
-      HIP_TRY(gemm(mk(kv_out, D, N, dckv, kv_out, false, h, D, false, gr->dWdkv_kr, D, t, DT_F32), split, se, s));
+      HIP_TRY(gemm(mk(kv_out, D, N, dckv, kv_out, false, h, D, false, gr->dWdkv_kr, D, t, DT_F32), sk.p, sk.elems, s));
     }
   }
   return MLA_OK;
@@ -558,7 +585,8 @@ int mla_recon_bwd(const mla_recon_cfg* cfg, const void* h, const mla_student_w* 
 // W_O^T W_O (bf16, ws region l_gram) for the step without dA
 static int gram_impl(const Dims& d, const Layout& L, const void* Wo, void* ws, hipStream_t s) {
   const int D = (int)d.D, HV = (int)(d.H * d.dv);
-  HIP_TRY(gemm(mk(HV, HV, D, Wo, HV, false, Wo, HV, false, at(ws, L.l_gram), HV, d.t, d.t), nullptr, 0, s));
+  const Scratch sk = fwd_scratch(L, ws);
+  HIP_TRY(gemm(mk(HV, HV, D, Wo, HV, false, Wo, HV, false, at(ws, L.l_gram), HV, d.t, d.t), sk.p, sk.elems, s));
   return MLA_OK;
 }
 
@@ -590,7 +618,7 @@ static int student_step_impl(const mla_recon_cfg* cfg, const Layout& L, const vo
       // the product writes dO only; the backward's delta pass, which streams dO anyway,
       // sums dO . (o_s - o_t) = 2 L (so the product's epilogue does not read o_s - o_t)
       HIP_TRY(gemm_masked_scale(mk(N, HV, HV, odiff, HV, true, at(ws, L.l_gram), HV, true, dO, HV, d.t, d.t),
-                                loss_scale(scr), mask, parts, s));
+                                loss_scale(scr), mask, s));
       double* dot = (double*)at(ws, L.l_dot);
       int rc = bwd_impl(cfg, L, h, sw, Wo, nullptr, gr, ws, s, odiff, dot);
       if (rc) return rc;
@@ -895,15 +923,18 @@ int mla_recon_prefill(const mla_recon_cfg* cfg, const void* q, const void* cache
   // absorbed-query region that prefill_layout reserves
   const int nk = dn > 0 ? Gkv * dn : dr, nv = Gkv * dv;
   void* keys = ws;
-  void* vals = at(ws, al((size_t)rows * nk * 2));
+  const size_t off_v = al((size_t)rows * nk * 2), off_s = off_v + al((size_t)rows * std::max(nv, rkv) * 2);
+  void* vals = at(ws, off_v);
+  // split-K partials of the products: the rest of that region
+  const Scratch sk = {(float*)at(ws, off_s), off_o > off_s ? (off_o - off_s) / 4 : 0};
   // (an o that the vector stores cannot take is filled from ws at the end)
   const bool o_direct = o && (uintptr_t)o % 16 == 0;
   void* obuf = o_direct ? o : (void*)at(ws, off_o);
   void* lat = at(ws, off_lat);
   if (dn > 0)
-    HIP_TRY(gemm(mk(rows, nk, rkv, cache, rkv + dr, true, Wuk, rkv, true, keys, nk, DT_BF16, DT_BF16), nullptr, 0, s));
+    HIP_TRY(gemm(mk(rows, nk, rkv, cache, rkv + dr, true, Wuk, rkv, true, keys, nk, DT_BF16, DT_BF16), sk.p, sk.elems, s));
   if (!folded)
-    HIP_TRY(gemm(mk(rows, nv, rkv, cache, rkv + dr, true, Wuv, rkv, true, vals, nv, DT_BF16, DT_BF16), nullptr, 0, s));
+    HIP_TRY(gemm(mk(rows, nv, rkv, cache, rkv + dr, true, Wuv, rkv, true, vals, nv, DT_BF16, DT_BF16), sk.p, sk.elems, s));
   HIP_TRY(prefill_guard(cache, rows, rkv, dr, keys, nk, dn == 0, folded ? nullptr : vals, nv,
                         folded ? vals : nullptr, s));
   Attn p;
@@ -928,7 +959,7 @@ int mla_recon_prefill(const mla_recon_cfg* cfg, const void* q, const void* cache
     // A = o W_O^T, or with the folded weights A = latent W_O'^T (K = H r_kv)
     const int K = folded ? H * rkv : H * dv;
     HIP_TRY(gemm(mk(rows, D, K, folded ? lat : obuf, K, true, folded ? Wo_folded : Wo, K, true,
-                    A, D, DT_BF16, DT_F32), nullptr, 0, s));
+                    A, D, DT_BF16, DT_F32), sk.p, sk.elems, s));
   }
   return MLA_OK;
 }

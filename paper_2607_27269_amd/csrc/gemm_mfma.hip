@@ -51,8 +51,8 @@ struct GemmDev {
   const bf16_t* B; int64_t ldb;
   void* C; int64_t ldc;
   float* part;        // split-K partials [splits][M][N], or null
-  // masked-loss epilogue (with lpart set): C = lscale[0] mask[m] acc (not stored when C is
-  // NULL) and lpart[tile] = the sum over the tile of mask[m] acc^2, or of mask[m] acc
+  // masked-loss epilogue (with lscale set): C = lscale[0] mask[m] acc (not stored when C is
+  // NULL) and, with lpart set, lpart[tile] = the sum over the tile of mask[m] acc^2, or of mask[m] acc
   // lref[m, n] when lref is set
   const float* lscale; const uint8_t* lmask; double* lpart;
   const bf16_t* lref; int64_t ldref;
@@ -145,6 +145,13 @@ struct Loader<true, ROWS, NTHR, BK, false> {
                                       int row0, int rows_valid, int k0, bf16_t* lds) const {
     t.issue_s(lds, p + (int64_t)row0 * ld + k0, [&](int r, int c) { return r * (int)ld + c; });
   }
+  // the same for a tile cut by the matrix edge: rows past it repeat the last valid one
+  // (they feed only output rows that are not stored)
+  __device__ __forceinline__ void dma_edge(const Dma& t, const bf16_t* __restrict__ p, int64_t ld,
+                                           int row0, int rows_valid, int k0, bf16_t* lds) const {
+    t.issue_s(lds, p + (int64_t)row0 * ld + k0,
+              [&](int r, int c) { return min(r, rows_valid - 1) * (int)ld + c; });
+  }
   // operand fragment: rows row0 + lane%32, k = 16 kk + 8 half + 0..7 (row0 is a multiple of
   // 32, so the swizzle depends on the lane only)
   static __device__ __forceinline__ bf16x8 frag(const bf16_t* lds, int row0, int kk) {
@@ -206,6 +213,13 @@ struct Loader<false, ROWS, NTHR, BK, false> {
   __device__ __forceinline__ void dma(const Dma& t, const bf16_t* __restrict__ p, int64_t ld,
                                       int row0, int rows_valid, int k0, bf16_t* lds) const {
     t.issue_s(lds, p + (int64_t)k0 * ld + row0, [&](int r, int c) { return r * (int)ld + c; });
+  }
+  // (chunks past the edge repeat the last valid one)
+  __device__ __forceinline__ void dma_edge(const Dma& t, const bf16_t* __restrict__ p, int64_t ld,
+                                           int row0, int rows_valid, int k0, bf16_t* lds) const {
+    const int last = (rows_valid - 1) & ~7;
+    t.issue_s(lds, p + (int64_t)k0 * ld + row0,
+              [&](int r, int c) { return r * (int)ld + min(c, last); });
   }
 
   // operand fragment through the transposing read (lds_operand_tr's lane pattern: k-rows
@@ -367,9 +381,28 @@ __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, f32x4 v, float alpha, 
   *(u32x2*)p = u32x2{pack2bf(o[0], o[1]), pack2bf(o[2], o[3])};
 }
 
+// ---- edge tiles --------------------------------------------------------------------------
+// A last row or column tile that the matrix edge cuts is moved back so that it is whole (and
+// is copied straight to LDS like every other tile); it stores only the rows and columns that
+// no other tile owns.  Through registers, with zero fill, each of its slices had cost a whole
+// memory latency (about 1.7 us).  Not where the matrix is smaller than a tile, nor where the
+// shift would break the 16-byte chunks of an M- or N-contiguous operand or the 4-column
+// stores.  dS^T (ATILE) holds whole 32-row tiles past M.
+template <bool ATILE>
+__device__ __forceinline__ int edge_rows(const GemmDev& g) { return ATILE ? (g.M + 31) & ~31 : g.M; }
+template <int BM, int BN, bool AK, bool BKM, bool ATILE>
+__device__ __forceinline__ void shift_edge(const GemmDev& g, int& m0, int& n0) {
+  const int mtop = edge_rows<ATILE>(g);
+  if (mtop >= BM && (AK || mtop % 8 == 0)) m0 = min(m0, mtop - BM);
+  if (g.N >= BN && g.N % (BKM ? 4 : 8) == 0) n0 = min(n0, g.N - BN);
+}
+
 // ---- the kernel --------------------------------------------------------------------------
+// (SHIFT: the launch has tiles that the matrix edge cuts.  Whole-tile launches of the
+// matrix-core-bound products go without: the compare in their epilogues and the moved tile
+// origin cost the dS^T products and the NT kernel 1.5-2.5% at 16384 tokens.)
 template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK, int NST,
-          bool ATILE = false>
+          bool ATILE = false, bool SHIFT = true>
 __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
   constexpr int NTHR = 64 * WM * WN;
   constexpr int TM = BM / WM / 32;  // 32x32 MFMA tiles per wave along M
@@ -416,12 +449,14 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
     tm = first + (pid % (GROUP * ntn)) % gsz;
     tn = (pid % (GROUP * ntn)) / gsz;
   }
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int mlo = tm * BM, nlo = tn * BN;  // first row and column this tile stores
+  int m0 = mlo, n0 = nlo;
+  if constexpr (SHIFT) shift_edge<BM, BN, AK, BKM, ATILE>(g, m0, n0);
   const int split = blockIdx.y;
   int kbeg, kend;
   if (g.causal) {
-    kbeg = g.rev ? m0 : 0;
-    kend = g.rev ? g.ktotal : min(g.ktotal, m0 + BM);
+    kbeg = g.rev ? mlo : 0;
+    kend = g.rev ? g.ktotal : min(g.ktotal, mlo + BM);
   } else {
     kbeg = split * g.kchunk;
     kend = min(g.ktotal, kbeg + g.kchunk);
@@ -447,14 +482,16 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
   db.init();
   LA::swizzle(da);
   LB::swizzle(db);
-  const int mvalid = g.M - m0, nvalid = g.N - n0;
   const int nkg = (kend - kbeg + BK - 1) / BK;  // slices per operand group
   const int nk = nkg * (g.causal ? g.kgroups : 1);
-  // slices copied straight to LDS; a ragged last slice, and every slice of a tile that is
-  // cut by the matrix edge or whose operand rows are too far apart for 32-bit offsets,
-  // goes through registers with zero fill
-  const bool dma_ok = mvalid >= BM && nvalid >= BN &&
-                      (AK ? (int64_t)BM * g.lda : (int64_t)BK * g.lda) < (1ll << 30) &&
+  // slices copied straight to LDS (small tiles: also in a matrix smaller than the tile, with
+  // clamped rows); a
+  // ragged last slice, and every slice of a tile whose operand rows are too far apart for
+  // 32-bit offsets, goes through registers with zero fill
+  const int mvalid = edge_rows<ATILE>(g) - m0, nvalid = g.N - n0;
+  constexpr bool EDGE = BM <= 128 && !ATILE;  // (larger tiles are not used below their size)
+  const bool edge = mvalid < BM || nvalid < BN;  // uniform
+  const bool dma_ok = (EDGE || !edge) && (AK ? (int64_t)BM * g.lda : (int64_t)BK * g.lda) < (1ll << 30) &&
                       (BKM ? (int64_t)BN * g.ldb : (int64_t)BK * g.ldb) < (1ll << 30);
   const int nfull = dma_ok ? (kend - kbeg) / BK : 0;
   // rev: slices are walked from the top of the K range down, so that all row tiles of a
@@ -465,9 +502,14 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
     const int k0 = kbeg + ks * BK;
     const bf16_t* pa = gA + grp * g.sAk;
     const bf16_t* pb = gB + grp * g.sBk;
-    if (ks < nfull) {
+    if (ks < nfull && !(EDGE && edge)) {
       la.dma(da, pa, g.lda, m0, mvalid, k0, dst);
       lb.dma(db, pb, g.ldb, n0, nvalid, k0, dst + LA::ELEMS);
+    } else if (EDGE && ks < nfull) {
+      if constexpr (EDGE) {
+        la.dma_edge(da, pa, g.lda, m0, mvalid, k0, dst);
+        lb.dma_edge(db, pb, g.ldb, n0, nvalid, k0, dst + LA::ELEMS);
+      }
     } else {
       la.load(pa, g.lda, m0, mvalid, k0, kend);
       lb.load(pb, g.ldb, n0, nvalid, k0, kend);
@@ -540,7 +582,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
   static_assert(NTHR / 64 * 32 * SLD * 4 <= (int)sizeof(lds), "epilogue strip too large");
   float* strip = (float*)lds + wave * 32 * SLD;
   const bool vec = (g.ldc % 4) == 0;
-  const bool lmode = g.lpart != nullptr;  // uniform
+  const bool lmode = g.lscale != nullptr;  // uniform
   const float lsc = lmode ? *g.lscale : 0.f;
   float sse = 0.f;
   // two copies, as in the persistent epilogue: with beta = 0 no C is read
@@ -568,7 +610,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
         const int c = it * 64 + lane;
         const int r = c / CPR, col = (c % CPR) * 4;
         const int m = m0 + wrow0 + i * 32 + r, n = n0 + wcol0 + col;
-        if (m >= g.mstore || n >= g.N) continue;
+        if (m >= g.mstore || n >= g.N || (SHIFT && (m < mlo || n < nlo))) continue;
         f32x4 v = vv[it];
         if (lmode) {
           if (n + 4 > g.N) v = f32x4{v[0], n + 1 < g.N ? v[1] : 0.f, n + 2 < g.N ? v[2] : 0.f, 0.f};
@@ -614,7 +656,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
   // (the dS^T products never accumulate into C: beta = 0 is checked at their launch)
   if constexpr (ATILE) epilogue(std::false_type{});
   else if (g.beta != 0.f) epilogue(std::true_type{}); else epilogue(std::false_type{});
-  if (lmode) {
+  if (g.lpart != nullptr) {  // uniform
     // the tile's sum in a fixed order: lanes (fixed tree), then wavefronts in order
     // (the last bytes of the operand LDS, past every wavefront's strip)
     static_assert(NTHR / 64 * 32 * SLD * 4 + 8 * (NTHR / 64) <= (int)sizeof(lds), "LDS");
@@ -640,7 +682,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
 // longest K range first, and a workgroup takes them in snake order (forward in even rounds,
 // backward in odd ones), so that long and short ranges pair up on every CU.
 template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK, int NST,
-          bool CAUSAL>
+          bool CAUSAL, bool SHIFT = true>
 __device__ __forceinline__ void gemm_persist(const GemmDev& g) {
   // the causal products read a 32 x 32-tiled A (tile32_off)
   constexpr bool ATILE = CAUSAL;
@@ -676,7 +718,7 @@ __device__ __forceinline__ void gemm_persist(const GemmDev& g) {
   LB::swizzle(db);
 
   // nkg: slices of one operand group (the causal products walk kgroups stacked operands)
-  struct Item { int m0, n0, split, kbeg, kend, nk, nkg, nfull; int64_t aoff, boff, coff, coff_lo; };
+  struct Item { int m0, n0, mlo, nlo, split, kbeg, kend, nk, nkg, nfull; int64_t aoff, boff, coff, coff_lo; };
   auto item = [&](int it) {
     Item t;
     int tm, tn;
@@ -722,7 +764,12 @@ __device__ __forceinline__ void gemm_persist(const GemmDev& g) {
       t.kend = min(g.ktotal, t.kbeg + g.kchunk);
       t.nk = t.nkg = (t.kend - t.kbeg + BK - 1) / BK;
     }
-    const bool dma_ok = g.M - t.m0 >= BM && g.N - t.n0 >= BN &&
+    // a last tile cut by the edge starts early enough to be whole, and stores only its own
+    // rows and columns (the K range of a causal row tile is that of its own rows, set above)
+    t.mlo = t.m0;
+    t.nlo = t.n0;
+    if constexpr (SHIFT) shift_edge<BM, BN, AK, BKM, ATILE>(g, t.m0, t.n0);
+    const bool dma_ok = edge_rows<ATILE>(g) - t.m0 >= BM && g.N - t.n0 >= BN &&
                         (AK ? (int64_t)BM * g.lda : (int64_t)BK * g.lda) < (1ll << 30) &&
                         (BKM ? (int64_t)BN * g.ldb : (int64_t)BK * g.ldb) < (1ll << 30);
     t.nfull = dma_ok ? (t.kend - t.kbeg) / BK : 0;
@@ -735,6 +782,8 @@ __device__ __forceinline__ void gemm_persist(const GemmDev& g) {
     t.nk = __builtin_amdgcn_readfirstlane(t.nk);
     t.nkg = __builtin_amdgcn_readfirstlane(t.nkg);
     t.nfull = __builtin_amdgcn_readfirstlane(t.nfull);
+    t.mlo = __builtin_amdgcn_readfirstlane(t.mlo);
+    t.nlo = __builtin_amdgcn_readfirstlane(t.nlo);
     return t;
   };
   // slice kt of a tile: operand group kt / nkg, walked from the top of its K range down
@@ -879,7 +928,7 @@ __device__ __forceinline__ void gemm_persist(const GemmDev& g) {
             const int c = it * 64 + el;
             const int r = c / CPR, col = (c % CPR) * 4;
             const int m = cur.m0 + wrow0 + i * 32 + 16 * h + r, n = cur.n0 + wcol0 + col;
-            if (m >= g.mstore || n >= g.N) continue;
+            if (m >= g.mstore || n >= g.N || (SHIFT && (m < cur.mlo || n < cur.nlo))) continue;
             f32x4 v;
             if constexpr (BATCH) v = vv[it];
             else v = *(const f32x4*)(strip + r * SLD + col);
@@ -934,9 +983,9 @@ template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK
 __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_persist_kernel(GemmDev g) {
   gemm_persist<BM, BN, WM, WN, AK, BKM, TC, BK, NST, false>(g);
 }
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK, int NST>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK, int NST, bool SHIFT>
 __global__ __launch_bounds__(64 * WM * WN) void attn_ds_gemm_persist_kernel(GemmDev g) {
-  gemm_persist<BM, BN, WM, WN, AK, BKM, TC, BK, NST, true>(g);
+  gemm_persist<BM, BN, WM, WN, AK, BKM, TC, BK, NST, true, SHIFT>(g);
 }
 template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK, int NST>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(GemmDev g) {
@@ -944,14 +993,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(GemmDev g) {
 }
 // the same tile program for the dS products of attention's backward, on the 32 x 32-tiled
 // dS^T (own name, so that profiles tell them apart)
-template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK, int NST>
+template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK, int NST, bool SHIFT>
 __global__ __launch_bounds__(64 * WM * WN) void attn_ds_gemm_kernel(GemmDev g) {
-  gemm_tile<BM, BN, WM, WN, AK, BKM, TC, BK, NST, true>(g);
+  gemm_tile<BM, BN, WM, WN, AK, BKM, TC, BK, NST, true, SHIFT>(g);
 }
 
 // ---- NT products on four wavefronts, k-steps scheduled by hand ------------------------
 //
-// Both operands K-contiguous, M a multiple of 256, N of the tile width (256 or 192), K a
+// Both operands K-contiguous, M >= 256, N at least the tile width (256 or 192), K a
 // multiple of 128.  A workgroup of four wavefronts (one per SIMD) owns a 256 x 256 tile,
 // 128 x 128 per wavefront (16 accumulators of 32 x 32 in AGPRs; 256 x 192 tiles: 128 x 96,
 // 12 accumulators); per 16-wide k step each wavefront reads 8 KB of operands from LDS,
@@ -1016,7 +1065,7 @@ __global__ __launch_bounds__(64 * WM * WN) void attn_ds_gemm_kernel(GemmDev g) {
   [a0] "v"(cu[0]), [a1] "v"(cu[1]), [a2] "v"(cu[2]), [a3] "v"(cu[3]), [b0] "v"(cu[4]),      \
   [b1] "v"(cu[5]), [b2] "v"(cu[6]), [ra] "v"(ra), [rb] "v"(rb)
 
-template <int BN, typename TC>
+template <int BN, typename TC, bool SHIFT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_nt4_persist_kernel(GemmDev g) {
   constexpr int BM = 256, BKK = 64, TM = 4, TN = BN / 64;  // 4 or 3 fragments of B
@@ -1030,18 +1079,22 @@ void gemm_nt4_persist_kernel(GemmDev g) {
   static_assert(BN == 256 || BN == 192, "tile widths");
   static_assert(LA::Dma::PER == 8 && PB == TN * 2, "copies per lane per operand slice");
   __shared__ __attribute__((aligned(1024))) bf16_t lds[2 * STAGE + 2 * EPI];
-  const int ntm = g.M / BM, ntn = g.N / BN, ntiles = ntm * ntn;
+  const int ntm = (g.M + BM - 1) / BM, ntn = (g.N + BN - 1) / BN, ntiles = ntm * ntn;
   const int G = (int)gridDim.x;
   int w = blockIdx.x;
   if (w >= ntiles) return;
   const int lane = threadIdx.x & 63, wave = wave_id();
   const int wrow0 = (wave >> 1) * 128, wcol0 = (wave & 1) * WTN;
   // the tile order of the one-tile launch: XCD-aware remap, 8 row panels per group
-  auto tile_of = [&](int x, int& m0, int& n0) {
+  // (a tile that the edge cuts starts at M - BM or N - BN instead and stores only the rows
+  // and columns of its own)
+  auto tile_of = [&](int x, int& m0, int& n0, int& mlo, int& nlo) {
     const int pid = xcd_remap(x, ntiles);
     const int group = pid / (8 * ntn), first = group * 8, gsz = min(ntm - first, 8);
-    m0 = __builtin_amdgcn_readfirstlane((first + (pid % (8 * ntn)) % gsz) * BM);
-    n0 = __builtin_amdgcn_readfirstlane(((pid % (8 * ntn)) / gsz) * BN);
+    mlo = __builtin_amdgcn_readfirstlane((first + (pid % (8 * ntn)) % gsz) * BM);
+    nlo = __builtin_amdgcn_readfirstlane(((pid % (8 * ntn)) / gsz) * BN);
+    m0 = SHIFT ? min(mlo, g.M - BM) : mlo;
+    n0 = SHIFT ? min(nlo, g.N - BN) : nlo;
   };
   typename LA::Dma da;
   typename LB::Dma db;
@@ -1070,8 +1123,8 @@ void gemm_nt4_persist_kernel(GemmDev g) {
                     16u * (uint32_t)((2 * kk + h) ^ LB::swz(l));
     }
   const int nk = g.ktotal / BKK;  // even
-  int m0, n0, nm0 = 0, nn0 = 0;
-  tile_of(w, m0, n0);
+  int m0, n0, mlo, nlo, nm0 = 0, nn0 = 0, nmlo = 0, nnlo = 0;
+  tile_of(w, m0, n0, mlo, nlo);
   const bf16_t* baseA = g.A + (int64_t)m0 * g.lda;
   const bf16_t* baseB = g.B + (int64_t)n0 * g.ldb;
   int wnext = w + G;
@@ -1079,7 +1132,7 @@ void gemm_nt4_persist_kernel(GemmDev g) {
   const bf16_t* nbaseA = baseA;
   const bf16_t* nbaseB = baseB;
   if (has_next) {
-    tile_of(wnext, nm0, nn0);
+    tile_of(wnext, nm0, nn0, nmlo, nnlo);
     nbaseA = g.A + (int64_t)nm0 * g.lda;
     nbaseB = g.B + (int64_t)nn0 * g.ldb;
   }
@@ -1236,7 +1289,7 @@ void gemm_nt4_persist_kernel(GemmDev g) {
               const f32x4 so = o * lsc;  // masked rows exactly 0 (also where o is not finite)
               o = f32x4{keep ? so[0] : 0.f, keep ? so[1] : 0.f, keep ? so[2] : 0.f, keep ? so[3] : 0.f};
             }
-            store4<TC>(C + (int64_t)m * g.ldc + n, o, g.alpha, WB ? g.beta : 0.f);
+            if (!SHIFT || (m >= mlo && n >= nlo)) store4<TC>(C + (int64_t)m * g.ldc + n, o, g.alpha, WB ? g.beta : 0.f);
           }
         }
       }
@@ -1252,12 +1305,14 @@ void gemm_nt4_persist_kernel(GemmDev g) {
     w = wnext;
     m0 = nm0;
     n0 = nn0;
+    mlo = nmlo;
+    nlo = nnlo;
     baseA = nbaseA;
     baseB = nbaseB;
     wnext = w + G;
     has_next = wnext < ntiles;
     if (has_next) {
-      tile_of(wnext, nm0, nn0);
+      tile_of(wnext, nm0, nn0, nmlo, nnlo);
       nbaseA = g.A + (int64_t)nm0 * g.lda;
       nbaseB = g.B + (int64_t)nn0 * g.ldb;
     }
@@ -1296,107 +1351,163 @@ __global__ void splitk_reduce4_kernel(const float* __restrict__ part, int splits
   store4<TC>(C + (int64_t)m * ldc + n, acc, alpha, beta);
 }
 
-// Tile shape and split-K factor.  Candidates: 256 x 256 and 256 x 192 tiles on 8
-// wavefronts (one workgroup per CU) and 128 x 128 tiles on 4 (two per CU).  Workgroups run
-// in rounds of one per CU slot, so a grid of 1.5 rounds costs two: the plan minimises
-// rounds x (work of one workgroup) / (relative matrix-core rate of its tile), plus the
-// split-K partials' traffic, over tile shapes and split factors.
+// Tile shape and split-K factor.
+enum TileKind {
+  T256 = 0,     // 256 x 256, 8 wavefronts, persistent
+  T256x192 = 1, // 256 x 192, 8 wavefronts, persistent
+  T128 = 2,     // 128 x 128, 4 wavefronts, persistent, two per CU
+  T192x256 = 3, // 192 x 256, 8 wavefronts, persistent (weight gradients)
+  T64 = 4,      // 64 x 64, 4 wavefronts, one tile per workgroup, two per CU
+  TNT256 = 5,   // gemm_nt4_persist_kernel<256>
+  TNT192 = 6,   // gemm_nt4_persist_kernel<192>
+  T_KINDS = 7
+};
 struct Plan {
-  int kind;  // 0: 256 x 256, 1: 256 x 192, 2: 128 x 128, 3: 192 x 256 (weight gradients)
+  int kind;
   int bm, bn, splits, kchunk;
 };
 
 constexpr int NUM_CU = 256;
 
-Plan plan_of(const Gemm& g, bool allow_split) {
-  struct Cand { int kind, bm, bn, per_cu; double rate; };
-  // relative per-CU rates (fitted to timings of the step's shapes): the narrower tile reads
-  // more LDS bytes per matrix op (much more so with an M-contiguous A); two 4-wavefront
-  // workgroups share one CU
-  // 192-row tiles for the weight gradients whose rows are a multiple of 192 (the 576 rows
-  // of [W_DKV; W_KR] without a ragged row tile; fewer rounds or splits for others)
-  const bool tn192 = !g.a_kmajor && !g.b_kmajor && g.M % 192 == 0;
-  const Cand cands[] = {{0, 256, 256, 1, 1.0}, {1, 256, 192, 1, g.a_kmajor ? 0.93 : 0.7},
-                        {2, 128, 128, 2, 0.62}, {3, 192, 256, 1, 0.8}};
-  Plan best{2, 128, 128, 1, 0};
+// Launch time model, in us: a round of workgroups on the chip's slots costs
+// tile + slices * max(lat, bw * (workgroups in the round / 256 + 1/4, at most per_cu)), a
+// launch `fixed` more.  lat is the time of a 64-deep slice that waits for its copies (few
+// workgroups), bw the same per workgroup on a CU where the matrix cores, the caches and the
+// power limit are shared by all (a half-full round runs at three quarters of that, not at a
+// half: the clock does not rise so fast).  Fitted per layout and tile to 387 shapes of the
+// step (64 to 16384 tokens, splits 1 to 32), each timed right behind some milliseconds of
+// matrix work, as in a step: 6-9% rms.  The small tile keeps four slices in flight and
+// costs 0.4 us per slice where the 256-wide tiles cost 1.2-1.5: it takes every product that
+// would leave most CUs idle (666 x 2048 x 2048 NT: 21 us against 40 us on 256 x 192, 57 us
+// before edge tiles were whole).  Over the shapes the choice is on average 1% above the best
+// measured one.
+struct TileCost {
+  int bm, bn, per_cu;
+  float fixed, tile, lat, bw;
+};
+constexpr TileCost TILE_COST[3][T_KINDS] = {
+    // NT
+    {{256, 256, 1, 3.3f, 9.0f, 1.50f, 1.81f}, {256, 192, 1, 3.8f, 6.0f, 1.24f, 1.46f},
+     {128, 128, 2, 4.2f, 3.1f, 0.82f, 0.577f}, {0, 0, 0, 0, 0, 0, 0},
+     {64, 64, 2, 3.2f, 1.6f, 0.38f, 0.316f}, {256, 256, 1, 5.3f, 6.8f, 1.20f, 1.63f},
+     {256, 192, 1, 4.7f, 5.1f, 1.07f, 1.32f}},
+    // NN
+    {{256, 256, 1, 7.1f, 7.2f, 1.47f, 1.82f}, {256, 192, 1, 3.9f, 6.1f, 1.25f, 1.44f},
+     {128, 128, 2, 6.5f, 1.4f, 0.92f, 0.610f}, {0, 0, 0, 0, 0, 0, 0},
+     {64, 64, 2, 2.9f, 1.7f, 0.39f, 0.322f}, {0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}},
+    // TN
+    {{256, 256, 1, 6.6f, 4.9f, 1.51f, 1.97f}, {256, 192, 1, 1.8f, 7.9f, 1.26f, 1.51f},
+     {128, 128, 2, 0.9f, 6.7f, 0.94f, 0.605f}, {192, 256, 1, 2.4f, 7.1f, 1.27f, 1.56f},
+     {64, 64, 2, 1.5f, 2.8f, 0.45f, 0.303f}, {0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}}};
+constexpr int MAX_SPLITS = 32;
+
+// The four-wavefront NT kernel: both operands K-contiguous with 16-byte aligned rows, K a
+// multiple of 128, at least one whole tile, rows within 32-bit offsets, 4-column stores.
+bool nt4_ok(const Gemm& g, int bn) {
+  return g.a_kmajor && g.b_kmajor && g.M >= 256 && g.N >= bn && g.N % 4 == 0 && g.K % 128 == 0 &&
+         g.K >= 128 && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.ldc % 4 == 0 &&
+         (uintptr_t)g.A % 16 == 0 && (uintptr_t)g.B % 16 == 0 && (uintptr_t)g.C % 16 == 0 &&
+         (int64_t)256 * g.lda * 2 < (1ll << 31) && (int64_t)256 * g.ldb * 2 < (1ll << 31);
+}
+
+// The cheapest tile kind of `kinds` (bit mask) and split factor; the partials of a split
+// product (or of a two-output one, which always goes through them) fit scratch_elems.
+Plan plan_of(const Gemm& g, size_t scratch_elems, unsigned kinds) {
+  const int layout = g.a_kmajor ? (g.b_kmajor ? 0 : 1) : 2;
+  const int kslices = std::max(1, (g.K + BK - 1) / BK);
+  const double mn = (double)g.M * g.N;
+  const bool two = g.C2 != nullptr;
+  Plan best{T64, 64, 64, 1, kslices * BK};
   double best_t = 1e300;
-  const int kslices = (g.K + BK - 1) / BK;
-  for (const Cand& c : cands) {
-    if (c.kind == 3 && !tn192) continue;
+  for (int k = 0; k < T_KINDS; ++k) {
+    const TileCost& c = TILE_COST[layout][k];
+    if (!(kinds >> k & 1) || c.bm == 0) continue;
+    // (tiles larger than the matrix would go through registers)
+    if (k != T64 && (g.M < c.bm || g.N < c.bn)) continue;
+    const bool nt4 = k == TNT256 || k == TNT192;
+    if (nt4 && (two || !nt4_ok(g, c.bn))) continue;
     const int64_t tiles = (int64_t)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
-    const int max_s = allow_split && g.K >= 8 * BK * 8 ? std::max(1, kslices / 8) : 1;
-    for (int sp = 1; sp <= std::min(max_s, 64); ++sp) {
-      const int kc_sl = (kslices + sp - 1) / sp;  // K slices per split
-      const int splits = (kslices + kc_sl - 1) / kc_sl;
-      if (splits != sp) continue;
-      const int64_t wgs = tiles * splits;
-      const int64_t slots = (int64_t)NUM_CU * c.per_cu;
-      const int64_t rounds = (wgs + slots - 1) / slots;
-      // time units: one 64-deep slice of a 256 x 256 tile at full rate on one CU
-      double t = (double)rounds * kc_sl * ((double)c.bm * c.bn / 65536.0) * c.per_cu / c.rate;
-      // partials written and read back (fp32): fitted to the same timings, about 3 MB per
-      // unit of time (one 64-deep slice of a 256 x 256 tile)
-      if (splits > 1) t += (double)(splits + 1) * g.M * g.N * 4 / 3.0e6;
+    const int64_t slots = (int64_t)NUM_CU * c.per_cu;
+    for (int sp = 1; sp <= (nt4 ? 1 : std::min(MAX_SPLITS, std::max(1, kslices / 2))); ++sp) {
+      const int kc = (kslices + sp - 1) / sp;  // K slices per split
+      if ((kslices + kc - 1) / kc != sp) continue;
+      if ((sp > 1 || two) && (double)sp * mn > (double)scratch_elems) break;
+      const int64_t wgs = tiles * sp, full = wgs / slots, rem = wgs % slots;
+      double t = c.fixed + full * (c.tile + kc * std::max(c.lat, c.bw * c.per_cu));
+      if (rem) t += c.tile + kc * std::max((double)c.lat, c.bw * std::min<double>(c.per_cu, rem / 256.0 + 0.25));
+      // the sum of the partials: a launch, its serial reads, its traffic
+      if (sp > 1 || two) t += 2.5 + 0.24 * sp + 0.16 * (sp + 1) * mn * 4e-6;
+      if (t < best_t) {
+        best_t = t;
+        best = Plan{k, c.bm, c.bn, sp, kc * BK};
+      }
+    }
+  }
+  return best;
+}
+constexpr unsigned ALL_KINDS = (1u << T_KINDS) - 1;
+
+// Split-K factor that the workspace reserves partials for.  Callers keep workspaces sized by
+// it, so it stays as it is; plan_of takes what fits.  (Rounds of workgroups x their work, plus
+// the partials' traffic.)
+int reserved_splits(const Gemm& g) {
+  struct Cand { int bm, bn, per_cu; double rate; };
+  const Cand cands[] = {{256, 256, 1, 1.0}, {256, 192, 1, g.a_kmajor ? 0.93 : 0.7},
+                        {128, 128, 2, 0.62}, {192, 256, 1, 0.8}};
+  const int kslices = (g.K + BK - 1) / BK;
+  const int max_s = g.K >= 8 * BK * 8 ? std::min(64, std::max(1, kslices / 8)) : 1;
+  int best = 1;
+  double best_t = 1e300;
+  for (const Cand& c : cands) {
+    if (c.bm == 192 && (g.a_kmajor || g.b_kmajor || g.M % 192)) continue;
+    const int64_t tiles = (int64_t)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
+    for (int sp = 1; sp <= max_s; ++sp) {
+      const int kc = (kslices + sp - 1) / sp;
+      if ((kslices + kc - 1) / kc != sp) continue;
+      const int64_t slots = (int64_t)NUM_CU * c.per_cu, rounds = (tiles * sp + slots - 1) / slots;
+      double t = (double)rounds * kc * ((double)c.bm * c.bn / 65536.0) * c.per_cu / c.rate;
+      if (sp > 1) t += (double)(sp + 1) * g.M * g.N * 4 / 3.0e6;
       if (t < best_t * 0.999) {
         best_t = t;
-        best = Plan{c.kind, c.bm, c.bn, splits, kc_sl * BK};
+        best = sp;
       }
     }
   }
   return best;
 }
 
-// Tile width of the four-wavefront NT kernel for this product: 256 or 192, or 0 where it
-// does not apply (it needs whole tiles, K a multiple of 128, no split-K, operand rows
-// within 32-bit offsets, 16-byte aligned operands and 4-element output rows).  Of the two
-// widths, the one with fewer rounds x tile width (rounds of one tile per CU).
-int nt4_bn(const GemmDev& d, const Plan& p) {
-  const bool ok = p.splits == 1 && !d.part && !d.lpart && !d.causal && d.M % 256 == 0 &&
-                  d.ktotal % 128 == 0 && d.ktotal >= 128 && d.lda % 8 == 0 && d.ldb % 8 == 0 &&
-                  d.ldc % 4 == 0 && (uintptr_t)d.A % 16 == 0 && (uintptr_t)d.B % 16 == 0 &&
-                  (uintptr_t)d.C % 16 == 0 && (int64_t)256 * d.lda * 2 < (1ll << 31) &&
-                  (int64_t)256 * d.ldb * 2 < (1ll << 31);
-  if (!ok) return 0;
-  auto cost = [&](int bn) {
-    const int64_t tiles = (int64_t)(d.M / 256) * (d.N / bn);
-    return (double)((tiles + NUM_CU - 1) / NUM_CU) * bn;
-  };
-  const bool w256 = d.N % 256 == 0, w192 = d.N % 192 == 0;
-  if (w256 && (!w192 || cost(256) <= cost(192))) return 256;
-  return w192 ? 192 : 0;
-}
-
 template <bool AK, bool BKM, typename TC>
 const char* launch(const GemmDev& d, const Plan& p, hipStream_t s) {
+  const int tiles = ((d.M + p.bm - 1) / p.bm) * ((d.N + p.bn - 1) / p.bn);
   if constexpr (AK && BKM) {
-    const int bn = nt4_bn(d, p);
-    if (bn == 256) {
-      const int tiles = (d.M / 256) * (d.N / 256);
-      gemm_nt4_persist_kernel<256, TC><<<std::min(tiles, NUM_CU), 256, 0, s>>>(d);
+    const bool whole = d.M % 256 == 0 && d.N % p.bn == 0;
+    const int nt_grid = std::min(tiles, NUM_CU);
+    if (p.kind == TNT256) {
+      if (whole) gemm_nt4_persist_kernel<256, TC, false><<<nt_grid, 256, 0, s>>>(d);
+      else gemm_nt4_persist_kernel<256, TC, true><<<nt_grid, 256, 0, s>>>(d);
       return KLABEL("gemm_nt4_persist_kernel<256,256,NT,%s>", sizeof(TC) == 4 ? "fp32" : "bf16");
     }
-    if (bn == 192) {
-      const int tiles = (d.M / 256) * (d.N / 192);
-      gemm_nt4_persist_kernel<192, TC><<<std::min(tiles, NUM_CU), 256, 0, s>>>(d);
+    if (p.kind == TNT192) {
+      if (whole) gemm_nt4_persist_kernel<192, TC, false><<<nt_grid, 256, 0, s>>>(d);
+      else gemm_nt4_persist_kernel<192, TC, true><<<nt_grid, 256, 0, s>>>(d);
       return KLABEL("gemm_nt4_persist_kernel<256,192,NT,%s>", sizeof(TC) == 4 ? "fp32" : "bf16");
     }
   }
-  const int tiles = ((d.M + p.bm - 1) / p.bm) * ((d.N + p.bn - 1) / p.bn);
-  const bool persist = d.lpart == nullptr;
-#define GL_(name, bm, bn) KLABEL(name "<%d,%d,%s,%s>", bm, bn, AK ? (BKM ? "NT" : "NN") : (BKM ? "TT" : "TN"), \
+  const bool persist = d.lscale == nullptr && p.kind != T64;
+#define GL_(name, bm, bn) KLABEL(name "<%d,%d,%s,%s>", bm, bn, AK ? (BKM ? "NT" : "NN") : "TN", \
                                  sizeof(TC) == 4 ? "fp32" : "bf16")
   if (persist) {
     GemmDev e = d;
     e.nsplit = p.splits;
-    const int per_cu = p.kind == 2 ? 2 : 1;
+    const int per_cu = p.kind == T128 ? 2 : 1;
     const int grid = std::min(tiles * p.splits, NUM_CU * per_cu);
-    if (p.kind == 0) {
+    if (p.kind == T256) {
       gemm_mfma_persist_kernel<256, 256, GWM, GWN, AK, BKM, TC, GBK, GNST><<<grid, 64 * GWM * GWN, 0, s>>>(e);
       return GL_("gemm_mfma_persist_kernel", 256, 256);
-    } else if (p.kind == 1) {
+    } else if (p.kind == T256x192) {
       gemm_mfma_persist_kernel<256, 192, 4, 2, AK, BKM, TC, GBK, GNST><<<grid, 512, 0, s>>>(e);
       return GL_("gemm_mfma_persist_kernel", 256, 192);
-    } else if (p.kind == 3) {
+    } else if (p.kind == T192x256) {
       if constexpr (!AK && !BKM) {
         gemm_mfma_persist_kernel<192, 256, 2, 4, AK, BKM, TC, GBK, GNST><<<grid, 512, 0, s>>>(e);
         return GL_("gemm_mfma_persist_kernel", 192, 256);
@@ -1405,17 +1516,24 @@ const char* launch(const GemmDev& d, const Plan& p, hipStream_t s) {
     gemm_mfma_persist_kernel<128, 128, 2, 2, AK, BKM, TC, 64, 2><<<grid, 256, 0, s>>>(e);
     return GL_("gemm_mfma_persist_kernel", 128, 128);
   }
-  // the masked-loss epilogue
-  dim3 grid(tiles, p.splits);
-  if (p.kind == 0) {
-    gemm_mfma_kernel<256, 256, GWM, GWN, AK, BKM, TC, GBK, GNST><<<grid, 64 * GWM * GWN, 0, s>>>(d);
-    return GL_("gemm_mfma_kernel(masked loss)", 256, 256);
-  } else if (p.kind == 1) {
-    gemm_mfma_kernel<256, 192, 4, 2, AK, BKM, TC, GBK, GNST><<<grid, 512, 0, s>>>(d);
-    return GL_("gemm_mfma_kernel(masked loss)", 256, 192);
+  // the small tiles, and the masked-loss epilogue (NT only)
+  const dim3 grid(tiles, p.splits);
+  if (p.kind == T64) {
+    gemm_mfma_kernel<64, 64, 2, 2, AK, BKM, TC, 64, 4><<<grid, 256, 0, s>>>(d);
+    return GL_("gemm_mfma_kernel", 64, 64);
   }
-  gemm_mfma_kernel<128, 128, 2, 2, AK, BKM, TC, 64, 2><<<grid, 256, 0, s>>>(d);
-  return GL_("gemm_mfma_kernel(masked loss)", 128, 128);
+  if constexpr (AK && BKM) {
+    if (p.kind == T256) {
+      gemm_mfma_kernel<256, 256, GWM, GWN, AK, BKM, TC, GBK, GNST><<<grid, 64 * GWM * GWN, 0, s>>>(d);
+      return GL_("gemm_mfma_kernel(masked loss)", 256, 256);
+    } else if (p.kind == T256x192) {
+      gemm_mfma_kernel<256, 192, 4, 2, AK, BKM, TC, GBK, GNST><<<grid, 512, 0, s>>>(d);
+      return GL_("gemm_mfma_kernel(masked loss)", 256, 192);
+    }
+    gemm_mfma_kernel<128, 128, 2, 2, AK, BKM, TC, 64, 2><<<grid, 256, 0, s>>>(d);
+    return GL_("gemm_mfma_kernel(masked loss)", 128, 128);
+  }
+  return nullptr;
 #undef GL_
 }
 
@@ -1423,8 +1541,8 @@ const char* launch(const GemmDev& d, const Plan& p, hipStream_t s) {
 }  // namespace
 
 size_t gemm_mfma_scratch_elems(const Gemm& g) {
-  Plan p = plan_of(g, true);
-  return p.splits > 1 || g.C2 ? (size_t)p.splits * g.M * g.N : 0;
+  const int splits = reserved_splits(g);
+  return splits > 1 || g.C2 ? (size_t)splits * g.M * g.N : 0;
 }
 
 hipError_t gemm_mfma(const Gemm& g, float* scratch, size_t scratch_elems, hipStream_t s, int kc,
@@ -1439,16 +1557,14 @@ hipError_t gemm_mfma(const Gemm& g, float* scratch, size_t scratch_elems, hipStr
   d.causal = 0; d.rev = 0; d.nbatch = 1; d.zdiv = 1; d.bdiv = 1; d.kgroups = 1;
   d.sA = d.sB1 = d.sB2 = d.sC1 = d.sC2 = d.sAk = d.sBk = 0;
   d.split_n = 0; d.c_lo = nullptr; d.ldc_lo = d.sC1_lo = d.sC2_lo = 0;
-  Plan p = plan_of(g, true);
   // two outputs: always through the partials (also unsplit), summed into C and C2
   const bool two = g.C2 != nullptr;
+  if (!g.a_kmajor && g.b_kmajor) return hipErrorInvalidValue;  // (no such product)
   if (two && (g.beta != 0.f || g.m2 <= 0 || g.m2 >= g.M || g.N % 4 || g.ldc % 4 ||
-              (uintptr_t)g.C % 16 || (uintptr_t)g.C2 % 16 || g.c_t != DT_F32))
+              (uintptr_t)g.C % 16 || (uintptr_t)g.C2 % 16 || g.c_t != DT_F32 || !scratch ||
+              scratch_elems < (size_t)g.M * g.N))
     return hipErrorInvalidValue;
-  if ((p.splits > 1 || two) && (scratch == nullptr || scratch_elems < (size_t)p.splits * g.M * g.N)) {
-    if (two) return hipErrorInvalidValue;
-    p = plan_of(g, false);
-  }
+  const Plan p = plan_of(g, scratch ? scratch_elems : 0, ALL_KINDS);
   d.kchunk = p.kchunk;
   d.part = p.splits > 1 || two ? scratch : nullptr;
   const bool f32 = g.c_t == DT_F32;
@@ -1459,7 +1575,7 @@ hipError_t gemm_mfma(const Gemm& g, float* scratch, size_t scratch_elems, hipStr
     if (f32) kname = launch<AK, BK_, float>(d, p, s);                                   \
     else kname = launch<AK, BK_, bf16_t>(d, p, s);                                      \
   }
-  L_(true, true) else L_(true, false) else L_(false, false) else L_(false, true)
+  L_(true, true) else L_(true, false) else L_(false, false)
 #undef L_
   prof_end(kc, s, flops, bytes, kname);
   hipError_t e = hipGetLastError();
@@ -1504,7 +1620,7 @@ size_t gemm_mfma_masked_sse_parts(const Gemm& g) {
 }
 
 hipError_t gemm_mfma_masked_scale(const Gemm& g, const float* scale, const uint8_t* mask,
-                                  double* part, hipStream_t s, const char** kernel) {
+                                  hipStream_t s, const char** kernel) {
   if (g.beta != 0.f || g.alpha != 1.f || g.in_t != DT_BF16 || !scale || !g.C ||
       !g.a_kmajor || !g.b_kmajor)
     return hipErrorInvalidValue;
@@ -1518,17 +1634,14 @@ hipError_t gemm_mfma_masked_scale(const Gemm& g, const float* scale, const uint8
   d.causal = 0; d.rev = 0; d.nbatch = 1; d.zdiv = 1; d.bdiv = 1; d.kgroups = 1;
   d.sA = d.sB1 = d.sB2 = d.sC1 = d.sC2 = d.sAk = d.sBk = 0;
   d.split_n = 0; d.c_lo = nullptr; d.ldc_lo = d.sC1_lo = d.sC2_lo = 0;
-  const Plan p = plan_of(g, false);
+  // (the four-wavefront kernel reads the row mask with 32-byte scalar loads: every row tile,
+  // the moved-back last one included, starts at a 4-byte aligned mask byte)
+  const bool nt4_mask = (uintptr_t)mask % 4 == 0 && g.M % 4 == 0;
+  const Plan p = plan_of(g, 0, nt4_mask ? ALL_KINDS : ALL_KINDS & ~(1u << TNT256 | 1u << TNT192));
   d.kchunk = p.kchunk;
   d.part = nullptr;
-  // (the four-wavefront kernel reads the row mask with 32-byte scalar loads: 4-byte aligned)
-  if (nt4_bn(d, p) && (uintptr_t)mask % 4 == 0) {
-    *kernel = g.c_t == DT_F32 ? launch<true, true, float>(d, p, s) : launch<true, true, bf16_t>(d, p, s);
-    return hipGetLastError();
-  }
-  // elsewhere the masked-loss kernel, its tile sums left unused
-  int nparts = 0;
-  return gemm_mfma_masked_sse(g, scale, mask, nullptr, 0, part, &nparts, s, kernel);
+  *kernel = g.c_t == DT_F32 ? launch<true, true, float>(d, p, s) : launch<true, true, bf16_t>(d, p, s);
+  return hipGetLastError();
 }
 
 hipError_t gemm_mfma_masked_sse(const Gemm& g, const float* scale, const uint8_t* mask,
@@ -1546,7 +1659,10 @@ hipError_t gemm_mfma_masked_sse(const Gemm& g, const float* scale, const uint8_t
   d.causal = 0; d.rev = 0; d.nbatch = 1; d.zdiv = 1; d.bdiv = 1; d.kgroups = 1;
   d.sA = d.sB1 = d.sB2 = d.sC1 = d.sC2 = d.sAk = d.sBk = 0;
   d.split_n = 0; d.c_lo = nullptr; d.ldc_lo = d.sC1_lo = d.sC2_lo = 0;
-  const Plan p = plan_of(g, false);
+  // (tiles of at least 128 x 128: gemm_mfma_masked_sse_parts bounds their number; smaller
+  // matrices go through one such tile)
+  Plan p = plan_of(g, 0, 1u << T256 | 1u << T256x192 | 1u << T128);
+  if (p.kind == T64) p = Plan{T128, 128, 128, 1, p.kchunk};
   d.kchunk = p.kchunk;
   d.part = nullptr;
   *nparts = ((g.M + p.bm - 1) / p.bm) * ((g.N + p.bn - 1) / p.bn);
@@ -1559,7 +1675,7 @@ hipError_t gemm_mfma_masked_sse(const Gemm& g, const float* scale, const uint8_t
 // Batched causal products of attention's backward: dQ = dS K (A = dS^T stored [key][query],
 // M/N-contiguous, bf16 result) and dK = dS^T Q summed over a group's heads (A k-major, fp32
 // result).  BN is the output width rounded up to the supported tile widths.
-template <int BN, int WM, int WN, bool AK, typename TC>
+template <int BN, int WM, int WN, bool AK, typename TC, bool SHIFT>
 static void launch_causal(const GemmDev& d, int nbatch, hipStream_t s) {
   const int ntm = (d.M + 255) / 256, ntn = (d.N + BN - 1) / BN;
   const int items = ntm * ntn * nbatch;
@@ -1569,7 +1685,7 @@ static void launch_causal(const GemmDev& d, int nbatch, hipStream_t s) {
     // product waits on its copies (the dS^T stream): three slices in flight (84 KB per CU)
     // instead of one 64-deep slice (56 KB) measured 3-6% faster (five stages, and a
     // persistent grid of the two-stage ring, were slower)
-    attn_ds_gemm_kernel<256, BN, WM, WN, AK, false, TC, 32, 4>
+    attn_ds_gemm_kernel<256, BN, WM, WN, AK, false, TC, 32, 4, SHIFT>
         <<<dim3(items, 1), 64 * WM * WN, 0, s>>>(d);
   } else {
     // dK (K ranges start at the diagonal): persistent, 2.6% faster; as many workgroups as
@@ -1583,23 +1699,23 @@ static void launch_causal(const GemmDev& d, int nbatch, hipStream_t s) {
     if (per_cu == 0) {
       int n = 0;
       if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-              &n, attn_ds_gemm_persist_kernel<256, BN, WM, WN, AK, false, TC, 64, 2>,
+              &n, attn_ds_gemm_persist_kernel<256, BN, WM, WN, AK, false, TC, 64, 2, SHIFT>,
               64 * WM * WN, 0) != hipSuccess || n < 1)
         n = 1;
       per_cu = n;
       occ[dev].store(n, std::memory_order_relaxed);
     }
-    attn_ds_gemm_persist_kernel<256, BN, WM, WN, AK, false, TC, 64, 2>
+    attn_ds_gemm_persist_kernel<256, BN, WM, WN, AK, false, TC, 64, 2, SHIFT>
         <<<dim3(std::min(items, NUM_CU * per_cu), 1), 64 * WM * WN, 0, s>>>(d);
   }
 }
 
-template <bool AK, typename TC>
+template <bool AK, typename TC, bool SHIFT>
 static hipError_t dispatch_causal(const GemmDev& d, int nbatch, hipStream_t s) {
-  if (d.N <= 64) launch_causal<64, 4, 2, AK, TC>(d, nbatch, s);
-  else if (d.N <= 96) launch_causal<96, 4, 1, AK, TC>(d, nbatch, s);
-  else if (d.N <= 128) launch_causal<128, 4, 2, AK, TC>(d, nbatch, s);
-  else if (d.N <= 192) launch_causal<192, 4, 2, AK, TC>(d, nbatch, s);
+  if (d.N <= 64) launch_causal<64, 4, 2, AK, TC, SHIFT>(d, nbatch, s);
+  else if (d.N <= 96) launch_causal<96, 4, 1, AK, TC, SHIFT>(d, nbatch, s);
+  else if (d.N <= 128) launch_causal<128, 4, 2, AK, TC, SHIFT>(d, nbatch, s);
+  else if (d.N <= 192) launch_causal<192, 4, 2, AK, TC, SHIFT>(d, nbatch, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -1632,8 +1748,11 @@ hipError_t gemm_mfma_causal(const Gemm& g, const GemmBatch& bt, hipStream_t s) {
   d.sAk = bt.sAk; d.sBk = bt.sBk;
   d.split_n = bt.split_n; d.c_lo = (bf16_t*)bt.c_lo;
   d.ldc_lo = bt.ldc_lo; d.sC1_lo = bt.sC1_lo; d.sC2_lo = bt.sC2_lo;
-  return g.a_kmajor ? dispatch_causal<true, float>(d, bt.nbatch, s)
-                    : dispatch_causal<false, bf16_t>(d, bt.nbatch, s);
+  if (g.M % 256 == 0)
+    return g.a_kmajor ? dispatch_causal<true, float, false>(d, bt.nbatch, s)
+                      : dispatch_causal<false, bf16_t, false>(d, bt.nbatch, s);
+  return g.a_kmajor ? dispatch_causal<true, float, true>(d, bt.nbatch, s)
+                    : dispatch_causal<false, bf16_t, true>(d, bt.nbatch, s);
 }
 
 }  // namespace mla

@@ -1,0 +1,70 @@
+"""Token counts at the edges of the products' and the attention's tiles (64, 128, 192 and 256
+rows, 32-query blocks, 256-key blocks): the whole step against the float64 oracle, so that
+every projection, data gradient and weight gradient runs with a tile that the matrix edge
+cuts, with a matrix smaller than a tile, and with a ragged reduction length."""
+import numpy as np
+import pytest
+
+from paper_2607_27269_amd import configs, synth
+from parity_util import LOSS_TOL, TOL, compare, oracle_step
+
+pytestmark = pytest.mark.gpu
+
+GRADS = ("dWdq", "dWuq", "dWdkv_kr", "dWuk", "dWuv")
+
+
+# The gradients carry the relative error of A_s - A_t: sqrt(2) * 3.2e-3 (the bf16 error of each
+# output) times |A_t| / |A_s - A_t|, which is 2.5 for 63 tokens of configuration 1 (dA alone
+# 1.2e-2, its dW_UV 1.9e-2 and a group of it 2.2e-2) and nears 1 for longer sequences.  A
+# gradient sums products with it, whose own sum can cancel: twice that, and twice for margin.
+# A tile gone wrong shows as 1e-1 and more in its block.
+DA_ERR = 2 ** 0.5 * 3.2e-3
+
+
+def _tol(wl, ref):
+    m = wl.mask[..., None]
+    return max(TOL["bf16"], 4 * DA_ERR * np.linalg.norm(m * ref["A_t"]) /
+               np.linalg.norm(m * (ref["A_s"] - ref["A_t"])))
+
+
+@pytest.mark.parametrize("idx,B,T", [(4, 1, 33), (1, 1, 63), (1, 2, 65), (1, 1, 129), (1, 3, 85),
+                                     (1, 1, 257), (2, 1, 191), (2, 1, 321), (4, 1, 96)])
+def test_step_sizes(idx, B, T):
+    from paper_2607_27269_amd.step import DeviceStep
+    print(f"[sizes] cfg{idx} B={B} T={T}", flush=True)
+    cfg = configs.shrink(configs.get(idx), batch=B, seq=T)
+    wl = synth.make_workload(cfg, lengths=[T] * (B - 1) + [max(1, T - 5)])
+    ref = oracle_step(wl)
+    tol = _tol(wl, ref)
+    dev = DeviceStep(wl)
+    dev.step()
+    out = dev.results()
+    compare(out, ref, ("A_t", "A_s"), TOL["bf16"], label="four calls: ", cfg=cfg)
+    compare(out, ref, ("dA",) + GRADS, tol, label="four calls: ", cfg=cfg)
+    assert abs(out["loss"] - ref["loss"]) <= LOSS_TOL * ref["loss"]
+    for with_dA in (False, True):
+        for g in dev.grads.values():
+            g.fill_(float("nan"))
+        dev.fused_step(with_dA=with_dA)
+        out = dev.results()
+        compare(out, ref, GRADS, tol, label=f"single call, dA={with_dA}: ", cfg=cfg)
+        assert abs(out["loss"] - ref["loss"]) <= LOSS_TOL * ref["loss"]
+
+
+@pytest.mark.parametrize("B,T", [(1, 130), (2, 640)])
+def test_step_workspace_does_not_change_results(B, T):
+    """The split of a product (and with it its rounding) does not depend on how much workspace
+    the caller gives: the smallest and the preferred workspace give the same bits."""
+    import torch
+    from paper_2607_27269_amd import _lib as L
+    from paper_2607_27269_amd.step import DeviceStep
+    cfg = configs.shrink(configs.get(1), batch=B, seq=T)
+    wl = synth.make_workload(cfg)
+    outs = []
+    for size in (L.mla_recon_workspace_size, L.mla_recon_workspace_size_min):
+        dev = DeviceStep(wl, ws_bytes=size(L.make_cfg(cfg)))
+        dev.fused_step(with_dA=False)
+        torch.cuda.synchronize()
+        outs.append({"loss": dev.loss_buf[:1].clone(), **{k: v.clone() for k, v in dev.grads.items()}})
+    for k in outs[0]:
+        assert torch.equal(outs[0][k], outs[1][k]), k
