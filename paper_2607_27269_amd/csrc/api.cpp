@@ -130,7 +130,7 @@ static int check_cfg(const mla_recon_cfg* c) {
 static size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-  // teacher scratch
+  // teacher scratch (t_qkv sits among the backward's regions)
   size_t t_cos, t_sin, t_qkv, t_o;
   // student state kept from student_fwd to bwd
   size_t s_cos, s_sin, s_cq, s_q, s_ckv, s_knope, s_v, s_o, s_lse;
@@ -162,7 +162,6 @@ static Layout layout_of(const Dims& d, int chunk) {
   const size_t ts = d.ts, N = d.N;
   L.t_cos = take(d.T * (d.dk / 2) * 4);
   L.t_sin = take(d.T * (d.dk / 2) * 4);
-  L.t_qkv = take(N * (d.H + 2 * d.G) * d.dk * ts);
   L.t_o = take(N * d.H * d.dk * ts);
   L.s_cos = take(d.Gr * d.T * (d.dr / 2) * 4);
   L.s_sin = take(d.Gr * d.T * (d.dr / 2) * 4);
@@ -176,9 +175,13 @@ static Layout layout_of(const Dims& d, int chunk) {
   L.b_do = take(N * d.H * d.dv * ts);
   L.b_delta = take(N * d.H * 4);
   L.b_dqacc = take(d.t == DT_F32 ? N * d.H * d.dqk * 4 : 0);
-  L.b_dq = take(N * d.H * d.dqk * ts);
   L.b_dkv = take(N * d.Gkv * (d.dn + d.dv) * ts);
   L.b_dkpe = take(d.Gkv * N * d.dr * 4);
+  // dq .. split, side by side: before dQ is written, everything from a chunk's first dq row to
+  // the end of split is free for the attention backward's per-head partials (the teacher's
+  // projections, and o_s - o_t in their place, are read no more by then)
+  L.b_dq = take(N * d.H * d.dqk * ts);
+  L.t_qkv = take(N * (d.H + 2 * d.G) * d.dk * ts);
   L.b_dckv = take(N * d.kv_out * ts);
   L.b_dcq = take(N * d.rq * ts);
   size_t se = 0;
@@ -246,9 +249,10 @@ struct Scratch {
   float* p;
   size_t elems;
 };
-// forward products: the backward's regions, none of which is live before the backward
+// forward products: the backward's regions up to the teacher's projections, none of which is
+// live before the backward
 static Scratch fwd_scratch(const Layout& L, void* ws) {
-  return {(float*)at(ws, L.b_do), (L.l_scr - L.b_do) / 4};
+  return {(float*)at(ws, L.b_do), (L.t_qkv - L.b_do) / 4};
 }
 // backward products once the attention's backward is done: the largest of the reserved
 // partials, the teacher's projections, dO and delta, and one sequence's dS^T
@@ -257,7 +261,7 @@ static Scratch bwd_scratch(const Dims& d, const Layout& L, void* ws) {
   auto better = [&](size_t off, size_t bytes) {
     if (bytes / 4 > s.elems) s = {(float*)at(ws, off), bytes / 4};
   };
-  better(L.t_qkv, L.t_o - L.t_qkv);
+  better(L.t_qkv, L.b_dckv - L.t_qkv);
   better(L.b_do, L.b_dqacc - L.b_do);
   if (L.chunk) better(L.b_ds, attn_ds_bytes(1, (int)d.H, (int)d.T));
   return s;
@@ -500,7 +504,7 @@ static int bwd_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
 
   // dO = dA W_O  (W_O frozen: no dW_O); without dA, dO is already in place (its partials: the
   // gradient regions that follow dO and delta, not yet written)
-  const Scratch sk_do = {(float*)at(ws, L.b_dqacc), (L.l_scr - L.b_dqacc) / 4};
+  const Scratch sk_do = {(float*)at(ws, L.b_dqacc), (L.t_qkv - L.b_dqacc) / 4};
   if (dA)
     HIP_TRY(gemm(mk(N, H * dv, D, dA, D, true, Wo, (int64_t)H * dv, false, dO, (int64_t)H * dv, t, t), sk_do.p, sk_do.elems, s));
   // softmax-attention backward -> dq (rotary block rotated back), dk^nope, dv, dk^PE partials
@@ -521,6 +525,7 @@ static int bwd_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
   ab.kcat = L.b_ds_bytes ? at(ws, L.b_kcat) : nullptr;
   ab.statT = L.b_ds_bytes ? (float*)at(ws, L.b_statT) : nullptr;
   ab.chunk_seqs = L.chunk;
+  ab.part_bytes = L.l_scr - L.b_dq;
   ab.loss_ref = loss_ref;
   ab.loss_part = loss_part;
   HIP_TRY(attn_bwd(ab, s));

@@ -116,6 +116,9 @@ struct AttnBwd {
   void* kcat;                // B' T * n_ka_groups * dqk bf16
   float* statT;              // attn_stats_bytes(B', f.H, f.T)
   int chunk_seqs;            // B' (>= 1, at most attn_bwd_chunk_seqs)
+  // bytes free at dq (dq included) until dQ is written: fp32 partials of dV and dK where the
+  // heads of a group are split over workgroups
+  size_t part_bytes = 0;
   // optional (bf16, dv % 8 == 0): with loss_ref [N, H*dv] (row stride H*dv) set, the delta
   // pass also leaves in loss_part[attn_delta_parts(N * H)] the fixed-order partial sums of
   // dO . loss_ref, one per workgroup
