@@ -8,9 +8,10 @@
 // with key width r_kv + d_rope, value width r_kv (the latent itself) and all H heads in one
 // MFMA column block, followed by a per-group projection.
 //
-// Kernels:
-// * group_gemm_kernel (+ absorb_rest_kernel): the absorbed queries [B][HP][DK] bf16 (heads
-//   padded to HP = 32k), the latent part as one product per KV group.
+// Kernels (three launches: with short caches the launches are most of the time):
+// * absorb_kernel: the absorbed queries [B][HP][DK] bf16 (heads padded to HP = 32k; padding
+//   rows are left as they are: every head is a column of its own from here on, and a padding
+//   head's partials are not stored), the latent part as one matrix-core product per KV group.
 // * decode_attn_kernel: split-K over the cache (flash-decoding).  A workgroup (4 waves)
 //   owns one (sequence, key chunk, block of 32 heads).  Key tiles of 32 rows are copied
 //   straight into LDS in a ring of three stages (two tiles in flight).  The
@@ -22,8 +23,8 @@
 //   Each wave then updates O^T += V^T P^T for its quarter of the latent width; V^T is the
 //   tile's latent columns read with the transposing LDS read.  Partial (max, sum,
 //   unnormalised output) per split.
-// * decode_combine_kernel: merges the splits of a (sequence, head) in split order.
-// * uv_proj_kernel: o = W_UV[g] (latent), one thread per output.
+// * decode_finish_kernel: merges the splits of 8 sequences of a head and applies W_UV on the
+//   matrix cores.
 #include <mutex>
 
 #include "attn_common.h"
@@ -76,93 +77,73 @@ struct DecodeDev {
   int64_t seq_stride;   // Lmax * ldc
   int ldc;              // row stride of the cache (elements)
   const int32_t* len;   // [B]
-  int Lmax, HP, nsplit, chunk;
+  int Lmax, H, HP, nsplit, chunk;
   float sl2;            // softmax scale * log2(e)
   float* part_o;        // [B][nsplit][HP][DVL]
   float* part_ml;       // [B][nsplit][HP][2]
 };
 
-// The query absorption as one product per KV group, C[r][n] = sum_k A[r][k] W_g[k][n] for
-// the H / G_kv heads of group g = blockIdx.z and sequences b: row r = (b, j) is head
-// i = g hpg + j of sequence b (A row at A + (b H + i) lda, C row at C + (b HC + i) ldc),
-// W_g = W + g K N (W_UK[g] = Wuk[g K + k][n]).  32 x 32 output tiles (enough workgroups for these small products), K
-// in chunks of 32 staged in LDS as fp32; each of the 256 threads owns 2 x 2 outputs.  fp32
-// accumulation in k order, bf16 output.
-template <typename TA>
-__global__ __launch_bounds__(256) void group_gemm_kernel(const TA* __restrict__ A, int64_t lda,
-                                                         const bf16_t* __restrict__ W,
-                                                         bf16_t* __restrict__ C, int64_t ldc,
-                                                         int HC, int B, int H, int hpg, int K,
-                                                         int N) {
-  constexpr int TR = 32, TN = 32, TK = 32;
-  __shared__ float As[TK][TR + 1];
-  __shared__ float Ws[TK][TN + 1];
-  const int g = blockIdx.z, n0 = blockIdx.x * TN, r0 = blockIdx.y * TR;
-  const int rows = B * hpg;
-  const int tid = threadIdx.x, tr = tid / 16, tn = tid % 16;
-  const bf16_t* Wg = W + (int64_t)g * K * N;
-  float acc[2][2] = {};
-  for (int k0 = 0; k0 < K; k0 += TK) {
-    // A tile: 32 rows x 32 k, transposed into As[k][r]
-    for (int e = tid; e < TR * TK; e += 256) {
-      const int r = e / TK, k = e % TK, rr = r0 + r, kk = k0 + k;
-      float v = 0.f;
-      if (rr < rows && kk < K) {
-        const int b = rr / hpg, i = g * hpg + rr % hpg;
-        v = ld(A + ((int64_t)b * H + i) * lda + kk);
-      }
-      As[k][r] = v;
+// The absorbed queries of the heads of group g = blockIdx.z: row r = (b, j) of the
+// B hpg rows is head i = g hpg + j of sequence b; qabs[b][i][c] = sum_d q[b][i][d] W_UK[g][d][c]
+// for c < rkv, then the rotary part copied.  A workgroup (two wavefronts) makes 32 rows x 64
+// columns; W_UK's 64 columns are staged in LDS as they lie ([d][c]) and read transposed
+// (MFMA row = c), the query rows come straight from memory (MFMA column = row), so that a
+// lane ends with 4 consecutive c of its row: 8-byte stores.  Bound by latency (W_UK is 1 MB at
+// H = 32, r_kv = 512; one round of small workgroups), fp32 accumulation.  Measured with the
+// rotary copy: 64 sequences 26 -> 9.0 us, one sequence 13.6 -> 4.1 us (a vector-ALU product and
+// a copy launch before).
+constexpr int ABS_LD = 96;  // LDS row stride: 4 rows of a transposing read on distinct banks
+constexpr int ABS_DN = 192;
+__global__ __launch_bounds__(128) void absorb_kernel(const bf16_t* __restrict__ q,
+                                                     const bf16_t* __restrict__ Wuk,
+                                                     bf16_t* __restrict__ qabs, int B, int H, int HP,
+                                                     int hpg, int dn, int dr, int rkv) {
+  __shared__ __attribute__((aligned(16))) bf16_t Ws[ABS_DN * ABS_LD];
+  const int g = blockIdx.z, c0 = 64 * blockIdx.x, r0 = 32 * blockIdx.y;
+  const int DK = rkv + dr, dq = dn + dr, tid = threadIdx.x;
+  const int lane = tid & 63, wave = wave_id(), half = lane >> 5, col = lane & 31;
+  const int dnp = (dn + 15) & ~15;  // d rounded up to the K step, zero filled
+  const bf16_t* Wg = Wuk + (int64_t)g * dn * rkv + c0;
+  if ((uintptr_t)Wuk % 16 == 0) {  // uniform
+    for (int e = tid; e < dnp * 8; e += 128) {
+      const int d = e >> 3, c = 8 * (e & 7);
+      *(u32x4*)(Ws + d * ABS_LD + c) = d < dn ? *(const u32x4*)(Wg + (int64_t)d * rkv + c) : u32x4{0u, 0u, 0u, 0u};
     }
-    // W tile: 32 k x 32 n
-    for (int e = tid; e < TK * TN; e += 256) {
-      const int k = e / TN, n = e % TN, kk = k0 + k, nn = n0 + n;
-      Ws[k][n] = kk < K && nn < N ? bf2f(Wg[(int64_t)kk * N + nn]) : 0.f;
+  } else {
+    for (int e = tid; e < dnp * 64; e += 128) {
+      const int d = e >> 6, c = e & 63;
+      Ws[d * ABS_LD + c] = d < dn ? Wg[(int64_t)d * rkv + c] : (bf16_t)0;
     }
-    __syncthreads();
-#pragma unroll 8
-    for (int k = 0; k < TK; ++k) {
-      const float a0 = As[k][tr], a1 = As[k][tr + 16], w0 = Ws[k][tn], w1 = Ws[k][tn + 16];
-      acc[0][0] += a0 * w0;
-      acc[0][1] += a0 * w1;
-      acc[1][0] += a1 * w0;
-      acc[1][1] += a1 * w1;
-    }
-    __syncthreads();
   }
+  const int rows = B * hpg, rr = r0 + col, rc = min(rr, rows - 1);
+  const int64_t bi = (int64_t)(rc / hpg) * H + g * hpg + rc % hpg;           // row of q
+  const int64_t qi = (int64_t)(rc / hpg) * HP + g * hpg + rc % hpg;          // row of qabs
+  const bf16_t* qp = q + bi * dq + 8 * half;
+  bf16x8 qf[ABS_DN / 16];  // this lane's row, asked for before the staging's barrier
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int rr = r0 + tr + 16 * u;
-    if (rr >= rows) continue;
-    const int b = rr / hpg, i = g * hpg + rr % hpg;
+  for (int kk = 0; kk < ABS_DN / 16; ++kk) {
+    u32x4 w = {0u, 0u, 0u, 0u};
+    if (16 * kk + 8 * half < dn) w = *(const u32x4*)(qp + 16 * kk);
+    qf[kk] = __builtin_bit_cast(bf16x8, w);
+  }
+  if (blockIdx.x == 0 && wave == 0 && rr < rows)  // rotary part: dr elements, half a row per lane
+    for (int c = 8 * half; c < dr; c += 16)
+      *(u32x4*)(qabs + qi * DK + rkv + c) = *(const u32x4*)(q + bi * dq + dn + c);
+  __syncthreads();
+  f32x16 acc;
 #pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      const int nn = n0 + tn + 16 * v;
-      if (nn < N) C[((int64_t)b * HC + i) * ldc + nn] = f2bf(acc[u][v]);
-    }
-  }
-}
-
-// The rest of the absorbed queries [B][HP][DK]: the rotary part copied from q, and zero
-// rows for the padding heads i >= H (the latent part of heads < H comes from the group
-// product).
-__global__ void absorb_rest_kernel(const bf16_t* __restrict__ q, bf16_t* __restrict__ qabs, int B,
-                                   int H, int HP, int dn, int dr, int rkv) {
-  const int DK = rkv + dr;
-  const int64_t n_rope = (int64_t)B * H * dr;
-  const int64_t n_pad = (int64_t)B * (HP - H) * DK;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < n_rope) {
-    const int c = (int)(idx % dr);
-    const int64_t bi = idx / dr;  // b * H + i
-    const int b = (int)(bi / H), i = (int)(bi % H);
-    qabs[((int64_t)b * HP + i) * DK + rkv + c] = q[bi * (dn + dr) + dn + c];
-  } else if (idx < n_rope + n_pad) {
-    const int64_t e = idx - n_rope;
-    const int c = (int)(e % DK);
-    const int64_t bp = e / DK;
-    const int b = (int)(bp / (HP - H)), i = H + (int)(bp % (HP - H));
-    qabs[((int64_t)b * HP + i) * DK + c] = (bf16_t)0;
-  }
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < ABS_DN / 16; ++kk)
+    if (16 * kk < dnp)  // uniform
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+          lds_operand_tr(Ws, ABS_LD, 32 * wave, 16 * kk + 8 * half, 16 * kk + 8 * half + 4), qf[kk], acc,
+          0, 0, 0);
+  if (rr >= rows) return;
+  bf16_t* out = qabs + qi * DK + c0 + 32 * wave + 4 * half;
+#pragma unroll
+  for (int e4 = 0; e4 < 4; ++e4)
+    *(u32x2*)(out + 8 * e4) = u32x2{pack2bf(acc[4 * e4], acc[4 * e4 + 1]), pack2bf(acc[4 * e4 + 2], acc[4 * e4 + 3])};
 }
 
 template <int DK, int DVL>
@@ -313,6 +294,7 @@ __global__ __launch_bounds__(64 * DEC_WAVES) void decode_attn_kernel(DecodeDev a
   // partial state of this split: lane (head col, half) holds rows
   // wave WV + 32 c + 8 (e / 4) + 4 half + e % 4 of the unnormalised latent output
   const float l = pair_sum32(l_run);
+  if (h0 + col >= a.H) return;  // a padding head
   const int64_t hrow = pbase + col;
   if (wave == 0 && half == 0) {
     a.part_ml[2 * hrow] = m_run;
@@ -327,29 +309,143 @@ __global__ __launch_bounds__(64 * DEC_WAVES) void decode_attn_kernel(DecodeDev a
           f32x4{acc[c][4 * g], acc[c][4 * g + 1], acc[c][4 * g + 2], acc[c][4 * g + 3]};
 }
 
-// lat[b][i][d] = sum_s o_s[d] 2^(m_s - M) / sum_s l_s 2^(m_s - M), splits in order (bf16:
-// the operand of the W_UV product)
-__global__ void decode_combine_kernel(const float* __restrict__ part_o,
-                                      const float* __restrict__ part_ml, bf16_t* __restrict__ lat,
-                                      int H, int HP, int nsplit, int DVL) {
-  const int b = blockIdx.y, i = blockIdx.x;
-  float M = -INFINITY;
-  for (int sp = 0; sp < nsplit; ++sp) M = fmaxf(M, part_ml[2 * (((int64_t)b * nsplit + sp) * HP + i)]);
-  float L = 0.f;
-  for (int sp = 0; sp < nsplit; ++sp) {
-    const int64_t r = ((int64_t)b * nsplit + sp) * HP + i;
-    const float m = part_ml[2 * r];
-    if (m != -INFINITY) L += part_ml[2 * r + 1] * __builtin_amdgcn_exp2f(m - M);
+// The splits of a (sequence, head) merged, then W_UV: lat[d] = sum_s o_s[d] 2^(m_s - M) /
+// sum_s l_s 2^(m_s - M), rounded to bf16, and o[b][i][e] = sum_d W_UV[g][e][d] lat[d].  A
+// workgroup owns head i and FIN_RB sequences.  Its wavefronts first ask for their W_UV rows
+// (kept in registers: the merge hides their latency), then the maxima and sums of the splits
+// go over the lanes of a wavefront per sequence, and DVL / 4 threads (each four columns) times
+// 1024 / DVL slots (each every so-many-th split) sum the partials, slots in order.  The product
+// runs on 16 x 16 x 32 steps with W_UV in the MFMA row.  Bound by latency; the merge reads
+// the partials once.  Measured: one sequence of 6000 rows (47 splits) 49 -> 9.6 us, 64 of
+// 4096 rows 19.6 -> 12.2 us (a merge that walked the splits one by one in every thread, and a
+// launch for the product, before).
+constexpr int FIN_RB = 8;
+template <int DVL, int DV>
+__global__ __launch_bounds__(256) void decode_finish_kernel(const float* __restrict__ part_o,
+                                                            const float* __restrict__ part_ml,
+                                                            const bf16_t* __restrict__ Wuv,
+                                                            bf16_t* __restrict__ o, int B, int H, int HP,
+                                                            int nsplit, int hpg) {
+  constexpr int NCG = DVL / 4, NSLOT = 256 / NCG, NK = DVL / 32, NT = DV / 64, LDL = DVL + 8;
+  __shared__ float red[FIN_RB][NSLOT][DVL];
+  __shared__ __attribute__((aligned(16))) bf16_t lat[FIN_RB * LDL];
+  __shared__ float sM[FIN_RB], sInv[FIN_RB];
+  const int i = blockIdx.x, b0 = FIN_RB * blockIdx.y, nb = min(FIN_RB, B - b0);
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+  // W_UV rows 16 (NT wave + t) + lane % 16, k = 32 kk + 8 (lane / 16) + 0..7
+  bf16x8 wf[NT][NK];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const bf16_t* wp = Wuv + ((int64_t)(i / hpg) * DV + 16 * (NT * wave + t) + (lane & 15)) * DVL + 8 * (lane >> 4);
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) wf[t][kk] = *(const bf16x8*)(wp + 32 * kk);
   }
-  const float inv = L > 0.f ? 1.f / L : 0.f;
-  for (int d = threadIdx.x; d < DVL; d += blockDim.x) {
-    float v = 0.f;
-    for (int sp = 0; sp < nsplit; ++sp) {
-      const int64_t r = ((int64_t)b * nsplit + sp) * HP + i;
-      const float m = part_ml[2 * r];
-      if (m != -INFINITY) v += part_o[r * DVL + d] * __builtin_amdgcn_exp2f(m - M);
+  // maxima and sums, a wavefront per FIN_RB / 4 sequences side by side; a lane takes every
+  // 64th split (its running sum rescaled as its maximum grows)
+  {
+    float M[FIN_RB / 4], L[FIN_RB / 4];
+#pragma unroll
+    for (int u = 0; u < FIN_RB / 4; ++u) {
+      M[u] = -INFINITY;
+      L[u] = 0.f;
     }
-    lat[((int64_t)b * H + i) * DVL + d] = f2bf(v * inv);
+    for (int sp = lane; sp < nsplit; sp += 64) {
+#pragma unroll
+      for (int u = 0; u < FIN_RB / 4; ++u) {
+        const int bb = min(wave + 4 * u, nb - 1);
+        const f32x2 ml = *(const f32x2*)(part_ml + 2 * (((int64_t)(b0 + bb) * nsplit + sp) * HP + i));
+        if (ml[0] != -INFINITY) {
+          const float m1 = fmaxf(M[u], ml[0]);
+          L[u] = L[u] * __builtin_amdgcn_exp2f(M[u] - m1) + ml[1] * __builtin_amdgcn_exp2f(ml[0] - m1);
+          M[u] = m1;
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < FIN_RB / 4; ++u) {
+      const float Mw = warp_max(M[u]);
+      const float Lw = warp_sum(M[u] == -INFINITY ? L[u] : L[u] * __builtin_amdgcn_exp2f(M[u] - Mw));
+      if (lane == 0 && wave + 4 * u < nb) {
+        sM[wave + 4 * u] = Mw;
+        sInv[wave + 4 * u] = Lw > 0.f ? 1.f / Lw : 0.f;
+      }
+    }
+  }
+  __syncthreads();
+  const int cg = tid % NCG, slot = tid / NCG;
+  const float* pol = part_o + 4 * cg;
+  if (nsplit <= 8 * NSLOT) {
+    // few splits: the sequences' loads of one split together
+    f32x4 v[FIN_RB];
+#pragma unroll
+    for (int bb = 0; bb < FIN_RB; ++bb) v[bb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int sp = slot; sp < nsplit; sp += NSLOT) {
+      f32x4 x[FIN_RB];
+      float m[FIN_RB];
+#pragma unroll
+      for (int bb = 0; bb < FIN_RB; ++bb) {
+        const int64_t rw = ((int64_t)(b0 + min(bb, nb - 1)) * nsplit + sp) * HP + i;
+        x[bb] = *(const f32x4*)(pol + rw * DVL);
+        m[bb] = part_ml[2 * rw];
+      }
+#pragma unroll
+      for (int bb = 0; bb < FIN_RB; ++bb)
+        if (m[bb] != -INFINITY)  // (an empty split adds nothing)
+          v[bb] += x[bb] * __builtin_amdgcn_exp2f(m[bb] - sM[min(bb, nb - 1)]);
+    }
+#pragma unroll
+    for (int bb = 0; bb < FIN_RB; ++bb) *(f32x4*)&red[bb][slot][4 * cg] = v[bb];
+  } else {
+    // many splits: eight of a sequence's together
+    for (int bb = 0; bb < nb; ++bb) {
+      const int64_t row0 = (int64_t)(b0 + bb) * nsplit * HP + i;
+      const float M = sM[bb];
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      for (int s0 = slot; s0 < nsplit; s0 += 8 * NSLOT) {
+        f32x4 x[8];
+        float m[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int64_t rw = row0 + (int64_t)HP * min(s0 + u * NSLOT, nsplit - 1);
+          x[u] = *(const f32x4*)(pol + rw * DVL);
+          m[u] = part_ml[2 * rw];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (m[u] != -INFINITY && s0 + u * NSLOT < nsplit) v += x[u] * __builtin_amdgcn_exp2f(m[u] - M);
+      }
+      *(f32x4*)&red[bb][slot][4 * cg] = v;
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < nb * NCG; e += 256) {
+    const int bb = e / NCG, c = 4 * (e % NCG);
+    f32x4 v = *(const f32x4*)&red[bb][0][c];
+#pragma unroll
+    for (int sl = 1; sl < NSLOT; ++sl) v += *(const f32x4*)&red[bb][sl][c];
+    v *= sInv[bb];
+    *(u32x2*)(lat + bb * LDL + c) = u32x2{pack2bf(v[0], v[1]), pack2bf(v[2], v[3])};
+  }
+  __syncthreads();
+  const int n = lane & 15;  // MFMA column: sequence b0 + n
+  const bf16_t* lp = lat + min(n, nb - 1) * LDL + 8 * (lane >> 4);
+  f32x4 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk) {
+    const bf16x8 lf = *(const bf16x8*)(lp + 32 * kk);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[t][kk], lf, acc[t], 0, 0, 0);
+  }
+  if (n >= nb) return;
+  // rows 4 (lane / 16) + 0..3 of each 16-row tile
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    bf16_t* op = o + ((int64_t)(b0 + n) * H + i) * DV + 16 * (NT * wave + t) + 4 * (lane >> 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) op[k] = f2bf(acc[t][k]);
   }
 }
 
@@ -424,26 +520,18 @@ hipError_t decode_attention(const Decode& d, hipStream_t s) {
   w += al((size_t)d.B * nsplit * HP * DVL * 4);
   float* part_ml = (float*)w;
   w += al((size_t)d.B * nsplit * HP * 2 * 4);
-  bf16_t* lat = (bf16_t*)w;
 
-  prof_begin(KC_ELEM, s);
-  const int64_t nq = (int64_t)d.B * HP * DK;
   const int G = d.H / d.hpg;
-  const int grow = (d.B * d.hpg + 31) / 32;
-  // latent part: q_abs[b][i][:rkv] = q^nope[b][i] W_UK[g]
-  group_gemm_kernel<bf16_t><<<dim3((d.rkv + 31) / 32, grow, G), 256, 0, s>>>(
-      (const bf16_t*)d.q, d.dn + d.dr, (const bf16_t*)d.Wuk, qabs, DK, HP, d.B, d.H, d.hpg, d.dn,
-      d.rkv);
-  {
-    const int64_t nrest = (int64_t)d.B * d.H * d.dr + (int64_t)d.B * (HP - d.H) * DK;
-    absorb_rest_kernel<<<(unsigned)((nrest + 255) / 256), 256, 0, s>>>(
-        (const bf16_t*)d.q, qabs, d.B, d.H, HP, d.dn, d.dr, d.rkv);
-  }
-  prof_end(KC_ELEM, s, 2.0 * d.B * d.H * d.dn * d.rkv, (double)nq * 2, KLABEL("group_gemm_kernel + absorb_rest_kernel"));
+  if (d.dn > ABS_DN || d.rkv % 64) return hipErrorInvalidValue;
+  prof_begin(KC_ELEM, s);
+  absorb_kernel<<<dim3(d.rkv / 64, (d.B * d.hpg + 31) / 32, G), 128, 0, s>>>(
+      (const bf16_t*)d.q, (const bf16_t*)d.Wuk, qabs, d.B, d.H, HP, d.hpg, d.dn, d.dr, d.rkv);
+  prof_end(KC_ELEM, s, 2.0 * d.B * d.H * d.dn * d.rkv, (double)d.B * d.H * (DK + d.dn + d.dr) * 2,
+           KLABEL("absorb_kernel"));
 
   DecodeDev a;
   a.qabs = qabs; a.cache = (const bf16_t*)d.cache; a.ldc = d.ldc;
-  a.seq_stride = (int64_t)d.Lmax * d.ldc; a.len = d.len; a.Lmax = d.Lmax; a.HP = HP;
+  a.seq_stride = (int64_t)d.Lmax * d.ldc; a.len = d.len; a.Lmax = d.Lmax; a.H = d.H; a.HP = HP;
   a.nsplit = nsplit; a.chunk = chunk; a.sl2 = d.scale * attn::LOG2E;
   a.part_o = part_o; a.part_ml = part_ml;
   const dim3 grid(nsplit, d.B, HP / 32);
@@ -456,13 +544,24 @@ hipError_t decode_attention(const Decode& d, hipStream_t s) {
 #undef X
   prof_end(KC_ATTN_FWD, s, 2.0 * d.B * d.H * (double)d.Lmax * (DK + DVL),
            (double)d.B * d.Lmax * DK * 2, KLABEL("decode_attn_kernel"));
+  const double fbytes = (double)d.B * nsplit * d.H * (DVL + 2) * 4 + (double)d.B * d.H * d.dv * 2;
+  const dim3 fgrid(d.H, (d.B + FIN_RB - 1) / FIN_RB);
   prof_begin(KC_ELEM, s);
-  decode_combine_kernel<<<dim3(d.H, d.B), 256, 0, s>>>(part_o, part_ml, lat, d.H, HP, nsplit, DVL);
-  prof_end(KC_ELEM, s, 0.0, (double)d.B * nsplit * HP * (DVL + 2) * 4 + (double)d.B * d.H * DVL * 2,
-           KLABEL("decode_combine_kernel"));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return uv_project(lat, d.Wuv, d.o, d.B, d.H, d.rkv, d.hpg, d.dv, s);
+#define X(a_, b_)                                                                                  \
+  if (DK == a_ && DVL == b_) {                                                                     \
+    if (d.dv == 128)                                                                               \
+      decode_finish_kernel<b_, 128><<<fgrid, 256, 0, s>>>(part_o, part_ml, (const bf16_t*)d.Wuv,   \
+                                                          (bf16_t*)d.o, d.B, d.H, HP, nsplit, d.hpg); \
+    else if (d.dv == 64)                                                                           \
+      decode_finish_kernel<b_, 64><<<fgrid, 256, 0, s>>>(part_o, part_ml, (const bf16_t*)d.Wuv,    \
+                                                         (bf16_t*)d.o, d.B, d.H, HP, nsplit, d.hpg); \
+    else                                                                                           \
+      return hipErrorInvalidValue;                                                                 \
+  }
+  MLA_DECODE_SHAPES(X)
+#undef X
+  prof_end(KC_ELEM, s, 2.0 * d.B * d.H * d.dv * d.rkv, fbytes, KLABEL("decode_finish_kernel"));
+  return hipGetLastError();
 }
 
 hipError_t uv_project(const void* lat, const void* Wuv, void* o, int rows, int H, int rkv, int hpg,
