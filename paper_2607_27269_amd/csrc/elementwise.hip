@@ -605,9 +605,11 @@ hipError_t adamw_step(const AdamwTensor* t, int count, DType wt, float lr, float
   return hipGetLastError();
 }
 
-// Residual add and RMS normalisation of one row per workgroup -------------------------------
+// Residual add and RMS normalisation -----------------------------------------------------
 // x[n] += A[n] (A optional); h[n] = x[n] / sqrt(mean(x[n]^2) + eps) in h's dtype.  The row
 // sum runs in a fixed order (per-thread strided partials, then a fixed tree).
+
+// The general kernel: one row per workgroup, any width and alignment.
 template <typename T>
 __global__ __launch_bounds__(256) void residual_rmsnorm_kernel(float* __restrict__ x,
                                                                const float* __restrict__ A,
@@ -637,14 +639,73 @@ __global__ __launch_bounds__(256) void residual_rmsnorm_kernel(float* __restrict
   for (int d = threadIdx.x; d < D; d += 256) st<T>(hr + d, xr[d] * inv);
 }
 
+// Rows of a multiple of four values, 16-byte aligned arrays, at most 256 x 4 PER values: a
+// wavefront-quartet per row keeps the row in registers (one pass over x and A, 16-byte
+// accesses, two barriers).  Bound by HBM: 14 bytes per value with A.  Measured at 8192 x 4096
+// in bf16: 70 us (6.7 TB/s) against 136 us for the general kernel (4-byte accesses, nine barriers and
+// a second read of the row).
+template <typename T, int PER>
+__global__ __launch_bounds__(256) void residual_rmsnorm4_kernel(float* __restrict__ x,
+                                                                const float* __restrict__ A,
+                                                                T* __restrict__ h, int D,
+                                                                float eps) {
+  __shared__ float red[4];
+  const int64_t row = blockIdx.x;
+  float* xr = x + row * D;
+  f32x4 v[PER];
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    const int d = 4 * ((int)threadIdx.x + 256 * p);
+    v[p] = d < D ? *(const f32x4*)(xr + d) : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  if (A) {  // uniform
+    const float* ar = A + row * D;
+    f32x4 u[PER];
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int d = 4 * ((int)threadIdx.x + 256 * p);
+      u[p] = d < D ? __builtin_nontemporal_load((const f32x4*)(ar + d)) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int d = 4 * ((int)threadIdx.x + 256 * p);
+      v[p] += u[p];
+      if (d < D) *(f32x4*)(xr + d) = v[p];
+    }
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int p = 0; p < PER; ++p) ss += v[p][0] * v[p][0] + v[p][1] * v[p][1] + v[p][2] * v[p][2] + v[p][3] * v[p][3];
+  ss = warp_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  const float inv = 1.f / sqrtf((red[0] + red[1] + (red[2] + red[3])) / (float)D + eps);
+  T* hr = h + row * D;
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    const int d = 4 * ((int)threadIdx.x + 256 * p);
+    if (d < D) store4<T>(hr + d, v[p][0] * inv, v[p][1] * inv, v[p][2] * inv, v[p][3] * inv);
+  }
+}
+
+template <typename T>
+static void rmsnorm_launch(float* x, const float* A, T* h, int64_t N, int D, float eps, hipStream_t s) {
+  const bool vec = D % 4 == 0 && D <= 8192 && (uintptr_t)x % 16 == 0 && (uintptr_t)A % 16 == 0 &&
+                   (uintptr_t)h % (4 * sizeof(T)) == 0;
+  const unsigned g = (unsigned)N;
+  if (!vec) residual_rmsnorm_kernel<T><<<g, 256, 0, s>>>(x, A, h, D, eps);
+  else if (D <= 1024) residual_rmsnorm4_kernel<T, 1><<<g, 256, 0, s>>>(x, A, h, D, eps);
+  else if (D <= 2048) residual_rmsnorm4_kernel<T, 2><<<g, 256, 0, s>>>(x, A, h, D, eps);
+  else if (D <= 4096) residual_rmsnorm4_kernel<T, 4><<<g, 256, 0, s>>>(x, A, h, D, eps);
+  else residual_rmsnorm4_kernel<T, 8><<<g, 256, 0, s>>>(x, A, h, D, eps);
+}
+
 hipError_t residual_rmsnorm(float* x, const float* A, void* h, int64_t N, int D, DType t, float eps,
                             hipStream_t s) {
   if (N <= 0 || D <= 0) return hipSuccess;
   prof_begin(KC_ELEM, s);
-  if (t == DT_BF16)
-    residual_rmsnorm_kernel<bf16_t><<<(unsigned)N, 256, 0, s>>>(x, A, (bf16_t*)h, D, eps);
-  else
-    residual_rmsnorm_kernel<float><<<(unsigned)N, 256, 0, s>>>(x, A, (float*)h, D, eps);
+  if (t == DT_BF16) rmsnorm_launch<bf16_t>(x, A, (bf16_t*)h, N, D, eps, s);
+  else rmsnorm_launch<float>(x, A, (float*)h, N, D, eps, s);
   prof_end(KC_ELEM, s, 0.0, (double)N * D * ((A ? 12.0 : 4.0) + dsize(t)), KLABEL("residual_rmsnorm_kernel"));
   return hipGetLastError();
 }
