@@ -316,10 +316,21 @@ size_t mla_recon_workspace_size_min(const mla_recon_cfg* cfg) {
   return layout_of(d, std::min(1, max_chunk(d))).total;
 }
 
+// The student's products of h: c^Q = W_DQ h (or q = W_UQ h without a query latent) and, Eq. 5,
+// [c^KV | k^PE] = [W^DKV; W^KR] h
+static void student_h_products(const Dims& d, const Layout& L, const void* h, const mla_student_w* w,
+                               void* ws, Gemm* out) {
+  const int N = (int)d.N, D = (int)d.D, rq = (int)d.rq, kv_out = (int)d.kv_out;
+  const int nq = rq > 0 ? rq : (int)(d.H * d.dqk);
+  out[0] = mk(N, nq, D, h, D, true, rq > 0 ? w->Wdq : w->Wuq, D, true, at(ws, rq > 0 ? L.s_cq : L.s_q), nq, d.t, d.t);
+  out[1] = mk(N, kv_out, D, h, D, true, w->Wdkv_kr, D, true, at(ws, L.s_ckv), kv_out, d.t, d.t);
+}
+
 // Teacher forward up to the attention output o_t (ws region t_o); with A_t also the frozen
-// output projection.
+// output projection; with sw also the student's products of h, next to the teacher's.
 static int teacher_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
-                        const mla_teacher_w* w, float* A_t, void* ws, hipStream_t s) {
+                        const mla_teacher_w* w, float* A_t, void* ws, hipStream_t s,
+                        const mla_student_w* sw = nullptr) {
   const Dims d = dims_of(cfg);
   const int N = (int)d.N, D = (int)d.D, H = (int)d.H, G = (int)d.G, dk = (int)d.dk;
   const int64_t ld_qkv = (H + 2 * G) * (int64_t)dk;
@@ -332,9 +343,12 @@ static int teacher_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h
 
   HIP_TRY(rope_tables(w->inv_freq, 1, (int)d.T, dk / 2, cs, sn, s));
   // Eq. 1: q = W^Q h, k = W^K h, v = W^V h  (columns [Q | K | V] of one buffer)
-  HIP_TRY(gemm(mk(N, H * dk, D, h, D, true, w->Wq, D, true, qkv, ld_qkv, d.t, d.t), sk.p, sk.elems, s));
-  HIP_TRY(gemm(mk(N, G * dk, D, h, D, true, w->Wk, D, true, qkv + (size_t)H * dk * ts, ld_qkv, d.t, d.t), sk.p, sk.elems, s));
-  HIP_TRY(gemm(mk(N, G * dk, D, h, D, true, w->Wv, D, true, qkv + (size_t)(H + G) * dk * ts, ld_qkv, d.t, d.t), sk.p, sk.elems, s));
+  Gemm pr[5] = {
+      mk(N, H * dk, D, h, D, true, w->Wq, D, true, qkv, ld_qkv, d.t, d.t),
+      mk(N, G * dk, D, h, D, true, w->Wk, D, true, qkv + (size_t)H * dk * ts, ld_qkv, d.t, d.t),
+      mk(N, G * dk, D, h, D, true, w->Wv, D, true, qkv + (size_t)(H + G) * dk * ts, ld_qkv, d.t, d.t)};
+  if (sw) student_h_products(d, L, h, sw, ws, pr + 3);
+  HIP_TRY(gemm_group(pr, sw ? 5 : 3, sk.p, sk.elems, s));
   // R_t on queries and keys (Sec. 3.1); on the matrix-core path the attention kernel rotates
   // the queries as it loads them (the teacher's rotated queries are not needed elsewhere)
   const bool q_on_load = d.t == DT_BF16 && attn_mfma_supported(dk, dk) && dk % 32 == 0;
@@ -378,10 +392,10 @@ static bool student_w_ok(const mla_recon_cfg* cfg, const mla_student_w* w) {
 
 // Student forward up to the attention output o_s (kept in ws for the backward); then
 // A_s = o_s W_O^T when A_s is given, and o_diff = o_s - o_ref (storage dtype, same layout)
-// when o_diff is given.
+// when o_diff is given.  have_h_products: student_h_products have run (with the teacher's).
 static int student_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
                         const mla_student_w* w, const void* Wo, float* A_s, const void* o_ref,
-                        void* o_diff, void* ws, hipStream_t s) {
+                        void* o_diff, void* ws, hipStream_t s, bool have_h_products = false) {
   const Dims d = dims_of(cfg);
   const int N = (int)d.N, D = (int)d.D, H = (int)d.H, T = (int)d.T;
   const int rq = (int)d.rq, rkv = (int)d.rkv, dn = (int)d.dn, dr = (int)d.dr, dqk = (int)d.dqk;
@@ -399,20 +413,21 @@ static int student_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h
   const Scratch sk = fwd_scratch(L, ws);
 
   HIP_TRY(rope_tables(w->inv_freq, Gr, T, dr / 2, cs, sn, s));
-  // low-rank query: c^Q = W_DQ h, q = W_UQ c^Q  (q = W_UQ h when r_q = 0)
-  const void* qin = h;
-  int qk = D;
-  if (rq > 0) {
-    HIP_TRY(gemm(mk(N, rq, D, h, D, true, w->Wdq, D, true, cq, rq, d.t, d.t), sk.p, sk.elems, s));
-    qin = cq;
-    qk = rq;
+  // low-rank query: c^Q = W_DQ h, q = W_UQ c^Q  (q = W_UQ h when r_q = 0); Eq. 5:
+  // [c^KV | k^PE] = [W^DKV; W^KR] h, [k^nope; v] = W^UKV c^KV
+  if (!have_h_products) {
+    Gemm pr[2];
+    student_h_products(d, L, h, w, ws, pr);
+    HIP_TRY(gemm_group(pr, 2, sk.p, sk.elems, s));
   }
-  HIP_TRY(gemm(mk(N, H * dqk, qk, qin, qk, true, w->Wuq, qk, true, q, (int64_t)H * dqk, d.t, d.t), sk.p, sk.elems, s));
-  // Eq. 5: [c^KV | k^PE] = [W^DKV; W^KR] h, [k^nope; v] = W^UKV c^KV
-  HIP_TRY(gemm(mk(N, kv_out, D, h, D, true, w->Wdkv_kr, D, true, ckv, kv_out, d.t, d.t), sk.p, sk.elems, s));
+  Gemm up[3];
+  int nup = 0;
+  if (rq > 0)
+    up[nup++] = mk(N, H * dqk, rq, cq, rq, true, w->Wuq, rq, true, q, (int64_t)H * dqk, d.t, d.t);
   if (dn > 0)
-    HIP_TRY(gemm(mk(N, Gkv * dn, rkv, ckv, kv_out, true, w->Wuk, rkv, true, knope, (int64_t)Gkv * dn, d.t, d.t), sk.p, sk.elems, s));
-  HIP_TRY(gemm(mk(N, Gkv * dv, rkv, ckv, kv_out, true, w->Wuv, rkv, true, v, (int64_t)Gkv * dv, d.t, d.t), sk.p, sk.elems, s));
+    up[nup++] = mk(N, Gkv * dn, rkv, ckv, kv_out, true, w->Wuk, rkv, true, knope, (int64_t)Gkv * dn, d.t, d.t);
+  up[nup++] = mk(N, Gkv * dv, rkv, ckv, kv_out, true, w->Wuv, rkv, true, v, (int64_t)Gkv * dv, d.t, d.t);
+  HIP_TRY(gemm_group(up, nup, sk.p, sk.elems, s));
   // decoupled RoPE on q^rope (rope group i / (H/G_r)) and on k^PE
   HIP_TRY(rope_apply(q, d.t, N, T, H, (int64_t)H * dqk, dqk, dn, dr / 2, H / Gr, cs, sn, s));
   HIP_TRY(rope_apply(ckv, d.t, N, T, Gr, kv_out, dr, rkv, dr / 2, 1, cs, sn, s));
@@ -531,44 +546,48 @@ static int bwd_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
   HIP_TRY(attn_bwd(ab, s));
   const Scratch sk = bwd_scratch(d, L, ws);
 
-  if (need_q) {
-    const void* qin = rq > 0 ? (const void*)cq : h;
-    const int qk = rq > 0 ? rq : D;
-    // dW_UQ = dq^T c^Q
-    if (gr->dWuq)
-      HIP_TRY(gemm(mk(H * dqk, qk, N, dq, (int64_t)H * dqk, false, qin, qk, false, gr->dWuq, qk, t, DT_F32), sk.p, sk.elems, s));
-    if (gr->dWdq) {
-      // dc^Q = dq W_UQ, dW_DQ = dc^Q^T h
-      HIP_TRY(gemm(mk(N, rq, H * dqk, dq, (int64_t)H * dqk, true, w->Wuq, rq, false, dcq, rq, t, t), sk.p, sk.elems, s));
-      HIP_TRY(gemm(mk(rq, D, N, dcq, rq, false, h, D, false, gr->dWdq, D, t, DT_F32), sk.p, sk.elems, s));
-    }
+  // data gradients: dc^Q = dq W_UQ; Eq. 5 backward dc^KV = dk^nope W_UK + dv W_UV and
+  // dk^PE = R^T sum of the head partials
+  Gemm pr[4];
+  int np = 0;
+  if (need_q && gr->dWdq)
+    pr[np++] = mk(N, rq, H * dqk, dq, (int64_t)H * dqk, true, w->Wuq, rq, false, dcq, rq, t, t);
+  if (need_kv && gr->dWdkv_kr) {
+    if (dn > 0)
+      pr[np++] = mk(N, rkv, Gkv * dn, dkv, ld_dkv, true, w->Wuk, rkv, false, dckv, kv_out, t, t);
+    pr[np++] = mk(N, rkv, Gkv * dv, dkv + (size_t)Gkv * dn * ts, ld_dkv, true, w->Wuv, rkv, false, dckv, kv_out, t, t, dn > 0 ? 1.f : 0.f);
   }
-  if (need_kv) {
-    // Eq. 5 backward: dW_UK = dk^nope^T c^KV, dW_UV = dv^T c^KV.  In bf16 both are one
-    // product over the adjacent [dk^nope | dv] columns of dkv, its split-K sum written to the
-    // two outputs (one launch pair instead of two for these short, wide-K products)
-    Gemm both = mk(Gkv * (dn + dv), rkv, N, dkv, ld_dkv, false, ckv, kv_out, false, gr->dWuk, rkv, t, DT_F32);
-    both.C2 = gr->dWuv;
-    both.m2 = Gkv * dn;
-    if (t == DT_BF16 && gr->dWuk && gr->dWuv && dn > 0 && rkv % 4 == 0 &&
-        (uintptr_t)gr->dWuk % 16 == 0 && (uintptr_t)gr->dWuv % 16 == 0 &&
-        sk.elems >= (size_t)both.M * both.N) {
-      HIP_TRY(gemm(both, sk.p, sk.elems, s));
-    } else {
-      if (gr->dWuk && dn > 0)
-        HIP_TRY(gemm(mk(Gkv * dn, rkv, N, dkv, ld_dkv, false, ckv, kv_out, false, gr->dWuk, rkv, t, DT_F32), sk.p, sk.elems, s));
-      if (gr->dWuv)
-        HIP_TRY(gemm(mk(Gkv * dv, rkv, N, dkv + (size_t)Gkv * dn * ts, ld_dkv, false, ckv, kv_out, false, gr->dWuv, rkv, t, DT_F32), sk.p, sk.elems, s));
-    }
-    if (gr->dWdkv_kr) {
-      // dc^KV = dk^nope W_UK + dv W_UV; dk^PE = R^T sum of the head partials
-      if (dn > 0)
-        HIP_TRY(gemm(mk(N, rkv, Gkv * dn, dkv, ld_dkv, true, w->Wuk, rkv, false, dckv, kv_out, t, t), sk.p, sk.elems, s));
-      HIP_TRY(gemm(mk(N, rkv, Gkv * dv, dkv + (size_t)Gkv * dn * ts, ld_dkv, true, w->Wuv, rkv, false, dckv, kv_out, t, t, dn > 0 ? 1.f : 0.f), sk.p, sk.elems, s));
-      HIP_TRY(dkpe_finish(dkpe, dckv + (size_t)rkv * ts, t, kv_out, N, T, Gr, Gkv / Gr, dr, cs, sn, s));
-      // d[W_DKV; W_KR] = [dc^KV | dk^PE]^T h
-      HIP_TRY(gemm(mk(kv_out, D, N, dckv, kv_out, false, h, D, false, gr->dWdkv_kr, D, t, DT_F32), sk.p, sk.elems, s));
-    }
+  if (np) HIP_TRY(gemm_group(pr, np, sk.p, sk.elems, s));
+  if (need_kv && gr->dWdkv_kr)
+    HIP_TRY(dkpe_finish(dkpe, dckv + (size_t)rkv * ts, t, kv_out, N, T, Gr, Gkv / Gr, dr, cs, sn, s));
+  // weight gradients: dW_UQ = dq^T c^Q, dW_DQ = dc^Q^T h, dW_UK = dk^nope^T c^KV,
+  // dW_UV = dv^T c^KV, d[W_DKV; W_KR] = [dc^KV | dk^PE]^T h
+  np = 0;
+  const void* qin = rq > 0 ? (const void*)cq : h;
+  const int qk = rq > 0 ? rq : D;
+  if (gr->dWuq)
+    pr[np++] = mk(H * dqk, qk, N, dq, (int64_t)H * dqk, false, qin, qk, false, gr->dWuq, qk, t, DT_F32);
+  if (need_q && gr->dWdq)
+    pr[np++] = mk(rq, D, N, dcq, rq, false, h, D, false, gr->dWdq, D, t, DT_F32);
+  // In bf16 dW_UK and dW_UV are one product over the adjacent [dk^nope | dv] columns of dkv,
+  // its split-K sum written to the two outputs
+  Gemm both = mk(Gkv * (dn + dv), rkv, N, dkv, ld_dkv, false, ckv, kv_out, false, gr->dWuk, rkv, t, DT_F32);
+  both.C2 = gr->dWuv;
+  both.m2 = Gkv * dn;
+  const bool one_up = t == DT_BF16 && gr->dWuk && gr->dWuv && dn > 0 && rkv % 4 == 0 &&
+                      (uintptr_t)gr->dWuk % 16 == 0 && (uintptr_t)gr->dWuv % 16 == 0 &&
+                      sk.elems >= (size_t)both.M * both.N;
+  Gemm one_k = mk(Gkv * dn, rkv, N, dkv, ld_dkv, false, ckv, kv_out, false, gr->dWuk, rkv, t, DT_F32);
+  Gemm one_v = mk(Gkv * dv, rkv, N, dkv + (size_t)Gkv * dn * ts, ld_dkv, false, ckv, kv_out, false, gr->dWuv, rkv, t, DT_F32);
+  if (one_up) pr[np++] = both;
+  if (gr->dWdkv_kr)
+    pr[np++] = mk(kv_out, D, N, dckv, kv_out, false, h, D, false, gr->dWdkv_kr, D, t, DT_F32);
+  if (np) HIP_TRY(gemm_group(pr, np, sk.p, sk.elems, s));
+  if (!one_up) {
+    np = 0;
+    if (gr->dWuk && dn > 0) pr[np++] = one_k;
+    if (gr->dWuv) pr[np++] = one_v;
+    if (np) HIP_TRY(gemm_group(pr, np, sk.p, sk.elems, s));
   }
   return MLA_OK;
 }
@@ -600,13 +619,14 @@ static int gram_impl(const Dims& d, const Layout& L, const void* Wo, void* ws, h
 static int student_step_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
                              const mla_student_w* sw, const void* Wo, const uint8_t* mask,
                              float* loss, void* dA, const mla_student_grads* gr, void* ws,
-                             hipStream_t s) {
+                             hipStream_t s, bool have_h_products = false) {
   const Dims d = dims_of(cfg);
   int rc;
   // o_s (kept for the backward) and o_s - o_t, the latter into the teacher's q/k/v region,
   // which is free once the teacher's attention has run
   void* odiff = at(ws, L.t_qkv);
-  if ((rc = student_impl(cfg, L, h, sw, Wo, nullptr, at(ws, L.t_o), odiff, ws, s))) return rc;
+  if ((rc = student_impl(cfg, L, h, sw, Wo, nullptr, at(ws, L.t_o), odiff, ws, s, have_h_products)))
+    return rc;
   // A_s - A_t = (o_s - o_t) W_O^T: both blocks end in the same frozen W_O
   const int N = (int)d.N, D = (int)d.D, HV = (int)(d.H * d.dv);
   if (d.t == DT_BF16 && !dA) {
@@ -677,9 +697,9 @@ int mla_recon_step(const mla_recon_cfg* cfg, const void* h, const mla_teacher_w*
   Layout L;
   if ((rc = check_ws(cfg, ws, ws_bytes, &L))) return rc;
   hipStream_t s = (hipStream_t)hip_stream;
-  if ((rc = teacher_impl(cfg, L, h, tw, nullptr, ws, s))) return rc;
+  if ((rc = teacher_impl(cfg, L, h, tw, nullptr, ws, s, sw))) return rc;
   if (cfg->dtype == MLA_BF16 && !dA && (rc = gram_impl(dims_of(cfg), L, tw->Wo, ws, s))) return rc;
-  return student_step_impl(cfg, L, h, sw, tw->Wo, mask, loss, dA, gr, ws, s);
+  return student_step_impl(cfg, L, h, sw, tw->Wo, mask, loss, dA, gr, ws, s, true);
 }
 
 int mla_recon_teacher_cache(const mla_recon_cfg* cfg, const void* h, const mla_teacher_w* tw,
@@ -936,10 +956,11 @@ int mla_recon_prefill(const mla_recon_cfg* cfg, const void* q, const void* cache
   const bool o_direct = o && (uintptr_t)o % 16 == 0;
   void* obuf = o_direct ? o : (void*)at(ws, off_o);
   void* lat = at(ws, off_lat);
-  if (dn > 0)
-    HIP_TRY(gemm(mk(rows, nk, rkv, cache, rkv + dr, true, Wuk, rkv, true, keys, nk, DT_BF16, DT_BF16), sk.p, sk.elems, s));
-  if (!folded)
-    HIP_TRY(gemm(mk(rows, nv, rkv, cache, rkv + dr, true, Wuv, rkv, true, vals, nv, DT_BF16, DT_BF16), sk.p, sk.elems, s));
+  Gemm up[2];
+  int nup = 0;
+  if (dn > 0) up[nup++] = mk(rows, nk, rkv, cache, rkv + dr, true, Wuk, rkv, true, keys, nk, DT_BF16, DT_BF16);
+  if (!folded) up[nup++] = mk(rows, nv, rkv, cache, rkv + dr, true, Wuv, rkv, true, vals, nv, DT_BF16, DT_BF16);
+  if (nup) HIP_TRY(gemm_group(up, nup, sk.p, sk.elems, s));
   HIP_TRY(prefill_guard(cache, rows, rkv, dr, keys, nk, dn == 0, folded ? nullptr : vals, nv,
                         folded ? vals : nullptr, s));
   Attn p;

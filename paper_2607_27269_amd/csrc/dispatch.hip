@@ -13,11 +13,33 @@ size_t gemm_scratch_elems(const Gemm& g) {
   return g.in_t == DT_BF16 ? gemm_mfma_scratch_elems(g) : 0;
 }
 
+static double gemm_flops(const Gemm& g) { return 2.0 * g.M * g.N * (double)g.K; }
+static double gemm_bytes(const Gemm& g) {
+  return ((double)g.M * g.K + (double)g.N * g.K) * dsize(g.in_t) +
+         (double)g.M * g.N * dsize(g.c_t) * (g.beta != 0.f ? 2.0 : 1.0);
+}
+
+hipError_t gemm_group(const Gemm* g, int n, float* scratch, size_t scratch_elems, hipStream_t s) {
+  if (n > 1 && g[0].in_t == DT_BF16) {
+    double flops = 0.0, bytes = 0.0;
+    for (int i = 0; i < n; ++i) {
+      flops += gemm_flops(g[i]);
+      bytes += gemm_bytes(g[i]);
+    }
+    const int kc = g[0].a_kmajor ? (g[0].b_kmajor ? KC_GEMM_NT : KC_GEMM_NN) : KC_GEMM_TN;
+    const hipError_t e = gemm_mfma_group(g, n, scratch, scratch_elems, s, kc, flops, bytes);
+    if (e != hipErrorNotSupported) return e;
+  }
+  for (int i = 0; i < n; ++i) {
+    const hipError_t e = gemm(g[i], scratch, scratch_elems, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t gemm(const Gemm& g, float* scratch, size_t scratch_elems, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return hipSuccess;
-  double flops = 2.0 * g.M * g.N * (double)g.K;
-  double bytes = ((double)g.M * g.K + (double)g.N * g.K) * dsize(g.in_t) +
-                 (double)g.M * g.N * dsize(g.c_t) * (g.beta != 0.f ? 2.0 : 1.0);
+  const double flops = gemm_flops(g), bytes = gemm_bytes(g);
   const int kc = g.a_kmajor ? (g.b_kmajor ? KC_GEMM_NT : KC_GEMM_NN) : KC_GEMM_TN;
   // the matrix-core path brackets its product and its split-K sum separately
   if (g.in_t == DT_BF16) return gemm_mfma(g, scratch, scratch_elems, s, kc, flops, bytes);

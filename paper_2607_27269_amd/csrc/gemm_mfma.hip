@@ -403,7 +403,7 @@ __device__ __forceinline__ void shift_edge(const GemmDev& g, int& m0, int& n0) {
 // origin cost the dS^T products and the NT kernel 1.5-2.5% at 16384 tokens.)
 template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK, int NST,
           bool ATILE = false, bool SHIFT = true>
-__device__ __forceinline__ void gemm_tile(const GemmDev& g) {
+__device__ __forceinline__ void gemm_tile(const GemmDev& g, int wg, int split) {
   constexpr int NTHR = 64 * WM * WN;
   constexpr int TM = BM / WM / 32;  // 32x32 MFMA tiles per wave along M
   constexpr int TN = BN / WN / 32;
@@ -425,7 +425,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
     // the longest K ranges first (row tile by row tile); inside one row tile, batch entries
     // that share their B panel (bdiv consecutive entries) are dispatched to one XCD
     // (workgroup ids go round-robin over the 8 XCDs) so that they stream it through one L2
-    const int pid = blockIdx.x;
+    const int pid = wg;
     const int per = g.nbatch * ntn;
     tm = g.rev ? pid / per : ntm - 1 - pid / per;
     const int r = pid % per;
@@ -441,7 +441,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
     C += z1 * g.sC1 + z2 * g.sC2;
   } else {
     // XCD-aware remap, then group 8 row panels together for L2 reuse
-    const int pid = xcd_remap(blockIdx.x, ntiles);
+    const int pid = xcd_remap(wg, ntiles);
     const int GROUP = 8;
     const int group = pid / (GROUP * ntn);
     const int first = group * GROUP;
@@ -452,7 +452,6 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
   const int mlo = tm * BM, nlo = tn * BN;  // first row and column this tile stores
   int m0 = mlo, n0 = nlo;
   if constexpr (SHIFT) shift_edge<BM, BN, AK, BKM, ATILE>(g, m0, n0);
-  const int split = blockIdx.y;
   int kbeg, kend;
   if (g.causal) {
     kbeg = g.rev ? mlo : 0;
@@ -667,7 +666,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g) {
     if (threadIdx.x == 0) {
       double t = 0.0;
       for (int w = 0; w < NTHR / 64; ++w) t += lred[w];
-      g.lpart[blockIdx.x] = t;
+      g.lpart[wg] = t;
     }
   }
 }
@@ -989,13 +988,35 @@ __global__ __launch_bounds__(64 * WM * WN) void attn_ds_gemm_persist_kernel(Gemm
 }
 template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK, int NST>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(GemmDev g) {
-  gemm_tile<BM, BN, WM, WN, AK, BKM, TC, BK, NST>(g);
+  gemm_tile<BM, BN, WM, WN, AK, BKM, TC, BK, NST>(g, blockIdx.x, blockIdx.y);
+}
+// Several products of one layout in one launch, on 64 x 64 tiles: workgroup ids run over the
+// (split, tile) pairs of the first product, then of the second, ..
+constexpr int GROUP_MAX = 5;
+struct GroupDev {
+  int n;
+  int end[GROUP_MAX];    // workgroups of products 0 .. i
+  int tiles[GROUP_MAX];  // tiles of product i
+  GemmDev p[GROUP_MAX];
+};
+template <bool AK, bool BKM, typename TC>
+__global__ __launch_bounds__(256) void gemm_group_kernel(GroupDev gr) {
+  const int w = blockIdx.x;
+  int i = 0, beg = 0;
+#pragma unroll
+  for (int j = 0; j < GROUP_MAX - 1; ++j)
+    if (j + 1 < gr.n && w >= gr.end[j]) {
+      i = j + 1;
+      beg = gr.end[j];
+    }
+  const int tiles = gr.tiles[i];
+  gemm_tile<64, 64, 2, 2, AK, BKM, TC, 64, 4>(gr.p[i], (w - beg) % tiles, (w - beg) / tiles);
 }
 // the same tile program for the dS products of attention's backward, on the 32 x 32-tiled
 // dS^T (own name, so that profiles tell them apart)
 template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK, int NST, bool SHIFT>
 __global__ __launch_bounds__(64 * WM * WN) void attn_ds_gemm_kernel(GemmDev g) {
-  gemm_tile<BM, BN, WM, WN, AK, BKM, TC, BK, NST, true, SHIFT>(g);
+  gemm_tile<BM, BN, WM, WN, AK, BKM, TC, BK, NST, true, SHIFT>(g, blockIdx.x, blockIdx.y);
 }
 
 // ---- NT products on four wavefronts, k-steps scheduled by hand ------------------------
@@ -1337,18 +1358,32 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ part, int splits,
   store_out<TC>(c, v);
 }
 
-// the same, four consecutive outputs per thread (N and ldc multiples of 4)
+// the same, four consecutive outputs per thread (N and ldc multiples of 4), for several sums
+// in one launch
+struct SumDev {
+  const float* part;
+  int64_t sstride, ldc, end;  // end: quadruples of sums 0 .. i
+  void* C;
+  int splits, N;
+  float alpha, beta;
+};
+constexpr int SUM_MAX = GROUP_MAX + 1;
+struct SumGroup {
+  int n;
+  SumDev s[SUM_MAX];
+};
 template <typename TC>
-__global__ void splitk_reduce4_kernel(const float* __restrict__ part, int splits, int64_t sstride,
-                                      int M, int N, TC* __restrict__ C, int64_t ldc, float alpha,
-                                      float beta) {
-  const int64_t idx = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
-  const int64_t total = (int64_t)M * N;
-  if (idx >= total) return;
-  const int m = (int)(idx / N), n = (int)(idx % N);
+__global__ __launch_bounds__(256) void splitk_reduce4_kernel(SumGroup gr) {
+  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (q >= gr.s[gr.n - 1].end) return;
+  int i = 0;
+  while (q >= gr.s[i].end) ++i;
+  const SumDev& d = gr.s[i];
+  const int64_t idx = 4 * (i ? q - gr.s[i - 1].end : q);
+  const int64_t m = idx / d.N;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int z = 0; z < splits; ++z) acc += *(const f32x4*)(part + (int64_t)z * sstride + idx);
-  store4<TC>(C + (int64_t)m * ldc + n, acc, alpha, beta);
+  for (int z = 0; z < d.splits; ++z) acc += *(const f32x4*)(d.part + z * d.sstride + idx);
+  store4<TC>((TC*)d.C + m * d.ldc + (idx - m * d.N), acc, d.alpha, d.beta);
 }
 
 // Tile shape and split-K factor.
@@ -1365,6 +1400,7 @@ enum TileKind {
 struct Plan {
   int kind;
   int bm, bn, splits, kchunk;
+  double t = 0.0;  // modelled us
 };
 
 constexpr int NUM_CU = 256;
@@ -1417,7 +1453,7 @@ Plan plan_of(const Gemm& g, size_t scratch_elems, unsigned kinds) {
   const int kslices = std::max(1, (g.K + BK - 1) / BK);
   const double mn = (double)g.M * g.N;
   const bool two = g.C2 != nullptr;
-  Plan best{T64, 64, 64, 1, kslices * BK};
+  Plan best{T64, 64, 64, 1, kslices * BK, 1e300};
   double best_t = 1e300;
   for (int k = 0; k < T_KINDS; ++k) {
     const TileCost& c = TILE_COST[layout][k];
@@ -1439,7 +1475,7 @@ Plan plan_of(const Gemm& g, size_t scratch_elems, unsigned kinds) {
       if (sp > 1 || two) t += 2.5 + 0.24 * sp + 0.16 * (sp + 1) * mn * 4e-6;
       if (t < best_t) {
         best_t = t;
-        best = Plan{k, c.bm, c.bn, sp, kc * BK};
+        best = Plan{k, c.bm, c.bn, sp, kc * BK, t};
       }
     }
   }
@@ -1545,25 +1581,66 @@ size_t gemm_mfma_scratch_elems(const Gemm& g) {
   return splits > 1 || g.C2 ? (size_t)splits * g.M * g.N : 0;
 }
 
-hipError_t gemm_mfma(const Gemm& g, float* scratch, size_t scratch_elems, hipStream_t s, int kc,
-                     double flops, double bytes) {
+// the device arguments of a plain product
+static GemmDev dev_of(const Gemm& g) {
   GemmDev d;
   d.M = g.M; d.N = g.N; d.ktotal = g.K; d.nsplit = 1;
   d.A = (const bf16_t*)g.A; d.lda = g.lda;
   d.B = (const bf16_t*)g.B; d.ldb = g.ldb;
   d.C = g.C; d.ldc = g.ldc; d.alpha = g.alpha; d.beta = g.beta;
-  d.mstore = g.M;
+  d.mstore = g.M; d.part = nullptr; d.kchunk = 0;
   d.lscale = nullptr; d.lmask = nullptr; d.lpart = nullptr; d.lref = nullptr; d.ldref = 0;
   d.causal = 0; d.rev = 0; d.nbatch = 1; d.zdiv = 1; d.bdiv = 1; d.kgroups = 1;
   d.sA = d.sB1 = d.sB2 = d.sC1 = d.sC2 = d.sAk = d.sBk = 0;
   d.split_n = 0; d.c_lo = nullptr; d.ldc_lo = d.sC1_lo = d.sC2_lo = 0;
+  return d;
+}
+
+// whether the four-column sum takes this output
+static bool sum4_ok(const Gemm& g) {
+  return g.N % 4 == 0 && g.ldc % 4 == 0 && (uintptr_t)g.C % (g.c_t == DT_F32 ? 16 : 8) == 0;
+}
+static bool two_ok(const Gemm& g) {
+  return g.beta == 0.f && g.m2 > 0 && g.m2 < g.M && g.N % 4 == 0 && g.ldc % 4 == 0 &&
+         (uintptr_t)g.C % 16 == 0 && (uintptr_t)g.C2 % 16 == 0 && g.c_t == DT_F32;
+}
+// the sums of one product's partials (two of them for a two-output product) added to gr
+static void add_sum(SumGroup& gr, const Gemm& g, const float* part, int splits) {
+  const int64_t total = (int64_t)g.M * g.N;
+  auto add = [&](const float* p, int64_t n, void* C, float beta) {
+    SumDev& d = gr.s[gr.n];
+    d.part = p; d.sstride = total; d.ldc = g.ldc; d.C = C; d.splits = splits; d.N = g.N;
+    d.alpha = g.alpha; d.beta = beta;
+    d.end = (gr.n ? gr.s[gr.n - 1].end : 0) + n / 4;
+    ++gr.n;
+  };
+  if (g.C2) {  // rows [0, m2) into C, [m2, M) into C2
+    const int64_t t1 = (int64_t)g.m2 * g.N;
+    add(part, t1, g.C, 0.f);
+    add(part + t1, total - t1, g.C2, 0.f);
+  } else {
+    add(part, total, g.C, g.beta);
+  }
+}
+static hipError_t run_sums(const SumGroup& gr, bool f32, double bytes, hipStream_t s) {
+  const unsigned grid = (unsigned)((gr.s[gr.n - 1].end + 255) / 256);
+  prof_begin(KC_ELEM, s);
+  if (f32) splitk_reduce4_kernel<float><<<grid, 256, 0, s>>>(gr);
+  else splitk_reduce4_kernel<bf16_t><<<grid, 256, 0, s>>>(gr);
+  prof_end(KC_ELEM, s, 0.0, bytes, KLABEL("splitk_reduce4_kernel"));
+  return hipGetLastError();
+}
+static double sum_bytes(const Gemm& g, int splits) {
+  return (double)g.M * g.N * (4.0 * splits + (g.c_t == DT_F32 ? 4.0 : 2.0) * (g.beta != 0.f ? 2.0 : 1.0));
+}
+
+hipError_t gemm_mfma(const Gemm& g, float* scratch, size_t scratch_elems, hipStream_t s, int kc,
+                     double flops, double bytes) {
+  GemmDev d = dev_of(g);
   // two outputs: always through the partials (also unsplit), summed into C and C2
   const bool two = g.C2 != nullptr;
   if (!g.a_kmajor && g.b_kmajor) return hipErrorInvalidValue;  // (no such product)
-  if (two && (g.beta != 0.f || g.m2 <= 0 || g.m2 >= g.M || g.N % 4 || g.ldc % 4 ||
-              (uintptr_t)g.C % 16 || (uintptr_t)g.C2 % 16 || g.c_t != DT_F32 || !scratch ||
-              scratch_elems < (size_t)g.M * g.N))
-    return hipErrorInvalidValue;
+  if (two && (!two_ok(g) || !scratch || scratch_elems < (size_t)g.M * g.N)) return hipErrorInvalidValue;
   const Plan p = plan_of(g, scratch ? scratch_elems : 0, ALL_KINDS);
   d.kchunk = p.kchunk;
   d.part = p.splits > 1 || two ? scratch : nullptr;
@@ -1581,38 +1658,131 @@ hipError_t gemm_mfma(const Gemm& g, float* scratch, size_t scratch_elems, hipStr
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || (p.splits == 1 && !two)) return e;
   // the split-K partials summed in a fixed order (an elementwise launch of its own)
-  int64_t total = (int64_t)g.M * g.N;
-  unsigned grid = (unsigned)((total + 255) / 256);
-  const double rbytes = (double)total * (4.0 * p.splits + (f32 ? 4.0 : 2.0) * (g.beta != 0.f ? 2.0 : 1.0));
+  if (two || sum4_ok(g)) {
+    SumGroup gr;
+    gr.n = 0;
+    add_sum(gr, g, scratch, p.splits);
+    return run_sums(gr, f32, sum_bytes(g, p.splits), s);
+  }
+  const int64_t total = (int64_t)g.M * g.N;
+  const unsigned grid = (unsigned)((total + 255) / 256);
   prof_begin(KC_ELEM, s);
-  if (two) {  // rows [0, m2) into C, [m2, M) into C2 (f32, 4-aligned: checked above)
-    const int64_t t1 = (int64_t)g.m2 * g.N, t2 = total - t1;
-    splitk_reduce4_kernel<float><<<(unsigned)((t1 / 4 + 255) / 256), 256, 0, s>>>(
-        scratch, p.splits, total, g.m2, g.N, (float*)g.C, g.ldc, g.alpha, 0.f);
-    splitk_reduce4_kernel<float><<<(unsigned)((t2 / 4 + 255) / 256), 256, 0, s>>>(
-        scratch + t1, p.splits, total, g.M - g.m2, g.N, (float*)g.C2, g.ldc, g.alpha, 0.f);
-    prof_end(KC_ELEM, s, 0.0, rbytes, KLABEL("splitk_reduce4_kernel"));
-    return hipGetLastError();
-  }
-  if (g.N % 4 == 0 && g.ldc % 4 == 0 && (uintptr_t)g.C % (f32 ? 16 : 8) == 0) {
-    const unsigned grid4 = (unsigned)((total / 4 + 255) / 256);
-    if (f32)
-      splitk_reduce4_kernel<float><<<grid4, 256, 0, s>>>(scratch, p.splits, total, g.M, g.N,
-                                                         (float*)g.C, g.ldc, g.alpha, g.beta);
-    else
-      splitk_reduce4_kernel<bf16_t><<<grid4, 256, 0, s>>>(scratch, p.splits, total, g.M, g.N,
-                                                          (bf16_t*)g.C, g.ldc, g.alpha, g.beta);
-    prof_end(KC_ELEM, s, 0.0, rbytes, KLABEL("splitk_reduce4_kernel"));
-    return hipGetLastError();
-  }
   if (f32)
     splitk_reduce_kernel<float><<<grid, 256, 0, s>>>(scratch, p.splits, total, g.M, g.N,
                                                      (float*)g.C, g.ldc, g.alpha, g.beta);
   else
     splitk_reduce_kernel<bf16_t><<<grid, 256, 0, s>>>(scratch, p.splits, total, g.M, g.N,
                                                       (bf16_t*)g.C, g.ldc, g.alpha, g.beta);
-  prof_end(KC_ELEM, s, 0.0, rbytes, KLABEL("splitk_reduce_kernel"));
+  prof_end(KC_ELEM, s, 0.0, sum_bytes(g, p.splits), KLABEL("splitk_reduce_kernel"));
   return hipGetLastError();
+}
+
+// One launch for all n products (plus one for the sums of their partials) where the time model
+// finds that quicker than a launch each: few tokens, where a launch costs more than its work
+// (about 4.6 us behind another one) and each product alone leaves CUs idle.  All on 64 x 64
+// tiles: the launch takes as long as its longest walk (`lat` per slice) or the CUs' share of
+// all slices (`bw`), so the products are split to walks of at most kc slices, kc chosen.
+// Returns hipErrorNotSupported (nothing launched) where separate launches are better.
+hipError_t gemm_mfma_group(const Gemm* g, int n, float* scratch, size_t scratch_elems, hipStream_t s,
+                           int kclass, double flops, double bytes) {
+  if (n < 2 || n > GROUP_MAX) return hipErrorNotSupported;
+  const int layout = g[0].a_kmajor ? (g[0].b_kmajor ? 0 : 1) : 2;
+  const size_t room = scratch ? scratch_elems : 0;
+  double sep = 0.0;
+  int kmax = 1;
+  for (int i = 0; i < n; ++i) {
+    if (g[i].a_kmajor != g[0].a_kmajor || g[i].b_kmajor != g[0].b_kmajor || g[i].c_t != g[0].c_t ||
+        (!g[i].a_kmajor && g[i].b_kmajor) || g[i].M <= 0 || g[i].N <= 0)
+      return hipErrorNotSupported;
+    if (g[i].C2 ? !two_ok(g[i]) : !sum4_ok(g[i])) return hipErrorNotSupported;
+    // (a product that adds to the one before it: both go as partials of one sum)
+    if (g[i].beta != 0.f && !(i > 0 && g[i].beta == 1.f && g[i].C == g[i - 1].C && g[i].M == g[i - 1].M &&
+                              g[i].N == g[i - 1].N && g[i].ldc == g[i - 1].ldc && !g[i].C2 && !g[i - 1].C2 &&
+                              g[i - 1].beta == 0.f && g[i].alpha == g[i - 1].alpha))
+      return hipErrorNotSupported;
+    sep += plan_of(g[i], room, ALL_KINDS).t;
+    kmax = std::max(kmax, (g[i].K + BK - 1) / BK);
+  }
+  const TileCost& c = TILE_COST[layout][T64];
+  const int64_t slots = (int64_t)NUM_CU * c.per_cu;
+  auto joined = [&](int i) { return g[i].beta != 0.f || (i + 1 < n && g[i + 1].beta != 0.f); };
+  auto splits_of = [&](int i, int kc) {
+    const int ks = std::max(1, (g[i].K + BK - 1) / BK), sp = (ks + kc - 1) / kc;
+    const int per = (ks + sp - 1) / sp;
+    return (ks + per - 1) / per;
+  };
+  int best_kc = 0;
+  double best_t = sep;
+  for (int kc = kmax; kc >= 2; kc = std::min(kc - 1, kc * 3 / 4)) {
+    double slices = 0.0, elems = 0.0;
+    int64_t wgs = 0;
+    int walk = 0, msp = 0;
+    for (int i = 0; i < n; ++i) {
+      const int64_t tiles = (int64_t)((g[i].M + 63) / 64) * ((g[i].N + 63) / 64);
+      const int ks = std::max(1, (g[i].K + BK - 1) / BK), sp = splits_of(i, kc);
+      wgs += tiles * sp;
+      slices += (double)tiles * ks;
+      walk = std::max(walk, (ks + sp - 1) / sp);
+      if (sp > 1 || g[i].C2 || joined(i)) {
+        elems += (double)sp * g[i].M * g[i].N;
+        msp = std::max(msp, sp);
+      }
+    }
+    if (elems > (double)room) break;  // (shorter walks need more partials)
+    // one round: as in plan_of; more: the CUs' share of all slices, then the last walks alone
+    double t = c.fixed + c.tile * ((wgs + slots - 1) / slots);
+    if (wgs <= slots) t += walk * std::max<double>(c.lat, c.bw * std::min<double>(c.per_cu, wgs / 256.0 + 0.25));
+    else t += slices / 256.0 * c.bw + 0.7 * walk * c.lat;
+    if (msp) t += 2.5 + 0.24 * msp + 0.16 * elems * 4e-6;
+    if (t < best_t) {
+      best_t = t;
+      best_kc = kc;
+    }
+  }
+  if (best_kc == 0) return hipErrorNotSupported;
+  GroupDev gr;
+  SumGroup sums;
+  gr.n = n;
+  sums.n = 0;
+  size_t off = 0;
+  int wgs = 0;
+  double sbytes = 0.0;
+  for (int i = 0; i < n; ++i) {
+    GemmDev d = dev_of(g[i]);
+    const int ks = std::max(1, (g[i].K + BK - 1) / BK), sp = splits_of(i, best_kc);
+    d.kchunk = (ks + sp - 1) / sp * BK;
+    if (sp > 1 || g[i].C2 || joined(i)) {
+      d.part = scratch + off;
+      const bool adds = g[i].beta != 0.f;
+      int all = sp;
+      if (adds) {  // its partials follow those of the product before it, one sum for both
+        all = sp + sums.s[sums.n - 1].splits;
+        sums.s[sums.n - 1].splits = all;
+      } else {
+        add_sum(sums, g[i], d.part, sp);
+      }
+      d.beta = 0.f;
+      sbytes += sum_bytes(g[i], sp);
+      off += (size_t)sp * g[i].M * g[i].N;
+    }
+    gr.tiles[i] = ((g[i].M + 63) / 64) * ((g[i].N + 63) / 64);
+    wgs += gr.tiles[i] * sp;
+    gr.end[i] = wgs;
+    gr.p[i] = d;
+  }
+  const bool f32 = g[0].c_t == DT_F32;
+  prof_begin(kclass, s);
+#define L_(AK, BK_)                                                             \
+  if (g[0].a_kmajor == AK && g[0].b_kmajor == BK_) {                            \
+    if (f32) gemm_group_kernel<AK, BK_, float><<<wgs, 256, 0, s>>>(gr);         \
+    else gemm_group_kernel<AK, BK_, bf16_t><<<wgs, 256, 0, s>>>(gr);            \
+  }
+  L_(true, true) else L_(true, false) else L_(false, false)
+#undef L_
+  prof_end(kclass, s, flops, bytes, KLABEL("gemm_group_kernel<64,64>"));
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || sums.n == 0) return e;
+  return run_sums(sums, f32, sbytes, s);
 }
 
 size_t gemm_mfma_masked_sse_parts(const Gemm& g) {
@@ -1624,16 +1794,8 @@ hipError_t gemm_mfma_masked_scale(const Gemm& g, const float* scale, const uint8
   if (g.beta != 0.f || g.alpha != 1.f || g.in_t != DT_BF16 || !scale || !g.C ||
       !g.a_kmajor || !g.b_kmajor)
     return hipErrorInvalidValue;
-  GemmDev d;
-  d.M = g.M; d.N = g.N; d.ktotal = g.K; d.nsplit = 1;
-  d.A = (const bf16_t*)g.A; d.lda = g.lda;
-  d.B = (const bf16_t*)g.B; d.ldb = g.ldb;
-  d.C = g.C; d.ldc = g.ldc; d.alpha = 1.f; d.beta = 0.f;
-  d.mstore = g.M;
+  GemmDev d = dev_of(g);
   d.lscale = scale; d.lmask = mask; d.lpart = nullptr; d.lref = nullptr; d.ldref = 0;
-  d.causal = 0; d.rev = 0; d.nbatch = 1; d.zdiv = 1; d.bdiv = 1; d.kgroups = 1;
-  d.sA = d.sB1 = d.sB2 = d.sC1 = d.sC2 = d.sAk = d.sBk = 0;
-  d.split_n = 0; d.c_lo = nullptr; d.ldc_lo = d.sC1_lo = d.sC2_lo = 0;
   // (the four-wavefront kernel reads the row mask with 32-byte scalar loads: every row tile,
   // the moved-back last one included, starts at a 4-byte aligned mask byte)
   const bool nt4_mask = (uintptr_t)mask % 4 == 0 && g.M % 4 == 0;
@@ -1648,21 +1810,13 @@ hipError_t gemm_mfma_masked_sse(const Gemm& g, const float* scale, const uint8_t
                                 const void* ref, int64_t ldref, double* part, int* nparts,
                                 hipStream_t s, const char** kernel) {
   if (g.beta != 0.f || g.alpha != 1.f || g.in_t != DT_BF16) return hipErrorInvalidValue;
-  GemmDev d;
-  d.M = g.M; d.N = g.N; d.ktotal = g.K; d.nsplit = 1;
-  d.A = (const bf16_t*)g.A; d.lda = g.lda;
-  d.B = (const bf16_t*)g.B; d.ldb = g.ldb;
-  d.C = g.C; d.ldc = g.ldc; d.alpha = 1.f; d.beta = 0.f;
-  d.mstore = g.M;
+  GemmDev d = dev_of(g);
   d.lscale = scale; d.lmask = mask; d.lpart = part;
   d.lref = (const bf16_t*)ref; d.ldref = ldref;
-  d.causal = 0; d.rev = 0; d.nbatch = 1; d.zdiv = 1; d.bdiv = 1; d.kgroups = 1;
-  d.sA = d.sB1 = d.sB2 = d.sC1 = d.sC2 = d.sAk = d.sBk = 0;
-  d.split_n = 0; d.c_lo = nullptr; d.ldc_lo = d.sC1_lo = d.sC2_lo = 0;
   // (tiles of at least 128 x 128: gemm_mfma_masked_sse_parts bounds their number; smaller
   // matrices go through one such tile)
   Plan p = plan_of(g, 0, 1u << T256 | 1u << T256x192 | 1u << T128);
-  if (p.kind == T64) p = Plan{T128, 128, 128, 1, p.kchunk};
+  if (p.kind == T64) p = Plan{T128, 128, 128, 1, p.kchunk, p.t};
   d.kchunk = p.kchunk;
   d.part = nullptr;
   *nparts = ((g.M + p.bm - 1) / p.bm) * ((g.N + p.bn - 1) / p.bn);
@@ -1675,9 +1829,9 @@ hipError_t gemm_mfma_masked_sse(const Gemm& g, const float* scale, const uint8_t
 // Batched causal products of attention's backward: dQ = dS K (A = dS^T stored [key][query],
 // M/N-contiguous, bf16 result) and dK = dS^T Q summed over a group's heads (A k-major, fp32
 // result).  BN is the output width rounded up to the supported tile widths.
-template <int BN, int WM, int WN, bool AK, typename TC, bool SHIFT>
+template <int BM, int BN, int WM, int WN, bool AK, typename TC, bool SHIFT>
 static void launch_causal(const GemmDev& d, int nbatch, hipStream_t s) {
-  const int ntm = (d.M + 255) / 256, ntn = (d.N + BN - 1) / BN;
+  const int ntm = (d.M + BM - 1) / BM, ntn = (d.N + BN - 1) / BN;
   const int items = ntm * ntn * nbatch;
   if constexpr (!AK) {
     // dQ (M-contiguous A; K ranges end at the diagonal): one tile per workgroup, dispatched
@@ -1685,7 +1839,7 @@ static void launch_causal(const GemmDev& d, int nbatch, hipStream_t s) {
     // product waits on its copies (the dS^T stream): three slices in flight (84 KB per CU)
     // instead of one 64-deep slice (56 KB) measured 3-6% faster (five stages, and a
     // persistent grid of the two-stage ring, were slower)
-    attn_ds_gemm_kernel<256, BN, WM, WN, AK, false, TC, 32, 4, SHIFT>
+    attn_ds_gemm_kernel<BM, BN, WM, WN, AK, false, TC, 32, 4, SHIFT>
         <<<dim3(items, 1), 64 * WM * WN, 0, s>>>(d);
   } else {
     // dK (K ranges start at the diagonal): persistent, 2.6% faster; as many workgroups as
@@ -1699,23 +1853,23 @@ static void launch_causal(const GemmDev& d, int nbatch, hipStream_t s) {
     if (per_cu == 0) {
       int n = 0;
       if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-              &n, attn_ds_gemm_persist_kernel<256, BN, WM, WN, AK, false, TC, 64, 2, SHIFT>,
+              &n, attn_ds_gemm_persist_kernel<BM, BN, WM, WN, AK, false, TC, 64, 2, SHIFT>,
               64 * WM * WN, 0) != hipSuccess || n < 1)
         n = 1;
       per_cu = n;
       occ[dev].store(n, std::memory_order_relaxed);
     }
-    attn_ds_gemm_persist_kernel<256, BN, WM, WN, AK, false, TC, 64, 2, SHIFT>
+    attn_ds_gemm_persist_kernel<BM, BN, WM, WN, AK, false, TC, 64, 2, SHIFT>
         <<<dim3(std::min(items, NUM_CU * per_cu), 1), 64 * WM * WN, 0, s>>>(d);
   }
 }
 
 template <bool AK, typename TC, bool SHIFT>
 static hipError_t dispatch_causal(const GemmDev& d, int nbatch, hipStream_t s) {
-  if (d.N <= 64) launch_causal<64, 4, 2, AK, TC, SHIFT>(d, nbatch, s);
-  else if (d.N <= 96) launch_causal<96, 4, 1, AK, TC, SHIFT>(d, nbatch, s);
-  else if (d.N <= 128) launch_causal<128, 4, 2, AK, TC, SHIFT>(d, nbatch, s);
-  else if (d.N <= 192) launch_causal<192, 4, 2, AK, TC, SHIFT>(d, nbatch, s);
+  if (d.N <= 64) launch_causal<256, 64, 4, 2, AK, TC, SHIFT>(d, nbatch, s);
+  else if (d.N <= 96) launch_causal<256, 96, 4, 1, AK, TC, SHIFT>(d, nbatch, s);
+  else if (d.N <= 128) launch_causal<256, 128, 4, 2, AK, TC, SHIFT>(d, nbatch, s);
+  else if (d.N <= 192) launch_causal<256, 192, 4, 2, AK, TC, SHIFT>(d, nbatch, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -1748,7 +1902,7 @@ hipError_t gemm_mfma_causal(const Gemm& g, const GemmBatch& bt, hipStream_t s) {
   d.sAk = bt.sAk; d.sBk = bt.sBk;
   d.split_n = bt.split_n; d.c_lo = (bf16_t*)bt.c_lo;
   d.ldc_lo = bt.ldc_lo; d.sC1_lo = bt.sC1_lo; d.sC2_lo = bt.sC2_lo;
-  if (g.M % 256 == 0)
+  if (g.M % 256 == 0)  // whole row tiles of either height
     return g.a_kmajor ? dispatch_causal<true, float, false>(d, bt.nbatch, s)
                       : dispatch_causal<false, bf16_t, false>(d, bt.nbatch, s);
   return g.a_kmajor ? dispatch_causal<true, float, true>(d, bt.nbatch, s)

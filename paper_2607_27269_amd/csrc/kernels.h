@@ -59,6 +59,9 @@ struct Gemm {
 // Scratch (fp32 elements) a GEMM of this shape needs for split-K partials.
 size_t gemm_scratch_elems(const Gemm& g);
 hipError_t gemm(const Gemm& g, float* scratch, size_t scratch_elems, hipStream_t s);
+// n independent products (in order; one with beta = 1 may add to the one before it), in one
+// launch where that is quicker.
+hipError_t gemm_group(const Gemm* g, int n, float* scratch, size_t scratch_elems, hipStream_t s);
 
 // Per-head strided view: element (n, i, d) at ptr[n*tok + (i / div)*head + d].
 struct HeadView {

@@ -8,6 +8,11 @@ size_t gemm_mfma_scratch_elems(const Gemm& g);
 // an elementwise launch of its own).
 hipError_t gemm_mfma(const Gemm& g, float* scratch, size_t scratch_elems, hipStream_t s, int kc,
                      double flops, double bytes);
+// n products of one layout as one launch (plus one for the sums of partials), where that is
+// modelled to be quicker than a launch each; hipErrorNotSupported (nothing launched) elsewhere.
+// A product with beta = 1 whose C is the previous one's adds to it.
+hipError_t gemm_mfma_group(const Gemm* g, int n, float* scratch, size_t scratch_elems, hipStream_t s,
+                           int kc, double flops, double bytes);
 // C = scale[0] mask[m] X[m, n] with X = A B^T (mask null = all rows) and part[t] = the sum
 // over output tile t of mask[m] X[m, n]^2, or of mask[m] X[m, n] ref[m, n] (bf16, row
 // stride ldref) when ref is given, in a fixed order; *nparts = the number of tiles (at most
