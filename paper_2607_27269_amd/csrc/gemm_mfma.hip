@@ -990,8 +990,8 @@ template <int BM, int BN, int WM, int WN, bool AK, bool BKM, typename TC, int BK
 __global__ __launch_bounds__(64 * WM * WN) void gemm_mfma_kernel(GemmDev g) {
   gemm_tile<BM, BN, WM, WN, AK, BKM, TC, BK, NST>(g, blockIdx.x, blockIdx.y);
 }
-// Several products of one layout in one launch, on 64 x 64 tiles: workgroup ids run over the
-// (split, tile) pairs of the first product, then of the second, ..
+// Several products of one layout in one launch: workgroup ids run over the (split, tile) pairs
+// of the first product, then of the second, ..
 constexpr int GROUP_MAX = 5;
 struct GroupDev {
   int n;
@@ -999,7 +999,7 @@ struct GroupDev {
   int tiles[GROUP_MAX];  // tiles of product i
   GemmDev p[GROUP_MAX];
 };
-template <bool AK, bool BKM, typename TC>
+template <int BM, int BN, int NST, bool AK, bool BKM, typename TC>
 __global__ __launch_bounds__(256) void gemm_group_kernel(GroupDev gr) {
   const int w = blockIdx.x;
   int i = 0, beg = 0;
@@ -1010,7 +1010,7 @@ __global__ __launch_bounds__(256) void gemm_group_kernel(GroupDev gr) {
       beg = gr.end[j];
     }
   const int tiles = gr.tiles[i];
-  gemm_tile<64, 64, 2, 2, AK, BKM, TC, 64, 4>(gr.p[i], (w - beg) % tiles, (w - beg) / tiles);
+  gemm_tile<BM, BN, 2, 2, AK, BKM, TC, 64, NST>(gr.p[i], (w - beg) % tiles, (w - beg) / tiles);
 }
 // the same tile program for the dS products of attention's backward, on the 32 x 32-tiled
 // dS^T (own name, so that profiles tell them apart)
@@ -1677,11 +1677,18 @@ hipError_t gemm_mfma(const Gemm& g, float* scratch, size_t scratch_elems, hipStr
   return hipGetLastError();
 }
 
+// 128 x 64 tiles, three slices in flight, two workgroups per CU (group launches only; fitted as
+// TILE_COST)
+constexpr TileCost COST_128x64[3] = {{128, 64, 2, 5.5f, 0.f, 0.54f, 0.45f},
+                                     {128, 64, 2, 5.6f, 0.f, 0.56f, 0.452f},
+                                     {128, 64, 2, 2.2f, 3.5f, 0.69f, 0.494f}};
+
 // One launch for all n products (plus one for the sums of their partials) where the time model
 // finds that quicker than a launch each: few tokens, where a launch costs more than its work
-// (about 4.6 us behind another one) and each product alone leaves CUs idle.  All on 64 x 64
-// tiles: the launch takes as long as its longest walk (`lat` per slice) or the CUs' share of
-// all slices (`bw`), so the products are split to walks of at most kc slices, kc chosen.
+// (about 4.6 us behind another one) and each product alone leaves CUs idle.  All on one of
+// three tiles: the launch takes as long as its longest walk (`lat` per slice) or the CUs' share
+// of all slices (`bw`, per output least for the largest tile), so the products are split to
+// walks of at most kc slices, tile and kc chosen.
 // Returns hipErrorNotSupported (nothing launched) where separate launches are better.
 hipError_t gemm_mfma_group(const Gemm* g, int n, float* scratch, size_t scratch_elems, hipStream_t s,
                            int kclass, double flops, double bytes) {
@@ -1703,43 +1710,51 @@ hipError_t gemm_mfma_group(const Gemm* g, int n, float* scratch, size_t scratch_
     sep += plan_of(g[i], room, ALL_KINDS).t;
     kmax = std::max(kmax, (g[i].K + BK - 1) / BK);
   }
-  const TileCost& c = TILE_COST[layout][T64];
-  const int64_t slots = (int64_t)NUM_CU * c.per_cu;
+  // (the mixes of output types that the step has: bf16, and fp32 for the weight gradients)
+  if ((g[0].c_t == DT_F32) != (layout == 2)) return hipErrorNotSupported;
   auto joined = [&](int i) { return g[i].beta != 0.f || (i + 1 < n && g[i + 1].beta != 0.f); };
   auto splits_of = [&](int i, int kc) {
     const int ks = std::max(1, (g[i].K + BK - 1) / BK), sp = (ks + kc - 1) / kc;
     const int per = (ks + sp - 1) / sp;
     return (ks + per - 1) / per;
   };
-  int best_kc = 0;
+  int best_kc = 0, best_tile = 0;
   double best_t = sep;
-  for (int kc = kmax; kc >= 2; kc = std::min(kc - 1, kc * 3 / 4)) {
-    double slices = 0.0, elems = 0.0;
-    int64_t wgs = 0;
-    int walk = 0, msp = 0;
-    for (int i = 0; i < n; ++i) {
-      const int64_t tiles = (int64_t)((g[i].M + 63) / 64) * ((g[i].N + 63) / 64);
-      const int ks = std::max(1, (g[i].K + BK - 1) / BK), sp = splits_of(i, kc);
-      wgs += tiles * sp;
-      slices += (double)tiles * ks;
-      walk = std::max(walk, (ks + sp - 1) / sp);
-      if (sp > 1 || g[i].C2 || joined(i)) {
-        elems += (double)sp * g[i].M * g[i].N;
-        msp = std::max(msp, sp);
+  for (int tile = 0; tile < 3; ++tile) {
+    const TileCost& c = tile == 0   ? TILE_COST[layout][T64]
+                        : tile == 1 ? COST_128x64[layout]
+                                    : TILE_COST[layout][T128];
+    const int64_t slots = (int64_t)NUM_CU * c.per_cu;
+    for (int kc = kmax; kc >= 2; kc = std::min(kc - 1, kc * 3 / 4)) {
+      double slices = 0.0, elems = 0.0;
+      int64_t wgs = 0;
+      int walk = 0, msp = 0;
+      for (int i = 0; i < n; ++i) {
+        const int64_t tiles = (int64_t)((g[i].M + c.bm - 1) / c.bm) * ((g[i].N + c.bn - 1) / c.bn);
+        const int ks = std::max(1, (g[i].K + BK - 1) / BK), sp = splits_of(i, kc);
+        wgs += tiles * sp;
+        slices += (double)tiles * ks;
+        walk = std::max(walk, (ks + sp - 1) / sp);
+        if (sp > 1 || g[i].C2 || joined(i)) {
+          elems += (double)sp * g[i].M * g[i].N;
+          msp = std::max(msp, sp);
+        }
       }
-    }
-    if (elems > (double)room) break;  // (shorter walks need more partials)
-    // one round: as in plan_of; more: the CUs' share of all slices, then the last walks alone
-    double t = c.fixed + c.tile * ((wgs + slots - 1) / slots);
-    if (wgs <= slots) t += walk * std::max<double>(c.lat, c.bw * std::min<double>(c.per_cu, wgs / 256.0 + 0.25));
-    else t += slices / 256.0 * c.bw + 0.7 * walk * c.lat;
-    if (msp) t += 2.5 + 0.24 * msp + 0.16 * elems * 4e-6;
-    if (t < best_t) {
-      best_t = t;
-      best_kc = kc;
+      if (elems > (double)room) break;  // (shorter walks need more partials)
+      // one round: as in plan_of; more: the CUs' share of all slices, then the last walks alone
+      double t = c.fixed + c.tile * ((wgs + slots - 1) / slots);
+      if (wgs <= slots) t += walk * std::max<double>(c.lat, c.bw * std::min<double>(c.per_cu, wgs / 256.0 + 0.25));
+      else t += slices / 256.0 * c.bw + 0.7 * walk * c.lat;
+      if (msp) t += 2.5 + 0.24 * msp + 0.16 * elems * 4e-6;
+      if (t < best_t) {
+        best_t = t;
+        best_kc = kc;
+        best_tile = tile;
+      }
     }
   }
   if (best_kc == 0) return hipErrorNotSupported;
+  const int bm = best_tile == 0 ? 64 : 128, bn = best_tile == 2 ? 128 : 64;
   GroupDev gr;
   SumGroup sums;
   gr.n = n;
@@ -1765,21 +1780,22 @@ hipError_t gemm_mfma_group(const Gemm* g, int n, float* scratch, size_t scratch_
       sbytes += sum_bytes(g[i], sp);
       off += (size_t)sp * g[i].M * g[i].N;
     }
-    gr.tiles[i] = ((g[i].M + 63) / 64) * ((g[i].N + 63) / 64);
+    gr.tiles[i] = ((g[i].M + bm - 1) / bm) * ((g[i].N + bn - 1) / bn);
     wgs += gr.tiles[i] * sp;
     gr.end[i] = wgs;
     gr.p[i] = d;
   }
   const bool f32 = g[0].c_t == DT_F32;
   prof_begin(kclass, s);
-#define L_(AK, BK_)                                                             \
-  if (g[0].a_kmajor == AK && g[0].b_kmajor == BK_) {                            \
-    if (f32) gemm_group_kernel<AK, BK_, float><<<wgs, 256, 0, s>>>(gr);         \
-    else gemm_group_kernel<AK, BK_, bf16_t><<<wgs, 256, 0, s>>>(gr);            \
+#define L_(AK, BK_, TC)                                                                           \
+  {                                                                                               \
+    if (best_tile == 0) gemm_group_kernel<64, 64, 4, AK, BK_, TC><<<wgs, 256, 0, s>>>(gr);        \
+    else if (best_tile == 1) gemm_group_kernel<128, 64, 3, AK, BK_, TC><<<wgs, 256, 0, s>>>(gr);  \
+    else gemm_group_kernel<128, 128, 2, AK, BK_, TC><<<wgs, 256, 0, s>>>(gr);                     \
   }
-  L_(true, true) else L_(true, false) else L_(false, false)
+  if (layout == 0) L_(true, true, bf16_t) else if (layout == 1) L_(true, false, bf16_t) else L_(false, false, float)
 #undef L_
-  prof_end(kclass, s, flops, bytes, KLABEL("gemm_group_kernel<64,64>"));
+  prof_end(kclass, s, flops, bytes, KLABEL("gemm_group_kernel"));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || sums.n == 0) return e;
   return run_sums(sums, f32, sbytes, s);
