@@ -34,12 +34,12 @@ KCLASS_KERNELS = {"gemm_nt": "gemm_mfma_persist_kernel<..., true, true, ...> (an
                   "gemm_nn": "gemm_mfma_persist_kernel<..., true, false, ...>",
                   "gemm_tn": "gemm_mfma_persist_kernel<..., false, false, float> + splitk_reduce_kernel",
                   "attn_fwd": "attn_fwd_persist_kernel (or attn_fwd_mfma_kernel)",
-                  "attn_bwd_dkdv": "attn_dv_mfma_kernel (or attn_dkdv_mfma_kernel)",
-                  "attn_bwd_dq": "attn_ds_gemm_kernel<..., false, false, ...> (or attn_dq_mfma_kernel)",
+                  "attn_bwd_dkdv": "attn_dv_mfma_kernel",
+                  "attn_bwd_dq": "attn_ds_gemm_kernel<..., false, false, ...>",
                   "attn_bwd_dk": "attn_ds_gemm_persist_kernel<..., true, false, float>",
                   "loss": "mask_count_kernel + loss_main_kernel + loss_final_kernel",
-                  "elementwise": "rope_table_kernel, rope_apply_kernel, attn_delta_kernel, dkpe_finish_kernel, "
-                                 "kcat_kernel, attn_stats_t_kernel"}
+                  "elementwise": "step_prepare_kernel, rope_group8_kernel, attn_delta_bf16x8_kernel, "
+                                 "attn_bwd_prep_kernel, bwd_finish_kernel, split_sum_kernel, splitk_reduce4_kernel"}
 
 
 class MlaError(RuntimeError):

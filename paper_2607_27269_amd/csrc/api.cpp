@@ -326,11 +326,33 @@ static void student_h_products(const Dims& d, const Layout& L, const void* h, co
   out[1] = mk(N, kv_out, D, h, D, true, w->Wdkv_kr, D, true, at(ws, L.s_ckv), kv_out, d.t, d.t);
 }
 
+// The products of the latents: q = W_UQ c^Q, [k^nope; v] = W^UKV c^KV (Eq. 5); how many
+static int student_up_products(const Dims& d, const Layout& L, const mla_student_w* w, void* ws, Gemm* out) {
+  const int N = (int)d.N, rq = (int)d.rq, rkv = (int)d.rkv, nq = (int)(d.H * d.dqk);
+  const int nk = (int)(d.Gkv * d.dn), nv = (int)(d.Gkv * d.dv), kv_out = (int)d.kv_out;
+  const void* ckv = at(ws, L.s_ckv);
+  int n = 0;
+  if (rq > 0) out[n++] = mk(N, nq, rq, at(ws, L.s_cq), rq, true, w->Wuq, rq, true, at(ws, L.s_q), nq, d.t, d.t);
+  if (nk > 0) out[n++] = mk(N, nk, rkv, ckv, kv_out, true, w->Wuk, rkv, true, at(ws, L.s_knope), nk, d.t, d.t);
+  out[n++] = mk(N, nv, rkv, ckv, kv_out, true, w->Wuv, rkv, true, at(ws, L.s_v), nv, d.t, d.t);
+  return n;
+}
+
+// decoupled RoPE on q^rope (rope group i / (H/G_r)) and on k^PE
+static void student_rotations(const Dims& d, const Layout& L, void* ws, RopeArgs* out) {
+  const int H = (int)d.H, Gr = (int)d.Gr, dr = (int)d.dr;
+  const float* cs = (const float*)at(ws, L.s_cos);
+  const float* sn = (const float*)at(ws, L.s_sin);
+  out[0] = RopeArgs{at(ws, L.s_q), H, (int64_t)H * d.dqk, d.dqk, (int)d.dn, dr / 2, H / Gr, cs, sn};
+  out[1] = RopeArgs{at(ws, L.s_ckv), Gr, d.kv_out, dr, (int)d.rkv, dr / 2, 1, cs, sn};
+}
+
 // Teacher forward up to the attention output o_t (ws region t_o); with A_t also the frozen
-// output projection; with sw also the student's products of h, next to the teacher's.
+// output projection.  With sw (the single-call step) also everything of the student up to its
+// attention and the count of valid tokens of `mask`: both blocks' work shares launches.
 static int teacher_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
                         const mla_teacher_w* w, float* A_t, void* ws, hipStream_t s,
-                        const mla_student_w* sw = nullptr) {
+                        const mla_student_w* sw = nullptr, const uint8_t* mask = nullptr) {
   const Dims d = dims_of(cfg);
   const int N = (int)d.N, D = (int)d.D, H = (int)d.H, G = (int)d.G, dk = (int)d.dk;
   const int64_t ld_qkv = (H + 2 * G) * (int64_t)dk;
@@ -341,7 +363,13 @@ static int teacher_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h
   const size_t ts = d.ts;
   const Scratch sk = fwd_scratch(L, ws);
 
-  HIP_TRY(rope_tables(w->inv_freq, 1, (int)d.T, dk / 2, cs, sn, s));
+  if (sw) {
+    const RopeTable ta{w->inv_freq, 1, dk / 2, cs, sn};
+    const RopeTable tb{sw->inv_freq, (int)d.Gr, (int)d.dr / 2, (float*)at(ws, L.s_cos), (float*)at(ws, L.s_sin)};
+    HIP_TRY(step_prepare(ta, tb, (int)d.T, mask, d.N, D, at(ws, L.l_scr), s));
+  } else {
+    HIP_TRY(rope_tables(w->inv_freq, 1, (int)d.T, dk / 2, cs, sn, s));
+  }
   // Eq. 1: q = W^Q h, k = W^K h, v = W^V h  (columns [Q | K | V] of one buffer)
   Gemm pr[5] = {
       mk(N, H * dk, D, h, D, true, w->Wq, D, true, qkv, ld_qkv, d.t, d.t),
@@ -349,12 +377,19 @@ static int teacher_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h
       mk(N, G * dk, D, h, D, true, w->Wv, D, true, qkv + (size_t)(H + G) * dk * ts, ld_qkv, d.t, d.t)};
   if (sw) student_h_products(d, L, h, sw, ws, pr + 3);
   HIP_TRY(gemm_group(pr, sw ? 5 : 3, sk.p, sk.elems, s));
+  if (sw) {
+    Gemm up[3];
+    const int nup = student_up_products(d, L, sw, ws, up);
+    HIP_TRY(gemm_group(up, nup, sk.p, sk.elems, s));
+  }
   // R_t on queries and keys (Sec. 3.1); on the matrix-core path the attention kernel rotates
   // the queries as it loads them (the teacher's rotated queries are not needed elsewhere)
   const bool q_on_load = d.t == DT_BF16 && attn_mfma_supported(dk, dk) && dk % 32 == 0;
   if (!q_on_load)
     HIP_TRY(rope_apply(qkv, d.t, N, (int)d.T, H, ld_qkv, dk, 0, dk / 2, H, cs, sn, s));
-  HIP_TRY(rope_apply(qkv + (size_t)H * dk * ts, d.t, N, (int)d.T, G, ld_qkv, dk, 0, dk / 2, G, cs, sn, s));
+  RopeArgs rot[3] = {{qkv + (size_t)H * dk * ts, G, ld_qkv, dk, 0, dk / 2, G, cs, sn}};
+  if (sw) student_rotations(d, L, ws, rot + 1);
+  HIP_TRY(rope_group(rot, sw ? 3 : 1, d.t, N, (int)d.T, s));
   // Eq. 2-4: causal softmax attention, head i reads KV group i / (H/G)
   Attn a;
   a.B = (int)d.B; a.T = (int)d.T; a.H = H; a.dqk = dk; a.dnope = dk; a.dv = dk;
@@ -392,10 +427,11 @@ static bool student_w_ok(const mla_recon_cfg* cfg, const mla_student_w* w) {
 
 // Student forward up to the attention output o_s (kept in ws for the backward); then
 // A_s = o_s W_O^T when A_s is given, and o_diff = o_s - o_ref (storage dtype, same layout)
-// when o_diff is given.  have_h_products: student_h_products have run (with the teacher's).
+// when o_diff is given.  have_inputs: everything before the attention has run
+// (with the teacher's).
 static int student_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
                         const mla_student_w* w, const void* Wo, float* A_s, const void* o_ref,
-                        void* o_diff, void* ws, hipStream_t s, bool have_h_products = false) {
+                        void* o_diff, void* ws, hipStream_t s, bool have_inputs = false) {
   const Dims d = dims_of(cfg);
   const int N = (int)d.N, D = (int)d.D, H = (int)d.H, T = (int)d.T;
   const int rq = (int)d.rq, rkv = (int)d.rkv, dn = (int)d.dn, dr = (int)d.dr, dqk = (int)d.dqk;
@@ -412,25 +448,17 @@ static int student_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h
   float* lse = (float*)at(ws, L.s_lse);
   const Scratch sk = fwd_scratch(L, ws);
 
-  HIP_TRY(rope_tables(w->inv_freq, Gr, T, dr / 2, cs, sn, s));
-  // low-rank query: c^Q = W_DQ h, q = W_UQ c^Q  (q = W_UQ h when r_q = 0); Eq. 5:
-  // [c^KV | k^PE] = [W^DKV; W^KR] h, [k^nope; v] = W^UKV c^KV
-  if (!have_h_products) {
-    Gemm pr[2];
+  if (!have_inputs) {
+    HIP_TRY(rope_tables(w->inv_freq, Gr, T, dr / 2, cs, sn, s));
+    Gemm pr[3];
     student_h_products(d, L, h, w, ws, pr);
     HIP_TRY(gemm_group(pr, 2, sk.p, sk.elems, s));
+    const int nup = student_up_products(d, L, w, ws, pr);
+    HIP_TRY(gemm_group(pr, nup, sk.p, sk.elems, s));
+    RopeArgs rot[2];
+    student_rotations(d, L, ws, rot);
+    HIP_TRY(rope_group(rot, 2, d.t, N, T, s));
   }
-  Gemm up[3];
-  int nup = 0;
-  if (rq > 0)
-    up[nup++] = mk(N, H * dqk, rq, cq, rq, true, w->Wuq, rq, true, q, (int64_t)H * dqk, d.t, d.t);
-  if (dn > 0)
-    up[nup++] = mk(N, Gkv * dn, rkv, ckv, kv_out, true, w->Wuk, rkv, true, knope, (int64_t)Gkv * dn, d.t, d.t);
-  up[nup++] = mk(N, Gkv * dv, rkv, ckv, kv_out, true, w->Wuv, rkv, true, v, (int64_t)Gkv * dv, d.t, d.t);
-  HIP_TRY(gemm_group(up, nup, sk.p, sk.elems, s));
-  // decoupled RoPE on q^rope (rope group i / (H/G_r)) and on k^PE
-  HIP_TRY(rope_apply(q, d.t, N, T, H, (int64_t)H * dqk, dqk, dn, dr / 2, H / Gr, cs, sn, s));
-  HIP_TRY(rope_apply(ckv, d.t, N, T, Gr, kv_out, dr, rkv, dr / 2, 1, cs, sn, s));
   // Eq. 2-4 with q = [q^nope; R q^rope], k = [k^nope_{g(i)}; R k^PE_{r(i)}]
   Attn a;
   a.B = (int)d.B; a.T = T; a.H = H; a.dqk = dqk; a.dnope = dn; a.dv = dv;
@@ -488,7 +516,8 @@ static int check_grads(const mla_recon_cfg* cfg, const mla_student_grads* gr, co
 static int bwd_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
                     const mla_student_w* w, const void* Wo, const void* dA,
                     const mla_student_grads* gr, void* ws, hipStream_t s,
-                    const void* loss_ref = nullptr, double* loss_part = nullptr) {
+                    const void* loss_ref = nullptr, double* loss_part = nullptr,
+                    float* loss = nullptr) {
   const bool need_q = gr->dWuq || gr->dWdq;
   const bool need_kv = gr->dWuk || gr->dWuv || gr->dWdkv_kr;
   if (!need_q && !need_kv) return MLA_OK;
@@ -546,8 +575,22 @@ static int bwd_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
   HIP_TRY(attn_bwd(ab, s));
   const Scratch sk = bwd_scratch(d, L, ws);
 
-  // data gradients: dc^Q = dq W_UQ; Eq. 5 backward dc^KV = dk^nope W_UK + dv W_UV and
-  // dk^PE = R^T sum of the head partials
+  // R^T on the rotary block of dq, dk^PE = R^T sum of the head partials, Eq. 11 from its partials
+  // (the vector-ALU path has rotated dq itself)
+  const bool want_pe = need_kv && gr->dWdkv_kr;
+  if (t == DT_BF16 && attn_mfma_supported(dqk, dv)) {
+    const RopeArgs rot{dq, H, (int64_t)H * dqk, dqk, dn, dr / 2, H / Gr, cs, sn};
+    HIP_TRY(bwd_finish(&rot, want_pe ? dkpe : nullptr, dckv + (size_t)rkv * ts, kv_out, N, T, Gr, Gkv / Gr,
+                       dr, cs, sn, loss_part, loss_part ? attn_delta_parts((int64_t)d.N * H) : 0, D,
+                       at(ws, L.l_scr), loss, s));
+  } else {
+    if (want_pe)
+      HIP_TRY(dkpe_finish(dkpe, dckv + (size_t)rkv * ts, t, kv_out, N, T, Gr, Gkv / Gr, dr, cs, sn, s));
+    if (loss_part)  // (bf16 on the vector-ALU attention: only the loss is left)
+      HIP_TRY(bwd_finish(nullptr, nullptr, nullptr, 0, N, T, Gr, Gkv / Gr, dr, cs, sn, loss_part,
+                         attn_delta_parts((int64_t)d.N * H), D, at(ws, L.l_scr), loss, s));
+  }
+  // data gradients: dc^Q = dq W_UQ; Eq. 5 backward dc^KV = dk^nope W_UK + dv W_UV
   Gemm pr[4];
   int np = 0;
   if (need_q && gr->dWdq)
@@ -558,8 +601,6 @@ static int bwd_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
     pr[np++] = mk(N, rkv, Gkv * dv, dkv + (size_t)Gkv * dn * ts, ld_dkv, true, w->Wuv, rkv, false, dckv, kv_out, t, t, dn > 0 ? 1.f : 0.f);
   }
   if (np) HIP_TRY(gemm_group(pr, np, sk.p, sk.elems, s));
-  if (need_kv && gr->dWdkv_kr)
-    HIP_TRY(dkpe_finish(dkpe, dckv + (size_t)rkv * ts, t, kv_out, N, T, Gr, Gkv / Gr, dr, cs, sn, s));
   // weight gradients: dW_UQ = dq^T c^Q, dW_DQ = dc^Q^T h, dW_UK = dk^nope^T c^KV,
   // dW_UV = dv^T c^KV, d[W_DKV; W_KR] = [dc^KV | dk^PE]^T h
   np = 0;
@@ -619,13 +660,13 @@ static int gram_impl(const Dims& d, const Layout& L, const void* Wo, void* ws, h
 static int student_step_impl(const mla_recon_cfg* cfg, const Layout& L, const void* h,
                              const mla_student_w* sw, const void* Wo, const uint8_t* mask,
                              float* loss, void* dA, const mla_student_grads* gr, void* ws,
-                             hipStream_t s, bool have_h_products = false) {
+                             hipStream_t s, bool have_inputs = false) {
   const Dims d = dims_of(cfg);
   int rc;
   // o_s (kept for the backward) and o_s - o_t, the latter into the teacher's q/k/v region,
   // which is free once the teacher's attention has run
   void* odiff = at(ws, L.t_qkv);
-  if ((rc = student_impl(cfg, L, h, sw, Wo, nullptr, at(ws, L.t_o), odiff, ws, s, have_h_products)))
+  if ((rc = student_impl(cfg, L, h, sw, Wo, nullptr, at(ws, L.t_o), odiff, ws, s, have_inputs)))
     return rc;
   // A_s - A_t = (o_s - o_t) W_O^T: both blocks end in the same frozen W_O
   const int N = (int)d.N, D = (int)d.D, HV = (int)(d.H * d.dv);
@@ -637,18 +678,14 @@ static int student_step_impl(const mla_recon_cfg* cfg, const Layout& L, const vo
     double* parts = (double*)at(ws, L.l_diff);
     void* dO = at(ws, L.b_do);
     int nparts = 0;
-    HIP_TRY(loss_prepare(mask, d.N, D, scr, s));
+    if (!have_inputs) HIP_TRY(loss_prepare(mask, d.N, D, scr, s));
     const bool any_grad = gr->dWdq || gr->dWuq || gr->dWdkv_kr || gr->dWuk || gr->dWuv;
     if (any_grad && d.dv % 8 == 0) {
       // the product writes dO only; the backward's delta pass, which streams dO anyway,
       // sums dO . (o_s - o_t) = 2 L (so the product's epilogue does not read o_s - o_t)
       HIP_TRY(gemm_masked_scale(mk(N, HV, HV, odiff, HV, true, at(ws, L.l_gram), HV, true, dO, HV, d.t, d.t),
                                 loss_scale(scr), mask, s));
-      double* dot = (double*)at(ws, L.l_dot);
-      int rc = bwd_impl(cfg, L, h, sw, Wo, nullptr, gr, ws, s, odiff, dot);
-      if (rc) return rc;
-      HIP_TRY(loss_from_dot(dot, attn_delta_parts((int64_t)d.N * d.H), D, loss, scr, s));
-      return MLA_OK;
+      return bwd_impl(cfg, L, h, sw, Wo, nullptr, gr, ws, s, odiff, (double*)at(ws, L.l_dot), loss);
     }
     HIP_TRY(gemm_masked_sse(mk(N, HV, HV, odiff, HV, true, at(ws, L.l_gram), HV, true, dO, HV, d.t, d.t),
                             loss_scale(scr), mask, odiff, HV, parts, &nparts, s));
@@ -662,7 +699,7 @@ static int student_step_impl(const mla_recon_cfg* cfg, const Layout& L, const vo
     void* scr = at(ws, L.l_scr);
     double* parts = (double*)at(ws, L.l_diff);
     int nparts = 0;
-    HIP_TRY(loss_prepare(mask, d.N, D, scr, s));
+    if (!have_inputs) HIP_TRY(loss_prepare(mask, d.N, D, scr, s));
     HIP_TRY(gemm_masked_sse(mk(N, D, HV, odiff, HV, true, Wo, HV, true, dA, D, d.t, d.t),
                             loss_scale(scr), mask, nullptr, 0, parts, &nparts, s));
     HIP_TRY(loss_from_parts(parts, nparts, D, loss, scr, s));
@@ -697,7 +734,7 @@ int mla_recon_step(const mla_recon_cfg* cfg, const void* h, const mla_teacher_w*
   Layout L;
   if ((rc = check_ws(cfg, ws, ws_bytes, &L))) return rc;
   hipStream_t s = (hipStream_t)hip_stream;
-  if ((rc = teacher_impl(cfg, L, h, tw, nullptr, ws, s, sw))) return rc;
+  if ((rc = teacher_impl(cfg, L, h, tw, nullptr, ws, s, sw, mask))) return rc;
   if (cfg->dtype == MLA_BF16 && !dA && (rc = gram_impl(dims_of(cfg), L, tw->Wo, ws, s))) return rc;
   return student_step_impl(cfg, L, h, sw, tw->Wo, mask, loss, dA, gr, ws, s, true);
 }

@@ -14,7 +14,7 @@
 //   the keys gathered per group into one [token][group][dqk] tensor; no recomputation of
 //   S or dP.
 // The dS^T buffer holds at most 16 GiB: larger batches run in chunks of whole sequences.
-// The rotary block of dQ is then rotated back with R^T.
+// The rotary block of dQ is then rotated back with R^T (bwd_finish).
 #include <algorithm>
 
 #include "attn_common.h"
@@ -73,27 +73,6 @@ constexpr int DS_STORES = DV_BQ * 32 * 2 / (64 * 16);
 constexpr int DV_NST = 3;  // LDS stages: a step's copies are issued two steps ahead
 constexpr int DV_WAVES = 8;
 constexpr int DV_BKB = 32 * DV_WAVES;  // keys per workgroup
-
-// [2][H][B][Tpad] fp32: log2-scaled lse (+inf past the sequence end) and delta (0 there)
-__global__ void attn_stats_t_kernel(const float* __restrict__ lse, const float* __restrict__ delta,
-                                    int B, int T, int H, int Tpad, float* __restrict__ out) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = 2LL * H * B * Tpad;
-  if (idx >= total) return;
-  const int q = (int)(idx % Tpad);
-  const int64_t r = idx / Tpad;
-  const int b = (int)(r % B);
-  const int h = (int)((r / B) % H);
-  const int part = (int)(r / ((int64_t)B * H));
-  float v;
-  if (q < T) {
-    const int64_t src = ((int64_t)b * T + q) * H + h;
-    v = part == 0 ? lse[src] * LOG2E : delta[src];
-  } else {
-    v = part == 0 ? INFINITY : 0.f;
-  }
-  out[idx] = v;
-}
 
 template <int DQK, int DV>
 struct DvStage {
@@ -438,13 +417,35 @@ __global__ __launch_bounds__(64 * DV_WAVES, 8 / DV_WAVES) void attn_dv_mfma_kern
     }
 }
 
-// kcat[n][g][d] = the logit key of Ka group g at token n: d < dnope from Ka, the rest from
-// Kb (rope group of the group's first head); 8 elements per thread
-__global__ void kcat_kernel(AttnDev a, int G, int DQK, bf16_t* __restrict__ out) {
+// What the chunk's kernels read besides the forward's tensors, in one launch: the statistics
+// [2][H][B][Tpad] fp32 (log2-scaled lse, +inf past the sequence end, and delta, 0 there), then
+// kcat[n][g][d], the logit key of Ka group g at token n: d < dnope from Ka, the rest from Kb
+// (rope group of the group's first head), 8 elements per thread.
+__global__ __launch_bounds__(256) void attn_bwd_prep_kernel(AttnDev a, const float* __restrict__ lse,
+                                                            const float* __restrict__ delta, int Tpad,
+                                                            float* __restrict__ stat, int stat_blocks, int G,
+                                                            int DQK, bf16_t* __restrict__ kcat) {
+  if ((int)blockIdx.x < stat_blocks) {
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= 2LL * a.H * a.B * Tpad) return;
+    const int q = (int)(idx % Tpad);
+    const int64_t r = idx / Tpad;
+    const int b = (int)(r % a.B);
+    const int h = (int)((r / a.B) % a.H);
+    const int part = (int)(r / ((int64_t)a.B * a.H));
+    float v;
+    if (q < a.T) {
+      const int64_t src = ((int64_t)b * a.T + q) * a.H + h;
+      v = part == 0 ? lse[src] * LOG2E : delta[src];
+    } else {
+      v = part == 0 ? INFINITY : 0.f;
+    }
+    stat[idx] = v;
+    return;
+  }
   const int cpr = DQK / 8;
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = (int64_t)a.B * a.T * G * cpr;
-  if (c >= total) return;
+  const int64_t c = (int64_t)((int)blockIdx.x - stat_blocks) * 256 + threadIdx.x;
+  if (c >= (int64_t)a.B * a.T * G * cpr) return;
   const int d = (int)(c % cpr) * 8;
   const int64_t ng = c / cpr;
   const int g = (int)(ng % G);
@@ -453,7 +454,7 @@ __global__ void kcat_kernel(AttnDev a, int G, int DQK, bf16_t* __restrict__ out)
   const bf16_t* src = d < a.dnope
                           ? a.Ka + n * a.ka_tok + (int64_t)(i / a.ka_div) * a.ka_head + d
                           : a.Kb + n * a.kb_tok + (int64_t)(i / a.kb_div) * a.kb_head + (d - a.dnope);
-  *(u32x4*)(out + ng * DQK + d) = *(const u32x4*)src;
+  *(u32x4*)(kcat + ng * DQK + d) = *(const u32x4*)src;
 }
 
 // Sum of the head splits in order, from part[n][G][S][W]: column c < n_lo of group g in bf16
@@ -549,13 +550,15 @@ hipError_t bwd_chunk(const AttnBwd& wb, int b0, int nb, hipStream_t s) {
             (int64_t)at.H * at.B * w.tpad * 4 * 2 < (1ll << 31);
   const double pairs = attn_causal_pairs(at);
   const double N = (double)at.B * at.T;
-  // statistics per (head, sequence) in query order, then dV and dS^T: algorithmic
-  // dV = P^T dO, dP = dO V^T
+  // statistics per (head, sequence) in query order and the keys of each group gathered into one
+  // operand, then dV and dS^T: algorithmic dV = P^T dO, dP = dO V^T
   prof_begin(KC_ELEM, s);
   const int64_t nst = 2LL * at.H * at.B * w.tpad;
-  attn_stats_t_kernel<<<(unsigned)((nst + 255) / 256), 256, 0, s>>>(at.lse, delta, at.B, at.T, at.H,
-                                                                    w.tpad, wb.statT);
-  prof_end(KC_ELEM, s, 0.0, nst * 4.0 * 2.0, KLABEL("attn_stats_t_kernel"));
+  const int64_t chunks = (int64_t)at.B * at.T * w.G * (DQK / 8);
+  const int stat_blocks = (int)((nst + 255) / 256);
+  attn_bwd_prep_kernel<<<stat_blocks + (unsigned)((chunks + 255) / 256), 256, 0, s>>>(
+      w.f, at.lse, delta, w.tpad, wb.statT, stat_blocks, w.G, DQK, (bf16_t*)wb.kcat);
+  prof_end(KC_ELEM, s, 0.0, nst * 4.0 * 2.0 + N * w.G * DQK * 2.0 * 2.0, KLABEL("attn_bwd_prep_kernel"));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   prof_begin(KC_ATTN_DKDV, s);
@@ -606,14 +609,8 @@ hipError_t bwd_chunk(const AttnBwd& wb, int b0, int nb, hipStream_t s) {
     if (e != hipSuccess) return e;
     if (sk > 1 && (e = split_sum(sk, DQK, at.dnope, dKa, wb.dka_tok, dkb)) != hipSuccess) return e;
   }
-  // keys of each group gathered into one operand, then dQ = scale dS K per (sequence,
-  // head): algorithmic dS read once, K read once per head, dQ written once
-  prof_begin(KC_ELEM, s);
-  const int64_t chunks = (int64_t)at.B * at.T * w.G * (DQK / 8);
-  kcat_kernel<<<(unsigned)((chunks + 255) / 256), 256, 0, s>>>(w.f, w.G, DQK, (bf16_t*)wb.kcat);
-  prof_end(KC_ELEM, s, 0.0, N * w.G * DQK * 2.0 * 2.0, KLABEL("kcat_kernel"));
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  // dQ = scale dS K per (sequence, head): algorithmic dS read once, K read once per head, dQ
+  // written once
   Gemm g;
   g.M = (int)w.ds_ld; g.N = DQK; g.K = at.T;
   g.A = wb.dsT; g.lda = w.ds_ld; g.a_kmajor = false;
@@ -649,10 +646,7 @@ hipError_t bwd_launch(const AttnBwd& wb, hipStream_t s) {
     e = bwd_chunk<DQK, DV>(wb, b0, std::min(chunk, at.B - b0), s);
     if (e != hipSuccess) return e;
   }
-  // rotary block of dQ back to the pre-rotation basis: R^T
-  const int np = (DQK - at.dnope) / 2;
-  return rope_apply(wb.dq, DT_BF16, at.B * at.T, at.T, at.H, (int64_t)at.H * DQK, DQK, at.dnope,
-                    np, wb.rdiv, wb.cos_t, wb.sin_t, s, true);
+  return hipSuccess;
 }
 
 }  // namespace

@@ -12,17 +12,21 @@ namespace mla {
 // ---------------------------------------------------------------------------------------
 // RoPE (Sec. 3.1): R_t rotates rotate-half pair p of a head by t * inv_freq[p].
 // ---------------------------------------------------------------------------------------
-__global__ void rope_table_kernel(const float* __restrict__ inv_freq, int G, int T, int np,
-                                  float* __restrict__ cos_t, float* __restrict__ sin_t) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t total = (int64_t)G * T * np;
-  if (idx >= total) return;
+// (cos, sin) of table entry idx of one [G][T][np] table
+__device__ __forceinline__ void rope_entry(const float* __restrict__ inv_freq, int T, int np, int64_t idx,
+                                           float* __restrict__ cos_t, float* __restrict__ sin_t) {
   int p = (int)(idx % np);
   int t = (int)((idx / np) % T);
   int g = (int)(idx / ((int64_t)np * T));
   double ang = (double)t * (double)inv_freq[g * np + p];
   cos_t[idx] = (float)cos(ang);
   sin_t[idx] = (float)sin(ang);
+}
+
+__global__ void rope_table_kernel(const float* __restrict__ inv_freq, int G, int T, int np,
+                                  float* __restrict__ cos_t, float* __restrict__ sin_t) {
+  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx < (int64_t)G * T * np) rope_entry(inv_freq, T, np, idx, cos_t, sin_t);
 }
 
 hipError_t rope_tables(const float* inv_freq, int G, int T, int npairs, float* cos_t,
@@ -76,13 +80,11 @@ __global__ void rope_apply_kernel(T* __restrict__ x, int N, int Tseq, int nheads
 }
 
 // the same for bf16 with 8 consecutive pairs per thread (16-byte loads and stores)
-__global__ void rope_apply8_kernel(bf16_t* __restrict__ x, int N, int Tseq, int nheads, int64_t tok,
-                                   int64_t head, int off, int np, int div,
-                                   const float* __restrict__ cos_t,
-                                   const float* __restrict__ sin_t, float sgn) {
+__device__ __forceinline__ void rope_item8(bf16_t* __restrict__ x, int64_t idx, int Tseq, int nheads,
+                                           int64_t tok, int64_t head, int off, int np, int div,
+                                           const float* __restrict__ cos_t,
+                                           const float* __restrict__ sin_t, float sgn) {
   const int nq = np / 8;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)N * nheads * nq) return;
   const int p = (int)(idx % nq) * 8;
   const int h = (int)((idx / nq) % nheads);
   const int64_t n = idx / ((int64_t)nq * nheads);
@@ -109,6 +111,70 @@ __global__ void rope_apply8_kernel(bf16_t* __restrict__ x, int N, int Tseq, int 
   *(u32x4*)(base + p + np) = ob;
 }
 
+__global__ void rope_apply8_kernel(bf16_t* __restrict__ x, int N, int Tseq, int nheads, int64_t tok,
+                                   int64_t head, int off, int np, int div,
+                                   const float* __restrict__ cos_t,
+                                   const float* __restrict__ sin_t, float sgn) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx < (int64_t)N * nheads * (np / 8))
+    rope_item8(x, idx, Tseq, nheads, tok, head, off, np, div, cos_t, sin_t, sgn);
+}
+
+// several rotations in one launch: block ids run over the first one's blocks, then the next's
+struct RopeGroup {
+  RopeArgs r[ROPE_MAX];
+  int end[ROPE_MAX];
+  int n;
+};
+__global__ void rope_group8_kernel(RopeGroup g, int N, int Tseq) {
+  int i = 0, beg = 0;
+#pragma unroll
+  for (int j = 0; j < ROPE_MAX - 1; ++j)
+    if (j + 1 < g.n && (int)blockIdx.x >= g.end[j]) {
+      i = j + 1;
+      beg = g.end[j];
+    }
+  const RopeArgs& a = g.r[i];
+  const int64_t idx = (int64_t)((int)blockIdx.x - beg) * blockDim.x + threadIdx.x;
+  if (idx < (int64_t)N * a.nheads * (a.npairs / 8))
+    rope_item8((bf16_t*)a.x, idx, Tseq, a.nheads, a.tok, a.head, a.off, a.npairs, a.div, a.cos_t, a.sin_t, 1.f);
+}
+
+static bool rope_v8(const void* x, DType t, int64_t tok, int64_t head, int off, int npairs) {
+  return t == DT_BF16 && npairs % 8 == 0 && tok % 8 == 0 && head % 8 == 0 && off % 8 == 0 &&
+         (uintptr_t)x % 16 == 0;
+}
+
+hipError_t rope_group(const RopeArgs* r, int n, DType t, int N, int T, hipStream_t s) {
+  RopeGroup g;
+  g.n = 0;
+  int blocks = 0;
+  bool ok = n <= ROPE_MAX;
+  for (int i = 0; i < n && ok; ++i) {
+    const int64_t items = (int64_t)N * r[i].nheads * (r[i].npairs / 8);
+    ok = rope_v8(r[i].x, t, r[i].tok, r[i].head, r[i].off, r[i].npairs) && items / 256 + blocks < (1 << 30);
+    if (!ok || items == 0) continue;
+    blocks += (int)((items + 255) / 256);
+    g.r[g.n] = r[i];
+    g.end[g.n++] = blocks;
+  }
+  if (!ok) {
+    for (int i = 0; i < n; ++i) {
+      const hipError_t e = rope_apply(r[i].x, t, N, T, r[i].nheads, r[i].tok, r[i].head, r[i].off,
+                                      r[i].npairs, r[i].div, r[i].cos_t, r[i].sin_t, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  if (blocks == 0) return hipSuccess;
+  double bytes = 0.0;
+  for (int i = 0; i < n; ++i) bytes += (double)N * r[i].nheads * r[i].npairs * 8.0;
+  prof_begin(KC_ELEM, s);
+  rope_group8_kernel<<<blocks, 256, 0, s>>>(g, N, T);
+  prof_end(KC_ELEM, s, 0.0, bytes, KLABEL("rope_group8_kernel"));
+  return hipGetLastError();
+}
+
 hipError_t rope_apply(void* x, DType t, int N, int T, int nheads, int64_t tok, int64_t head,
                       int off, int npairs, int div, const float* cos_t, const float* sin_t,
                       hipStream_t s, bool inverse) {
@@ -117,8 +183,7 @@ hipError_t rope_apply(void* x, DType t, int N, int T, int nheads, int64_t tok, i
   if (total == 0) return hipSuccess;
   unsigned grid = (unsigned)((total + 255) / 256);
   prof_begin(KC_ELEM, s);
-  const bool v8 = t == DT_BF16 && npairs % 8 == 0 && tok % 8 == 0 && head % 8 == 0 &&
-                  off % 8 == 0 && (uintptr_t)x % 16 == 0;
+  const bool v8 = rope_v8(x, t, tok, head, off, npairs);
   if (v8) {
     const int64_t total8 = (int64_t)N * nheads * (npairs / 8);
     rope_apply8_kernel<<<(unsigned)((total8 + 255) / 256), 256, 0, s>>>(
@@ -186,14 +251,11 @@ hipError_t dq_finish(const float* dq_acc, void* dq, DType t, int N, int T, int H
 }
 
 template <typename T>
-__global__ void dkpe_finish_kernel(const float* __restrict__ part, T* __restrict__ out,
-                                   int64_t out_tok, int N, int Tseq, int Gr, int per, int dr,
-                                   const float* __restrict__ cos_t,
-                                   const float* __restrict__ sin_t) {
+__device__ __forceinline__ void dkpe_item(int64_t idx, const float* __restrict__ part, T* __restrict__ out,
+                                          int64_t out_tok, int N, int Tseq, int Gr, int per, int dr,
+                                          const float* __restrict__ cos_t,
+                                          const float* __restrict__ sin_t) {
   int np = dr / 2;
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t total = (int64_t)N * Gr * np;
-  if (idx >= total) return;
   int p = (int)(idx % np);
   int r = (int)((idx / np) % Gr);
   int64_t n = idx / ((int64_t)np * Gr);
@@ -209,6 +271,16 @@ __global__ void dkpe_finish_kernel(const float* __restrict__ part, T* __restrict
   T* o = out + n * out_tok + (int64_t)r * dr;
   st(o + p, x1 * c + x2 * sn);
   st(o + p + np, -x1 * sn + x2 * c);
+}
+
+template <typename T>
+__global__ void dkpe_finish_kernel(const float* __restrict__ part, T* __restrict__ out,
+                                   int64_t out_tok, int N, int Tseq, int Gr, int per, int dr,
+                                   const float* __restrict__ cos_t,
+                                   const float* __restrict__ sin_t) {
+  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx < (int64_t)N * Gr * (dr / 2))
+    dkpe_item<T>(idx, part, out, out_tok, N, Tseq, Gr, per, dr, cos_t, sin_t);
 }
 
 hipError_t dkpe_finish(const float* part, void* out, DType t, int64_t out_tok, int N, int T,
@@ -248,9 +320,8 @@ struct LossScratch {
 
 size_t loss_scratch_bytes() { return sizeof(LossScratch); }
 
-__global__ void mask_count_kernel(const uint8_t* __restrict__ mask, int64_t N, int D,
-                                  LossScratch* __restrict__ ws) {
-  __shared__ double red[16];
+__device__ __forceinline__ void mask_count(const uint8_t* __restrict__ mask, int64_t N, int D,
+                                           LossScratch* __restrict__ ws, double* red) {
   double c = 0.0;
   if (mask) {
     // 16 mask bytes per thread and step where the mask is 16-byte aligned, the tail byte-wise
@@ -278,6 +349,41 @@ __global__ void mask_count_kernel(const uint8_t* __restrict__ mask, int64_t N, i
     ws->count = t;
     ws->scale = t > 0.0 ? (float)(2.0 / ((double)D * t)) : 0.f;
   }
+}
+
+__global__ void mask_count_kernel(const uint8_t* __restrict__ mask, int64_t N, int D,
+                                  LossScratch* __restrict__ ws) {
+  __shared__ double red[16];
+  mask_count(mask, N, D, ws, red);
+}
+
+// What the single-call step needs before its products: the rotation tables of both blocks and
+// the count of valid tokens (the last block), in one launch instead of three (a launch takes
+// about 4.6 us behind another one, whatever it does).
+__global__ __launch_bounds__(256) void step_prepare_kernel(RopeTable a, RopeTable b, int T, int blocks_a,
+                                                           int blocks_ab, const uint8_t* __restrict__ mask,
+                                                           int64_t N, int D, LossScratch* __restrict__ ws) {
+  __shared__ double red[16];
+  const int w = blockIdx.x;
+  if (w == blocks_ab) {
+    mask_count(mask, N, D, ws, red);
+    return;
+  }
+  const bool second = w >= blocks_a;
+  const RopeTable& t = second ? b : a;
+  const int64_t idx = (int64_t)(second ? w - blocks_a : w) * 256 + threadIdx.x;
+  if (idx < (int64_t)t.G * T * t.npairs) rope_entry(t.inv_freq, T, t.npairs, idx, t.cos_t, t.sin_t);
+}
+
+hipError_t step_prepare(const RopeTable& a, const RopeTable& b, int T, const uint8_t* mask, int64_t N,
+                        int D, void* scratch, hipStream_t s) {
+  auto blocks = [&](const RopeTable& t) { return (int)(((int64_t)t.G * T * t.npairs + 255) / 256); };
+  const int na = blocks(a), nb = blocks(b);
+  prof_begin(KC_ELEM, s);
+  step_prepare_kernel<<<na + nb + 1, 256, 0, s>>>(a, b, T, na, na + nb, mask, N, D, (LossScratch*)scratch);
+  prof_end(KC_ELEM, s, 0.0, (double)T * 8.0 * (a.G * a.npairs + b.G * b.npairs) + (mask ? (double)N : 0.0),
+           KLABEL("step_prepare_kernel"));
+  return hipGetLastError();
 }
 
 template <typename T>
@@ -433,20 +539,18 @@ hipError_t loss_from_parts(const double* part, int nparts, int D, float* loss,
 
 // Eq. 11 from the partials of sum dO . (o_s - o_t): with dO = 2 M Y / (D sum M), the
 // squared-error sum is sum M Y . (o_s - o_t) = dot D count / 2 and L = dot / 2
-// (tens of thousands of partials: thread t sums the contiguous run t * per .. in order,
-// with independent loads, then a fixed tree over the 1024 threads)
-__global__ __launch_bounds__(1024) void loss_dot_kernel(const double* __restrict__ part,
-                                                        int nparts, int D,
-                                                        LossScratch* __restrict__ ws,
-                                                        float* __restrict__ loss) {
-  __shared__ double red[1024];
-  const int per = (nparts + 1023) / 1024;
+// (thread t sums the contiguous run t * per .. in order, then a fixed tree over the threads)
+template <int THR>
+__device__ __forceinline__ void loss_dot(const double* __restrict__ part, int nparts, int D,
+                                         LossScratch* __restrict__ ws, float* __restrict__ loss,
+                                         double* red) {
+  const int per = (nparts + THR - 1) / THR;
   const int b0 = (int)threadIdx.x * per, b1 = min(nparts, b0 + per);
   double v = 0.0;
   for (int i = b0; i < b1; ++i) v += part[i];
   red[threadIdx.x] = v;
   __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
+  for (int w = THR / 2; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
@@ -458,11 +562,63 @@ __global__ __launch_bounds__(1024) void loss_dot_kernel(const double* __restrict
   loss[1] = NAN;
 }
 
-hipError_t loss_from_dot(const double* part, int64_t nparts, int D, float* loss, void* scratch,
-                         hipStream_t s) {
-  prof_begin(KC_LOSS, s);
-  loss_dot_kernel<<<1, 1024, 0, s>>>(part, (int)nparts, D, (LossScratch*)scratch, loss);
-  prof_end(KC_LOSS, s, 0.0, 8.0 * nparts, KLABEL("loss_dot_kernel"));
+// What follows the attention's backward, in one launch: R^T on the rotary block of dq, the
+// group sum of dk^PE with R^T (either may be absent) and, with dot, Eq. 11 from the partials of
+// the delta pass (the last block).
+struct BwdFinish {
+  RopeArgs dq;                 // npairs = 0: absent
+  const float* dkpe;           // null: absent
+  bf16_t* dkpe_out;
+  int64_t dkpe_tok;
+  int Gr, per, dr;
+  const float* cos_t;
+  const float* sin_t;
+  const double* dot;           // null: absent
+  int ndot, D;
+  LossScratch* ws;
+  float* loss;
+  int blocks_q, blocks_qk;
+};
+__global__ __launch_bounds__(256) void bwd_finish_kernel(BwdFinish f, int N, int Tseq) {
+  __shared__ double red[256];
+  const int w = blockIdx.x;
+  if (w < f.blocks_q) {
+    const RopeArgs& a = f.dq;
+    const int64_t idx = (int64_t)w * 256 + threadIdx.x;
+    if (idx < (int64_t)N * a.nheads * (a.npairs / 8))
+      rope_item8((bf16_t*)a.x, idx, Tseq, a.nheads, a.tok, a.head, a.off, a.npairs, a.div, a.cos_t, a.sin_t, -1.f);
+  } else if (w < f.blocks_qk) {
+    const int64_t idx = (int64_t)(w - f.blocks_q) * 256 + threadIdx.x;
+    if (idx < (int64_t)N * f.Gr * (f.dr / 2))
+      dkpe_item<bf16_t>(idx, f.dkpe, f.dkpe_out, f.dkpe_tok, N, Tseq, f.Gr, f.per, f.dr, f.cos_t, f.sin_t);
+  } else {
+    loss_dot<256>(f.dot, f.ndot, f.D, f.ws, f.loss, red);
+  }
+}
+
+hipError_t bwd_finish(const RopeArgs* dq, const float* dkpe, void* dkpe_out, int64_t dkpe_tok, int N, int T,
+                      int Gr, int per, int dr, const float* cos_t, const float* sin_t, const double* dot,
+                      int64_t ndot, int D, void* scratch, float* loss, hipStream_t s) {
+  if (dq && !rope_v8(dq->x, DT_BF16, dq->tok, dq->head, dq->off, dq->npairs)) {
+    const hipError_t e = rope_apply(dq->x, DT_BF16, N, T, dq->nheads, dq->tok, dq->head, dq->off, dq->npairs,
+                                    dq->div, dq->cos_t, dq->sin_t, s, true);
+    if (e != hipSuccess) return e;
+    dq = nullptr;
+  }
+  BwdFinish f;
+  f.dq = dq ? *dq : RopeArgs{nullptr, 0, 0, 0, 0, 0, 1, nullptr, nullptr};
+  f.dkpe = dkpe; f.dkpe_out = (bf16_t*)dkpe_out; f.dkpe_tok = dkpe_tok;
+  f.Gr = Gr; f.per = per; f.dr = dr; f.cos_t = cos_t; f.sin_t = sin_t;
+  f.dot = dot; f.ndot = (int)ndot; f.D = D; f.ws = (LossScratch*)scratch; f.loss = loss;
+  const int64_t nq = (int64_t)N * f.dq.nheads * (f.dq.npairs / 8), nk = dkpe ? (int64_t)N * Gr * (dr / 2) : 0;
+  f.blocks_q = (int)((nq + 255) / 256);
+  f.blocks_qk = f.blocks_q + (int)((nk + 255) / 256);
+  const int blocks = f.blocks_qk + (dot ? 1 : 0);
+  if (blocks == 0) return hipSuccess;
+  prof_begin(KC_ELEM, s);
+  bwd_finish_kernel<<<blocks, 256, 0, s>>>(f, N, T);
+  prof_end(KC_ELEM, s, 0.0, (double)nq * 64.0 + (dkpe ? (double)N * Gr * dr * (4.0 * per + 2.0) : 0.0) + 8.0 * ndot,
+           KLABEL("bwd_finish_kernel"));
   return hipGetLastError();
 }
 

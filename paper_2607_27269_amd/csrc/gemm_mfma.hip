@@ -1725,7 +1725,7 @@ hipError_t gemm_mfma_group(const Gemm* g, int n, float* scratch, size_t scratch_
                         : tile == 1 ? COST_128x64[layout]
                                     : TILE_COST[layout][T128];
     const int64_t slots = (int64_t)NUM_CU * c.per_cu;
-    for (int kc = kmax; kc >= 2; kc = std::min(kc - 1, kc * 3 / 4)) {
+    for (int kc = kmax; kc >= std::min(2, kmax); kc = std::min(kc - 1, kc * 3 / 4)) {
       double slices = 0.0, elems = 0.0;
       int64_t wgs = 0;
       int walk = 0, msp = 0;

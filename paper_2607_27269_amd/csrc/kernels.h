@@ -102,7 +102,8 @@ struct AttnBwd {
   float* delta;              // scratch [N, H]
   float* dq_acc;             // scratch [N, H, dqk] fp32 (vector-ALU path)
   void* dq;                  // out [N, H*dqk]: dQ with the rotary block [dnope, dqk) rotated
-  int rdiv;                  //   back by R^T using the tables of rope group i / rdiv
+  int rdiv;                  //   back by R^T using the tables of rope group i / rdiv (vector-ALU
+                             //   path; the matrix-core path leaves that to bwd_finish)
   const float* cos_t;        //   ([G_r][T][(dqk-dnope)/2] fp32)
   const float* sin_t;
   void* dKa; int64_t dka_tok;  // [N, ...]: group g's d_nope grads at dKa[n*dka_tok + g*dnope]
@@ -153,6 +154,28 @@ hipError_t rope_apply(void* x, DType t, int N, int T, int nheads, int64_t tok, i
                       int off, int npairs, int div, const float* cos_t, const float* sin_t,
                       hipStream_t s, bool inverse = false);
 
+// The rotation of rope_apply as arguments; rope_group runs up to ROPE_MAX of them (the same
+// dtype, tokens and positions) in one launch where all take the 16-byte kernel.
+struct RopeArgs {
+  void* x;
+  int nheads;
+  int64_t tok, head;
+  int off, npairs, div;
+  const float* cos_t;
+  const float* sin_t;
+};
+constexpr int ROPE_MAX = 3;
+hipError_t rope_group(const RopeArgs* r, int n, DType t, int N, int T, hipStream_t s);
+// Before the single-call step's products, one launch: both rotation tables and loss_prepare.
+struct RopeTable {
+  const float* inv_freq;
+  int G, npairs;
+  float* cos_t;
+  float* sin_t;
+};
+hipError_t step_prepare(const RopeTable& a, const RopeTable& b, int T, const uint8_t* mask, int64_t N,
+                        int D, void* scratch, hipStream_t s);
+
 // Backward finishing ----------------------------------------------------------------------
 // dq[n, i, :] = dq_acc with the rotary block [dnope, dqk) rotated back by R^T (tables of
 // rope group i / rdiv), written in storage dtype with row stride H*dqk.
@@ -160,6 +183,13 @@ hipError_t dq_finish(const float* dq_acc, void* dq, DType t, int N, int T, int H
                      int dnope, int rdiv, const float* cos_t, const float* sin_t, hipStream_t s);
 // dk^PE of rope group r = R^T sum of the partials of Ka groups r*per .. r*per+per-1,
 // written to out[n*out_tok + r*drope + e] in storage dtype.
+// bf16, one launch: R^T on dq (null: not), dkpe_finish (dkpe null: not) and, with dot, Eq. 11
+// from the ndot partials of sum dO . (o_s - o_t) left by the delta pass: with
+// dO = 2 M Y / (D sum M), L = sum(dO . (o_s - o_t)) / 2 (fixed order); loss[1] = NaN, the
+// squared-error sum kept for loss_rel_from_parts.
+hipError_t bwd_finish(const RopeArgs* dq, const float* dkpe, void* dkpe_out, int64_t dkpe_tok, int N, int T,
+                      int Gr, int per, int dr, const float* cos_t, const float* sin_t, const double* dot,
+                      int64_t ndot, int D, void* scratch, float* loss, hipStream_t s);
 hipError_t dkpe_finish(const float* part, void* out, DType t, int64_t out_tok, int N, int T,
                        int Gr, int per, int drope, const float* cos_t, const float* sin_t,
                        hipStream_t s);
@@ -247,12 +277,6 @@ hipError_t prefill_guard(const void* cache, int64_t rows, int rkv, int dr, void*
 // out = a - b elementwise over n elements of dtype t (fp32 arithmetic)
 hipError_t sub_elementwise(const void* a, const void* b, void* out, int64_t n, DType t,
                            hipStream_t s);
-
-// Eq. 11 from dO = 2 M Y / (D sum M) and o_s - o_t: L = sum(dO . (o_s - o_t)) / 2 (the
-// fixed-order sum of the nparts partials of the delta pass); loss[1] = NaN, the squared-error
-// sum kept for loss_rel_from_parts
-hipError_t loss_from_dot(const double* part, int64_t nparts, int D, float* loss, void* scratch,
-                         hipStream_t s);
 
 // Loss (Eq. 11) -------------------------------------------------------------------------
 // scratch: at least loss_scratch_bytes(); loss[0] = L, loss[1] = relative error.  With
