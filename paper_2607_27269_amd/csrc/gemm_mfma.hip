@@ -1086,9 +1086,19 @@ __global__ __launch_bounds__(64 * WM * WN) void attn_ds_gemm_kernel(GemmDev g) {
   [a0] "v"(cu[0]), [a1] "v"(cu[1]), [a2] "v"(cu[2]), [a3] "v"(cu[3]), [b0] "v"(cu[4]),      \
   [b1] "v"(cu[5]), [b2] "v"(cu[6]), [ra] "v"(ra), [rb] "v"(rb)
 
-template <int BN, typename TC, bool SHIFT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void gemm_nt4_persist_kernel(GemmDev g) {
+// Several products of one A (the same rows, K and row strides): column tiles run over the
+// outputs of the first product, then of the second, .. (g.N, g.B, g.C, g.ldc are not used)
+struct Nt4Group {
+  int n;
+  int end[GROUP_MAX];  // column tiles of products 0 .. i
+  int N[GROUP_MAX];
+  const bf16_t* B[GROUP_MAX];
+  void* C[GROUP_MAX];
+  int64_t ldc[GROUP_MAX];
+};
+
+template <int BN, typename TC, bool SHIFT, bool GROUP>
+__device__ __forceinline__ void gemm_nt4(const GemmDev& g, const Nt4Group& gr) {
   constexpr int BM = 256, BKK = 64, TM = 4, TN = BN / 64;  // 4 or 3 fragments of B
   constexpr int WTN = BN / 2;                              // columns per wavefront
   using LA = Loader<true, BM, 256, BKK>;  // operand tile layouts (swizzled rows)
@@ -1100,7 +1110,7 @@ void gemm_nt4_persist_kernel(GemmDev g) {
   static_assert(BN == 256 || BN == 192, "tile widths");
   static_assert(LA::Dma::PER == 8 && PB == TN * 2, "copies per lane per operand slice");
   __shared__ __attribute__((aligned(1024))) bf16_t lds[2 * STAGE + 2 * EPI];
-  const int ntm = (g.M + BM - 1) / BM, ntn = (g.N + BN - 1) / BN, ntiles = ntm * ntn;
+  const int ntm = (g.M + BM - 1) / BM, ntn = GROUP ? gr.end[gr.n - 1] : (g.N + BN - 1) / BN, ntiles = ntm * ntn;
   const int G = (int)gridDim.x;
   int w = blockIdx.x;
   if (w >= ntiles) return;
@@ -1109,14 +1119,27 @@ void gemm_nt4_persist_kernel(GemmDev g) {
   // the tile order of the one-tile launch: XCD-aware remap, 8 row panels per group
   // (a tile that the edge cuts starts at M - BM or N - BN instead and stores only the rows
   // and columns of its own)
-  auto tile_of = [&](int x, int& m0, int& n0, int& mlo, int& nlo) {
+  auto tile_of = [&](int x, int& m0, int& n0, int& mlo, int& nlo, int& pi) {
     const int pid = xcd_remap(x, ntiles);
     const int group = pid / (8 * ntn), first = group * 8, gsz = min(ntm - first, 8);
     mlo = __builtin_amdgcn_readfirstlane((first + (pid % (8 * ntn)) % gsz) * BM);
-    nlo = __builtin_amdgcn_readfirstlane(((pid % (8 * ntn)) / gsz) * BN);
+    int tn = __builtin_amdgcn_readfirstlane((pid % (8 * ntn)) / gsz);
+    pi = 0;
+    if constexpr (GROUP) {
+      int beg = 0;
+#pragma unroll
+      for (int j = 0; j < GROUP_MAX - 1; ++j)
+        if (j + 1 < gr.n && tn >= gr.end[j]) {
+          pi = j + 1;
+          beg = gr.end[j];
+        }
+      tn -= beg;
+    }
+    nlo = tn * BN;
     m0 = SHIFT ? min(mlo, g.M - BM) : mlo;
-    n0 = SHIFT ? min(nlo, g.N - BN) : nlo;
+    n0 = SHIFT ? min(nlo, (GROUP ? gr.N[pi] : g.N) - BN) : nlo;
   };
+  auto b_of = [&](int pi) { return GROUP ? gr.B[pi] : g.B; };
   typename LA::Dma da;
   typename LB::Dma db;
   da.init();
@@ -1144,18 +1167,18 @@ void gemm_nt4_persist_kernel(GemmDev g) {
                     16u * (uint32_t)((2 * kk + h) ^ LB::swz(l));
     }
   const int nk = g.ktotal / BKK;  // even
-  int m0, n0, mlo, nlo, nm0 = 0, nn0 = 0, nmlo = 0, nnlo = 0;
-  tile_of(w, m0, n0, mlo, nlo);
+  int m0, n0, mlo, nlo, pi, nm0 = 0, nn0 = 0, nmlo = 0, nnlo = 0, npi = 0;
+  tile_of(w, m0, n0, mlo, nlo, pi);
   const bf16_t* baseA = g.A + (int64_t)m0 * g.lda;
-  const bf16_t* baseB = g.B + (int64_t)n0 * g.ldb;
+  const bf16_t* baseB = b_of(pi) + (int64_t)n0 * g.ldb;
   int wnext = w + G;
   bool has_next = wnext < ntiles;
   const bf16_t* nbaseA = baseA;
   const bf16_t* nbaseB = baseB;
   if (has_next) {
-    tile_of(wnext, nm0, nn0, nmlo, nnlo);
+    tile_of(wnext, nm0, nn0, nmlo, nnlo, npi);
     nbaseA = g.A + (int64_t)nm0 * g.lda;
-    nbaseB = g.B + (int64_t)nn0 * g.ldb;
+    nbaseB = b_of(npi) + (int64_t)nn0 * g.ldb;
   }
   f32x16 acc[TM][TN];
   bf16x8 F[4][8];  // operand buffers of four k steps: A 0..3, B 4..7
@@ -1270,7 +1293,8 @@ void gemm_nt4_persist_kernel(GemmDev g) {
     // epilogue reads no C, so the compiler has no loads to wait for before each store (it
     // would otherwise wait for every memory operation in flight, the next tile's copies
     // included)
-    TC* C = (TC*)g.C;
+    TC* C = (TC*)(GROUP ? gr.C[pi] : g.C);
+    const int64_t ldc = GROUP ? gr.ldc[pi] : g.ldc;
     // (beta and the masked scale are compile-time in each copy: with no branch inside, the
     // four strip reads of a row group are issued together, then converted and stored)
     auto epilogue = [&](auto with_beta, auto with_scale) {
@@ -1310,12 +1334,14 @@ void gemm_nt4_persist_kernel(GemmDev g) {
               const f32x4 so = o * lsc;  // masked rows exactly 0 (also where o is not finite)
               o = f32x4{keep ? so[0] : 0.f, keep ? so[1] : 0.f, keep ? so[2] : 0.f, keep ? so[3] : 0.f};
             }
-            if (!SHIFT || (m >= mlo && n >= nlo)) store4<TC>(C + (int64_t)m * g.ldc + n, o, g.alpha, WB ? g.beta : 0.f);
+            if (!SHIFT || (m >= mlo && n >= nlo)) store4<TC>(C + (int64_t)m * ldc + n, o, g.alpha, WB ? g.beta : 0.f);
           }
         }
       }
     };
-    if (g.lscale) {  // the masked dO product (beta = 0)
+    if constexpr (GROUP) {
+      epilogue(std::false_type{}, std::false_type{});
+    } else if (g.lscale) {  // the masked dO product (beta = 0)
       if (g.beta != 0.f) epilogue(std::true_type{}, std::true_type{});
       else epilogue(std::false_type{}, std::true_type{});
     } else {
@@ -1328,16 +1354,28 @@ void gemm_nt4_persist_kernel(GemmDev g) {
     n0 = nn0;
     mlo = nmlo;
     nlo = nnlo;
+    pi = npi;
     baseA = nbaseA;
     baseB = nbaseB;
     wnext = w + G;
     has_next = wnext < ntiles;
     if (has_next) {
-      tile_of(wnext, nm0, nn0, nmlo, nnlo);
+      tile_of(wnext, nm0, nn0, nmlo, nnlo, npi);
       nbaseA = g.A + (int64_t)nm0 * g.lda;
-      nbaseB = g.B + (int64_t)nn0 * g.ldb;
+      nbaseB = b_of(npi) + (int64_t)nn0 * g.ldb;
     }
   }
+}
+
+template <int BN, typename TC, bool SHIFT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void gemm_nt4_persist_kernel(GemmDev g) {
+  gemm_nt4<BN, TC, SHIFT, false>(g, Nt4Group{});
+}
+template <int BN, typename TC, bool SHIFT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void gemm_nt4_group_kernel(GemmDev g, Nt4Group gr) {
+  gemm_nt4<BN, TC, SHIFT, true>(g, gr);
 }
 
 // C = alpha * sum_s part[s] + beta * C, summed in split order (split s of the M x N block at
@@ -1752,6 +1790,61 @@ hipError_t gemm_mfma_group(const Gemm* g, int n, float* scratch, size_t scratch_
         best_tile = tile;
       }
     }
+  }
+  // Large products of one A on the four-wavefront kernel: one grid of tiles instead of a partly
+  // filled last round of each. Measured against the launches it replaces: Q/K/V of 8192 tokens
+  // of the 8B layer 339 us, apart 232 + 85 + 85; the five products of h and the two of c^KV of
+  // 6002 tokens of the 4096-wide layer with 32 full heads: the whole step 3050 us, before 3125.
+  // The rule is the fitted time: where each product fills its rounds by itself, or is too small
+  // for 256-row tiles, the launches apart or the smaller tiles come out cheaper.
+  int best_bn = 0;
+  bool same_a = layout == 0 && g[0].c_t == DT_BF16;
+  for (int i = 0; i < n; ++i)
+    same_a = same_a && g[i].A == g[0].A && g[i].lda == g[0].lda && g[i].M == g[0].M && g[i].K == g[0].K &&
+             g[i].ldb == g[0].ldb && g[i].alpha == g[0].alpha && g[i].beta == 0.f && !g[i].C2;
+  for (int bn = 256; same_a && bn >= 192; bn -= 64) {
+    const TileCost& c = TILE_COST[0][bn == 256 ? TNT256 : TNT192];
+    bool ok = true;
+    int64_t tn = 0;
+    for (int i = 0; i < n; ++i) {
+      ok = ok && nt4_ok(g[i], bn);
+      tn += (g[i].N + bn - 1) / bn;
+    }
+    const int64_t tiles = tn * ((g[0].M + 255) / 256), full = tiles / NUM_CU, rem = tiles % NUM_CU;
+    const int ks = (g[0].K + BK - 1) / BK;
+    double t = c.fixed + full * (c.tile + ks * c.bw);
+    if (rem) t += c.tile + ks * std::max<double>(c.lat, c.bw * std::min(1.0, rem / 256.0 + 0.25));
+    if (ok && t < best_t) {
+      best_t = t;
+      best_bn = bn;
+    }
+  }
+  if (best_bn) {
+    Nt4Group gr;
+    gr.n = n;
+    int tn = 0;
+    bool whole = g[0].M % 256 == 0;
+    for (int i = 0; i < n; ++i) {
+      tn += (g[i].N + best_bn - 1) / best_bn;
+      whole = whole && g[i].N % best_bn == 0;
+      gr.end[i] = tn;
+      gr.N[i] = g[i].N;
+      gr.B[i] = (const bf16_t*)g[i].B;
+      gr.C[i] = g[i].C;
+      gr.ldc[i] = g[i].ldc;
+    }
+    const GemmDev d = dev_of(g[0]);
+    const int grid = std::min(tn * ((g[0].M + 255) / 256), NUM_CU);
+    prof_begin(kclass, s);
+    if (best_bn == 256) {
+      if (whole) gemm_nt4_group_kernel<256, bf16_t, false><<<grid, 256, 0, s>>>(d, gr);
+      else gemm_nt4_group_kernel<256, bf16_t, true><<<grid, 256, 0, s>>>(d, gr);
+    } else {
+      if (whole) gemm_nt4_group_kernel<192, bf16_t, false><<<grid, 256, 0, s>>>(d, gr);
+      else gemm_nt4_group_kernel<192, bf16_t, true><<<grid, 256, 0, s>>>(d, gr);
+    }
+    prof_end(kclass, s, flops, bytes, KLABEL("gemm_nt4_group_kernel"));
+    return hipGetLastError();
   }
   if (best_kc == 0) return hipErrorNotSupported;
   const int bm = best_tile == 0 ? 64 : 128, bn = best_tile == 2 ? 128 : 64;
