@@ -1302,13 +1302,24 @@ __device__ __forceinline__ void gemm_nt4(const GemmDev& g, const Nt4Group& gr) {
       constexpr bool LS = decltype(with_scale)::value;
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        // the row mask of this 32-row block through one scalar load (the launcher checks its
-        // 4-byte alignment): a vector load here would wait, in order, for the next tile's
-        // copies already in flight
+        // the row mask of this 32-row block through scalar loads of whole dwords (the launcher
+        // checks the mask's 4-byte alignment): a vector load here would wait, in order, for the
+        // next tile's copies already in flight. The last row tile, moved back, starts at any
+        // byte: the block's nine dwords are shifted down to it (each holds a byte of the block).
+        // (dO of 6002 tokens, 4096 x 4096: 189 us; on 256-wide tiles of the kernel that lets
+        // the compiler place the copies, 250 us)
         u32x8 mk = {1u, 1u, 1u, 1u, 1u, 1u, 1u, 1u};
         if (LS && g.lmask) {  // uniform
-          const uint64_t pa = uniform_ptr(g.lmask + m0 + wrow0 + i * 32);
+          const int r0 = m0 + wrow0 + i * 32, sh = SHIFT ? r0 & 3 : 0;
+          const uint64_t pa = uniform_ptr(g.lmask + r0 - sh);
           asm volatile("s_load_dwordx8 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(mk) : "s"(pa) : "memory");
+          if (SHIFT && __builtin_amdgcn_readfirstlane(sh) != 0) {
+            uint32_t top;
+            asm volatile("s_load_dword %0, %1, 0x20\n\ts_waitcnt lgkmcnt(0)" : "=s"(top) : "s"(pa) : "memory");
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+              mk[q] = (uint32_t)(((uint64_t)(q < 7 ? mk[q + 1] : top) << 32 | mk[q]) >> (8 * sh));
+          }
         }
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
@@ -1905,9 +1916,8 @@ hipError_t gemm_mfma_masked_scale(const Gemm& g, const float* scale, const uint8
     return hipErrorInvalidValue;
   GemmDev d = dev_of(g);
   d.lscale = scale; d.lmask = mask; d.lpart = nullptr; d.lref = nullptr; d.ldref = 0;
-  // (the four-wavefront kernel reads the row mask with 32-byte scalar loads: every row tile,
-  // the moved-back last one included, starts at a 4-byte aligned mask byte)
-  const bool nt4_mask = (uintptr_t)mask % 4 == 0 && g.M % 4 == 0;
+  // (the four-wavefront kernel reads the row mask with scalar loads of aligned dwords)
+  const bool nt4_mask = (uintptr_t)mask % 4 == 0;
   const Plan p = plan_of(g, 0, nt4_mask ? ALL_KINDS : ALL_KINDS & ~(1u << TNT256 | 1u << TNT192));
   d.kchunk = p.kchunk;
   d.part = nullptr;

@@ -28,7 +28,8 @@ def _tol(wl, ref):
 
 
 @pytest.mark.parametrize("idx,B,T", [(4, 1, 33), (1, 1, 63), (1, 2, 65), (1, 1, 129), (1, 3, 85),
-                                     (1, 1, 257), (2, 1, 191), (2, 1, 321), (4, 1, 96), (2, 4, 1021)])
+                                     (1, 1, 257), (2, 1, 191), (2, 1, 321), (4, 1, 96), (2, 4, 1021),
+                                     (2, 7, 883)])
 def test_step_sizes(idx, B, T):
     from paper_2607_27269_amd.step import DeviceStep
     print(f"[sizes] cfg{idx} B={B} T={T}", flush=True)
