@@ -489,8 +489,8 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict_
 // split (a divisor of hpg, at least two rounds of workgroups) and the fp32 partials summed in
 // order; from 512 workgroups on the walk is left whole (no partials).  Decided on the whole
 // batch, not on a chunk, so that the results do not depend on the workspace.  Measured (dV and
-// dK kernels with their sums, before -> after): 3 x 777 tokens of the 14-head layer
-// 381 -> 81 us, its 8 x 2048 851 -> 411 us, 2 x 333 of the 32-head layer 187 -> 53 us.
+// dK kernels with their sums, unsplit -> now): 3 x 777 tokens of the 14-head layer
+// 381 -> 75 us, its 8 x 2048 851 -> 380 us, 2 x 333 of the 32-head layer 187 -> 53 us.
 constexpr int SPLIT_WGS = 512;
 static int head_splits(int64_t wgs, int hpg, size_t bytes_per_split, size_t room) {
   int best = 1;
@@ -607,7 +607,7 @@ hipError_t bwd_chunk(const AttnBwd& wb, int b0, int nb, hipStream_t s) {
     e = gemm_mfma_causal(g, bt, s);
     prof_end(KC_ATTN_DK, s, 2.0 * pairs * DQK,
              pairs * 2.0 + N * at.H * DQK * 2.0 + N * w.G * (at.dnope * 2.0 + dr * 4.0),
-             KLABEL("attn_ds_gemm_persist_kernel<256,%d,dK,fp32>", DQK));
+             KLABEL("attn_ds_gemm_persist_kernel<%d,%d,dK,fp32>", DQK > 64 && DQK <= 96 ? 128 : 256, DQK));
     if (e != hipSuccess) return e;
     if (sk > 1 && (e = split_sum(sk, DQK, at.dnope, dKa, wb.dka_tok, dkb)) != hipSuccess) return e;
   }
@@ -628,7 +628,7 @@ hipError_t bwd_chunk(const AttnBwd& wb, int b0, int nb, hipStream_t s) {
   prof_begin(KC_ATTN_DQ, s);
   e = gemm_mfma_causal(g, bt, s);
   prof_end(KC_ATTN_DQ, s, 2.0 * pairs * DQK, pairs * 2.0 + N * at.H * DQK * 2.0 * 2.0,
-           KLABEL("attn_ds_gemm_kernel<256,%d,dQ,bf16>", DQK));
+           KLABEL("attn_ds_gemm_kernel<%d,%d,dQ,bf16>", DQK > 64 && DQK <= 96 ? 128 : 256, DQK));
   return e;
 }
 

@@ -20,12 +20,17 @@
 // The operand reads of a wavefront hit distinct banks: k-major rows are XOR-swizzled in
 // 16-byte chunks, m-major row strides are padded.  Large problems use 256 x 256 tiles on
 // 8 wavefronts (128 x 64 each), which halves the LDS bytes per MFMA compared with
-// 128 x 128 tiles on 4 wavefronts (64 x 64 each), used for small problems.  Workgroup
+// 128 x 128 tiles on 4 wavefronts (64 x 64 each), used for middling problems.  Workgroup
 // ids are remapped so that neighbouring tiles (sharing A row panels or B column panels)
 // run on one XCD and hit its L2.  Weight gradients reduce over all tokens (K up to 1e5)
 // and have few output tiles: they are split along K into fp32 partials that a second
-// kernel sums in a fixed order (deterministic).  NT products of whole tiles run on a
-// four-wavefront kernel whose k steps are scheduled by hand (below, gemm_nt4_persist_kernel).
+// kernel sums in a fixed order (deterministic).  Products too small to fill the chip take
+// 64 x 64 tiles with four slices in flight, and split along K in any layout.  Large NT
+// products run on a four-wavefront kernel whose k steps are scheduled by hand (below,
+// gemm_nt4).  A tile that the matrix edge would cut is moved back to end at the edge, so
+// that its copies stay whole, and stores only its own rows and columns.  Several products
+// of one layout can share a launch (gemm_mfma_group).  Which tiles, split and grouping a
+// product gets is the cheapest by a fitted time model (plan_of).
 #include <atomic>
 #include <type_traits>
 
