@@ -9,9 +9,8 @@
 // MFMA column block, followed by a per-group projection.
 //
 // Kernels (three launches: with short caches the launches are most of the time):
-// * absorb_kernel: the absorbed queries [B][HP][DK] bf16 (heads padded to HP = 32k; padding
-//   rows are left as they are: every head is a column of its own from here on, and a padding
-//   head's partials are not stored), the latent part as one matrix-core product per KV group.
+// * absorb_kernel: the absorbed queries [B][HP][DK] bf16 (heads padded to HP = 32k; the padding
+//   rows are neither written nor read), the latent part as one matrix-core product per KV group.
 // * decode_attn_kernel: split-K over the cache (flash-decoding).  A workgroup (4 waves)
 //   owns one (sequence, key chunk, block of 32 heads).  Key tiles of 32 rows are copied
 //   straight into LDS in a ring of three stages (two tiles in flight).  The
@@ -191,10 +190,11 @@ __global__ __launch_bounds__(64 * DEC_WAVES) void decode_attn_kernel(DecodeDev a
   if (ntile > 0) issue(0);
   if (ntile > 1) issue(1);
   // this lane's head as B-operand fragments for the wave's K steps (head h0 + col,
-  // k = 16 kk + 8 half + 0..7)
+  // k = 16 kk + 8 half + 0..7).  A column without a head repeats the last head: the ballot
+  // below takes all columns together, and what scratch held before must not reach it.
   bf16x8 qf[QMAX];
   {
-    const bf16_t* qsrc = a.qabs + ((int64_t)b * a.HP + h0 + col) * DK + 8 * half;
+    const bf16_t* qsrc = a.qabs + ((int64_t)b * a.HP + min(h0 + col, a.H - 1)) * DK + 8 * half;
 #pragma unroll
     for (int j = 0; j < QMAX; ++j)
       qf[j] = kk0 + j < kk1 ? *(const bf16x8*)(qsrc + 16 * (kk0 + j)) : bf16x8{};
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(64 * DEC_WAVES) void decode_attn_kernel(DecodeDev a
   // partial state of this split: lane (head col, half) holds rows
   // wave WV + 32 c + 8 (e / 4) + 4 half + e % 4 of the unnormalised latent output
   const float l = pair_sum32(l_run);
-  if (h0 + col >= a.H) return;  // a padding head
+  if (h0 + col >= a.H) return;  // a column without a head
   const int64_t hrow = pbase + col;
   if (wave == 0 && half == 0) {
     a.part_ml[2 * hrow] = m_run;

@@ -23,13 +23,16 @@ def _inputs(cfg, B, T, lengths, seed=3):
                 lens=torch.tensor(lengths, dtype=torch.int32, device="cuda"))
 
 
-def _run(cfg, c, x, T, shift=0):
-    """shift: elements by which W_UK and o are moved off their 16-byte alignment."""
+def _run(cfg, c, x, T, shift=0, ws=None):
+    """shift: elements by which W_UK and o are moved off their 16-byte alignment; ws: the
+    workspace (bytes), as its contents are."""
     import torch
     from paper_2607_27269_amd import _lib as L
     wsb = L.mla_recon_decode_workspace_size(c, T)
     assert wsb > 0, L.last_error()
-    ws = torch.full((wsb,), 255, dtype=torch.uint8, device="cuda")  # NaN patterns
+    if ws is None:
+        ws = torch.full((wsb,), 255, dtype=torch.uint8, device="cuda")  # NaN patterns
+    assert ws.numel() >= wsb
     n = cfg.batch * cfg.n_heads * cfg.head_dim
     ob = torch.full((n + 8,), float("nan"), dtype=torch.bfloat16, device="cuda")
     o = ob[shift:shift + n]
@@ -88,3 +91,45 @@ def test_decode_splits(idx, T, lengths, kw):
             assert e <= TOL, (b, n, e)
     # neither W_UK nor o needs more alignment than its elements'
     assert torch.equal(o, _run(cfg, c, x, T, shift=3))
+
+
+@pytest.mark.parametrize("idx,T,lengths,kw", [
+    (1, 1500, [1500, 700, 1337], {}),    # 14 heads in a block of 32 columns
+    (1, 4500, [4500, 4499, 1], SMALL),   # 6 heads
+    (2, 900, [900, 450], dict(n_heads=40, hidden=2560)),  # 40 heads: the second block has 8
+])
+def test_decode_scratch_contents_do_not_change_results(idx, T, lengths, kw):
+    """A head count that is no multiple of 32 leaves columns without a head; whatever the
+    workspace held before (nothing, NaN patterns, finite values that grow from row to row, what
+    another call left), the outputs are the same bits."""
+    import torch
+    from paper_2607_27269_amd import _lib as L
+    B = len(lengths)
+    cfg = configs.get(idx).replace(batch=B, seq=T, **kw)
+    assert cfg.n_heads % 32
+    c = L.make_cfg(cfg)
+    x = _inputs(cfg, B, T, lengths)
+    n = L.mla_recon_decode_workspace_size(c, T)
+    assert n > 0, L.last_error()
+    g = torch.Generator(device="cuda").manual_seed(9)
+    ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    outs = {"zeros": _run(cfg, c, x, T, ws=ws)}
+    outs["NaN patterns"] = _run(cfg, c, x, T, ws=ws.fill_(255))
+    for scale in (1.0, 30.0, 1e4):
+        # logits of a column in the order of scale: its maximum moves from key tile to key tile
+        print(f"[scratch] cfg{idx} T={T} H={cfg.n_heads} scale {scale}", flush=True)
+        row = cfg.kv_rank + cfg.rope_dim
+        v = torch.randn(n // 2 // row + 1, row, device="cuda", generator=g)
+        v *= scale * torch.linspace(0.5, 2, v.shape[0], device="cuda")[:, None]
+        ws[:n // 2 * 2].view(torch.bfloat16).copy_(v.reshape(-1)[:n // 2])
+        outs[f"finite, {scale}"] = _run(cfg, c, x, T, ws=ws)
+    # what a call with more heads left: its absorbed queries lie where this call's columns
+    # without a head are
+    other = cfg.replace(n_heads=32 * ((cfg.n_heads + 31) // 32), n_kv_groups=2, s_kv_groups=2)
+    co = L.make_cfg(other)
+    xo = _inputs(other, B, T, [T] * B, seed=4)
+    big = torch.zeros(L.mla_recon_decode_workspace_size(co, T), dtype=torch.uint8, device="cuda")
+    _run(other, co, dict(xo, q=xo["q"] * 20), T, ws=big)
+    outs["another call's"] = _run(cfg, c, x, T, ws=big)
+    for k, o in outs.items():
+        assert torch.equal(o, outs["zeros"]), k

@@ -65,6 +65,19 @@ def test_decode_noalloc_matches_decode():
     assert not got[2].float().any()  # empty cache: zero output
 
 
+def test_decode_noalloc_matches_decode_padded_heads():
+    """14 heads: the columns without a head find what an earlier call with 32 heads left in the
+    scratch, and other bytes in the workspace."""
+    import torch
+    for seed, (B, T, lens) in ((21, (13, 1500, [1500 - 97 * b for b in range(13)])),
+                               (22, (3, 700, [700, 1, 699]))):
+        print(f"[noalloc] 32 heads, then 14: B={B} T={T}", flush=True)
+        _both(configs.get(3), 40, 2048, [2048] * 40, seed=seed)
+        ref, got = _both(configs.get(1), B, T, lens, seed=seed)
+        assert torch.isfinite(got.float()).all()
+        assert torch.equal(ref, got)
+
+
 def test_decode_noalloc_rejects_large_batch():
     import torch
     from paper_2607_27269_amd import _lib as L
