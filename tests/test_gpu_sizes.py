@@ -52,20 +52,30 @@ def test_step_sizes(idx, B, T):
         assert abs(out["loss"] - ref["loss"]) <= LOSS_TOL * ref["loss"]
 
 
-@pytest.mark.parametrize("B,T", [(1, 130), (2, 640)])
+@pytest.mark.parametrize("B,T", [(2, 640), (3, 130), (5, 333)])
 def test_step_workspace_does_not_change_results(B, T):
-    """The split of a product (and with it its rounding) does not depend on how much workspace
-    the caller gives: the smallest and the preferred workspace give the same bits."""
+    """Neither the split of a product nor that of a group's heads (and with them the rounding)
+    depends on how much workspace the caller gives: the backward in chunks of one sequence, in
+    even and uneven chunks and in one pass gives the same bits."""
     import torch
     from paper_2607_27269_amd import _lib as L
     from paper_2607_27269_amd.step import DeviceStep
     cfg = configs.shrink(configs.get(1), batch=B, seq=T)
     wl = synth.make_workload(cfg)
+    c = L.make_cfg(cfg)
+    lo, hi = L.mla_recon_workspace_size_min(c), L.mla_recon_workspace_size(c)
+    assert hi - lo > (B - 1) * 2 * T * T * cfg.n_heads  # a sequence's dS^T each
+    # chunks of 1 .. B sequences: one more for each equal part between the two sizes
+    sizes = [hi] + [lo + (hi - lo) * n // (B - 1) + 4096 for n in range(B - 1)]
     outs = []
-    for size in (L.mla_recon_workspace_size, L.mla_recon_workspace_size_min):
-        dev = DeviceStep(wl, ws_bytes=size(L.make_cfg(cfg)))
+    for ws_bytes in sizes:
+        print(f"[workspace] B={B} T={T} {ws_bytes}", flush=True)
+        dev = DeviceStep(wl, ws_bytes=ws_bytes)
+        dev.ws.fill_(255)  # NaN patterns
         dev.fused_step(with_dA=False)
         torch.cuda.synchronize()
         outs.append({"loss": dev.loss_buf[:1].clone(), **{k: v.clone() for k, v in dev.grads.items()}})
-    for k in outs[0]:
-        assert torch.equal(outs[0][k], outs[1][k]), k
+    for o in outs[1:]:
+        for k in outs[0]:
+            assert torch.equal(outs[0][k], o[k]), k
+    assert all(torch.isfinite(v).all() for v in outs[0].values())
