@@ -41,10 +41,6 @@ struct BwdDev {
   int off32;             // one sequence's Q / dO rows and the statistics span < 2^31 bytes
 };
 
-// dS^T tile rows a dQ GEMM row tile reads: queries from the start of the 256-query tile
-// that holds the key (the GEMM's row tile) to the end
-constexpr int DQ_TILE = 256;
-
 // element (key, query) of a dS^T plane: 32 x 32 tiles of [32 keys][32 queries], the tiles
 // of a key block in query order (ld / 32 per row of tiles), key blocks in order.  A
 // wavefront's 32 x 32 block is then 2 KB of whole lines, and the products' slices are
@@ -72,6 +68,10 @@ constexpr int DS_STORES = DV_BQ * 32 * 2 / (64 * 16);
 constexpr int DV_NST = 3;  // LDS stages: a step's copies are issued two steps ahead
 constexpr int DV_WAVES = 8;
 constexpr int DV_BKB = 32 * DV_WAVES;  // keys per workgroup
+// The steps below write every entry from a key block's first query on.  The products read a
+// plane in row tiles of at most CAUSAL_BM, whose K ranges start or end at the tile: with key
+// blocks of whole tiles no entry before a block's first query reaches a row that is stored.
+static_assert(DV_BKB % CAUSAL_BM == 0, "key blocks of whole row tiles of the dS^T products");
 
 template <int DQK, int DV>
 struct DvStage {
@@ -214,22 +214,6 @@ __global__ __launch_bounds__(64 * DV_WAVES, 8 / DV_WAVES) void attn_dv_mfma_kern
   const int kw0 = k0 + 32 * wave;
   const int my_key = kw0 + col;
   const int i0 = (g * w.nsplit + sp) * hpg;
-
-  // dS^T rows of this workgroup's keys: the queries in [tile start, k0) precede every key
-  // here, so their entries are zeros that no step below writes
-  const int zq0 = k0 / DQ_TILE * DQ_TILE;
-  if (zq0 < k0) {
-    const int nz = k0 - zq0;                       // multiple of the key block
-    const int cpr = nz / 8;                        // 16-byte chunks per key row
-    const int kr = min(DV_BKB, a.T - k0);
-    for (int h = 0; h < hpg; ++h) {
-      bf16_t* plane = w.dsT + ((int64_t)b * a.H + i0 + h) * w.ds_ld * w.ds_ld;
-      for (int c = threadIdx.x; c < kr * cpr; c += 64 * DV_WAVES) {
-        const int r = c / cpr, q = zq0 + (c % cpr) * 8;
-        *(u32x4*)(plane + ds_at(k0 + r, q, w.ds_ld)) = u32x4{0u, 0u, 0u, 0u};
-      }
-    }
-  }
 
   // this lane's key and value as B operand fragments (col = key, k = 16 kk + 8 half + 0..7)
   bf16x8 kf[NKK], vf[NVK];

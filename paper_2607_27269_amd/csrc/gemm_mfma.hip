@@ -1955,6 +1955,7 @@ hipError_t gemm_mfma_masked_sse(const Gemm& g, const float* scale, const uint8_t
 // result).  BN is the output width rounded up to the supported tile widths.
 template <int BM, int BN, int WM, int WN, bool AK, typename TC, bool SHIFT>
 static void launch_causal(const GemmDev& d, int nbatch, hipStream_t s) {
+  static_assert(CAUSAL_BM % BM == 0, "row tiles that the producer of A counts on");
   const int ntm = (d.M + BM - 1) / BM, ntn = (d.N + BN - 1) / BN;
   const int items = ntm * ntn * nbatch;
   if constexpr (!AK) {
@@ -2029,7 +2030,7 @@ hipError_t gemm_mfma_causal(const Gemm& g, const GemmBatch& bt, hipStream_t s) {
   d.sAk = bt.sAk; d.sBk = bt.sBk;
   d.split_n = bt.split_n; d.c_lo = (bf16_t*)bt.c_lo;
   d.ldc_lo = bt.ldc_lo; d.sC1_lo = bt.sC1_lo; d.sC2_lo = bt.sC2_lo;
-  if (g.M % 256 == 0)  // whole row tiles of either height
+  if (g.M % CAUSAL_BM == 0)  // whole row tiles of any height
     return g.a_kmajor ? dispatch_causal<true, float, false>(d, bt.nbatch, s)
                       : dispatch_causal<false, bf16_t, false>(d, bt.nbatch, s);
   return g.a_kmajor ? dispatch_causal<true, float, true>(d, bt.nbatch, s)

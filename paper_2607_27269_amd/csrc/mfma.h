@@ -27,13 +27,14 @@ hipError_t gemm_mfma_masked_scale(const Gemm& g, const float* scale, const uint8
                                   hipStream_t s, const char** kernel);
 // Batch entry z of a batched causal GEMM uses A + z sA, B + (z / zdiv) sB1 +
 // ((z % zdiv) / bdiv) sB2 and C + (z / zdiv) sC1 + (z % zdiv) sC2 (elements).  Row m of C
-// sums k < min(K, end of m's 256-row tile) (rev = 0; A M-contiguous, bf16 C) or
-// k >= start of m's tile (rev = 1; A K-contiguous, fp32 C), so A must hold zeros for the
+// sums k < min(K, end of m's row tile) (rev = 0; A M-contiguous, bf16 C) or
+// k >= start of m's row tile (rev = 1; A K-contiguous, fp32 C), so A must hold zeros for the
 // excluded side of the diagonal inside a tile; that K range is summed kgroups times, the
 // j-th on A + j sAk and B + j sBk.  B is N-contiguous; rows m >= mstore are not written.
 // A (a dS^T plane, key r x query c) is stored in 32 x 32 tiles: element (r, c) at
 // ((r / 32) (lda / 32) + c / 32) 1024 + (r % 32) 32 + c % 32, lda a multiple of 32 (r is
 // the K index for rev = 0 and the M index for rev = 1).
+constexpr int CAUSAL_BM = 256;  // rows of the tallest row tile; the others' divide it
 struct GemmBatch {
   int nbatch, zdiv, bdiv, mstore, rev, kgroups;
   int64_t sA, sB1, sB2, sC1, sC2, sAk, sBk;
