@@ -83,7 +83,10 @@ def rocprof_label(name):
         # (64-wide tiles are plain products: those of the masked loss have 128 columns and more)
         tag = fn if fn == "gemm_mfma_persist_kernel" or args[1] == "64" else "gemm_mfma_kernel(masked loss)"
         return f"{tag}<{args[0]},{args[1]},{lay},{ty(args[6])}>"
-    if fn == "gemm_nt4_persist_kernel" and len(args) >= 2:
+    if fn == "gemm_group_kernel" and len(args) >= 6:
+        lay = {("true", "true"): "NT", ("true", "false"): "NN", ("false", "false"): "TN"}[(args[3], args[4])]
+        return f"{fn}<{args[0]},{args[1]},{lay},{ty(args[5])}>"
+    if fn in ("gemm_nt4_persist_kernel", "gemm_nt4_group_kernel") and len(args) >= 2:
         return f"{fn}<256,{args[0]},NT,{ty(args[1])}>"
     if fn in ("attn_ds_gemm_persist_kernel", "attn_ds_gemm_kernel") and len(args) >= 7:
         return f"{fn}<{args[0]},{args[1]},{'dK' if args[4] == 'true' else 'dQ'},{ty(args[6])}>"

@@ -845,7 +845,7 @@ __global__ __launch_bounds__(256) void residual_rmsnorm4_kernel(float* __restric
 }
 
 template <typename T>
-static void rmsnorm_launch(float* x, const float* A, T* h, int64_t N, int D, float eps, hipStream_t s) {
+static const char* rmsnorm_launch(float* x, const float* A, T* h, int64_t N, int D, float eps, hipStream_t s) {
   const bool vec = D % 4 == 0 && D <= 8192 && (uintptr_t)x % 16 == 0 && (uintptr_t)A % 16 == 0 &&
                    (uintptr_t)h % (4 * sizeof(T)) == 0;
   const unsigned g = (unsigned)N;
@@ -854,15 +854,16 @@ static void rmsnorm_launch(float* x, const float* A, T* h, int64_t N, int D, flo
   else if (D <= 2048) residual_rmsnorm4_kernel<T, 2><<<g, 256, 0, s>>>(x, A, h, D, eps);
   else if (D <= 4096) residual_rmsnorm4_kernel<T, 4><<<g, 256, 0, s>>>(x, A, h, D, eps);
   else residual_rmsnorm4_kernel<T, 8><<<g, 256, 0, s>>>(x, A, h, D, eps);
+  return vec ? KLABEL("residual_rmsnorm4_kernel") : KLABEL("residual_rmsnorm_kernel");
 }
 
 hipError_t residual_rmsnorm(float* x, const float* A, void* h, int64_t N, int D, DType t, float eps,
                             hipStream_t s) {
   if (N <= 0 || D <= 0) return hipSuccess;
   prof_begin(KC_ELEM, s);
-  if (t == DT_BF16) rmsnorm_launch<bf16_t>(x, A, (bf16_t*)h, N, D, eps, s);
-  else rmsnorm_launch<float>(x, A, (float*)h, N, D, eps, s);
-  prof_end(KC_ELEM, s, 0.0, (double)N * D * ((A ? 12.0 : 4.0) + dsize(t)), KLABEL("residual_rmsnorm_kernel"));
+  const char* kname = t == DT_BF16 ? rmsnorm_launch<bf16_t>(x, A, (bf16_t*)h, N, D, eps, s)
+                                   : rmsnorm_launch<float>(x, A, (float*)h, N, D, eps, s);
+  prof_end(KC_ELEM, s, 0.0, (double)N * D * ((A ? 12.0 : 4.0) + dsize(t)), kname);
   return hipGetLastError();
 }
 

@@ -1859,7 +1859,8 @@ hipError_t gemm_mfma_group(const Gemm* g, int n, float* scratch, size_t scratch_
       if (whole) gemm_nt4_group_kernel<192, bf16_t, false><<<grid, 256, 0, s>>>(d, gr);
       else gemm_nt4_group_kernel<192, bf16_t, true><<<grid, 256, 0, s>>>(d, gr);
     }
-    prof_end(kclass, s, flops, bytes, KLABEL("gemm_nt4_group_kernel"));
+    prof_end(kclass, s, flops, bytes, best_bn == 256 ? KLABEL("gemm_nt4_group_kernel<256,256,NT,bf16>")
+                                                     : KLABEL("gemm_nt4_group_kernel<256,192,NT,bf16>"));
     return hipGetLastError();
   }
   if (best_kc == 0) return hipErrorNotSupported;
@@ -1895,16 +1896,24 @@ hipError_t gemm_mfma_group(const Gemm* g, int n, float* scratch, size_t scratch_
     gr.p[i] = d;
   }
   const bool f32 = g[0].c_t == DT_F32;
+  const char* kname = nullptr;
   prof_begin(kclass, s);
+#define T_(bm_, bn_, nst, AK, BK_, TC)                                                            \
+  {                                                                                               \
+    gemm_group_kernel<bm_, bn_, nst, AK, BK_, TC><<<wgs, 256, 0, s>>>(gr);                        \
+    kname = KLABEL("gemm_group_kernel<%d,%d,%s,%s>", bm_, bn_, AK ? (BK_ ? "NT" : "NN") : "TN",   \
+                   sizeof(TC) == 4 ? "fp32" : "bf16");                                            \
+  }
 #define L_(AK, BK_, TC)                                                                           \
   {                                                                                               \
-    if (best_tile == 0) gemm_group_kernel<64, 64, 4, AK, BK_, TC><<<wgs, 256, 0, s>>>(gr);        \
-    else if (best_tile == 1) gemm_group_kernel<128, 64, 3, AK, BK_, TC><<<wgs, 256, 0, s>>>(gr);  \
-    else gemm_group_kernel<128, 128, 2, AK, BK_, TC><<<wgs, 256, 0, s>>>(gr);                     \
+    if (best_tile == 0) T_(64, 64, 4, AK, BK_, TC)                                                \
+    else if (best_tile == 1) T_(128, 64, 3, AK, BK_, TC)                                          \
+    else T_(128, 128, 2, AK, BK_, TC)                                                             \
   }
   if (layout == 0) L_(true, true, bf16_t) else if (layout == 1) L_(true, false, bf16_t) else L_(false, false, float)
 #undef L_
-  prof_end(kclass, s, flops, bytes, KLABEL("gemm_group_kernel"));
+#undef T_
+  prof_end(kclass, s, flops, bytes, kname);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || sums.n == 0) return e;
   return run_sums(sums, f32, sbytes, s);

@@ -16,6 +16,12 @@ def test_rocprof_label_per_kernel_family():
             "gemm_nt4_persist_kernel<256,256,NT,bf16>",
         ns + "gemm_nt4_persist_kernel<192, float>(mla::(anonymous namespace)::GemmDev)":
             "gemm_nt4_persist_kernel<256,192,NT,fp32>",
+        ns + "gemm_nt4_group_kernel<192, unsigned short, true>(GemmDev, Nt4Group)":
+            "gemm_nt4_group_kernel<256,192,NT,bf16>",
+        ns + "gemm_group_kernel<128, 64, 3, false, false, float>(GroupDev)":
+            "gemm_group_kernel<128,64,TN,fp32>",
+        ns + "gemm_mfma_kernel<64, 64, 2, 2, true, false, unsigned short, 64, 4>(GemmDev)":
+            "gemm_mfma_kernel<64,64,NN,bf16>",
         ns + "gemm_mfma_persist_kernel<256, 256, 2, 4, false, false, float, 64, 2>(GemmDev)":
             "gemm_mfma_persist_kernel<256,256,TN,fp32>",
         ns + "gemm_mfma_persist_kernel<256, 192, 4, 2, true, false, unsigned short, 64, 2>(GemmDev)":
