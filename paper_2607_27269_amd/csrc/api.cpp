@@ -922,7 +922,11 @@ int mla_recon_decode_noalloc(const mla_recon_cfg* cfg, const void* q, const void
   return MLA_OK;
 }
 
-// ---- absorbed-form prefill and the W_UV fold -------------------------------------------
+// ---- prefill and the W_UV fold ---------------------------------------------------------
+// The regions have the sizes of a prefill in absorbed form, with a decoding's scratch per token
+// (callers keep workspaces of this size): [0, off_o) holds the expanded keys, the values or
+// guarded latents and, in what is left, the products' split-K partials; then o where the caller's
+// cannot be written directly; at off_lat the weighted latents (folded).
 static size_t prefill_layout(const mla_recon_cfg* cfg, size_t* off_o, size_t* off_lat) {
   const int64_t rows = (int64_t)cfg->batch * cfg->seq;
   const int DK = cfg->kv_rank + cfg->rope_dim, DVL = cfg->kv_rank;
@@ -981,13 +985,14 @@ int mla_recon_prefill(const mla_recon_cfg* cfg, const void* q, const void* cache
   // 3 x 999, H = 14, r_kv = 256, d_k = 64: 105 us against 483 us.
   const int T = cfg->seq, Gkv = cfg->s_kv_groups, dn = cfg->nope_dim, dr = cfg->rope_dim;
   const int hpg = H / Gkv, dqk = dn + dr;
-  // ws: keys, then the values (or, folded, the guarded latents); both smaller than the
-  // absorbed-query region that prefill_layout reserves
+  // ws: keys, then the values (or, folded, the guarded latents).  Both fit below off_o: per
+  // token and head at most 160 and 128 values of 2 bytes (or r_kv of them per token), where the
+  // region holds r_kv + d_rope of 2 bytes and r_kv of 4, r_kv at least 128
   const int nk = dn > 0 ? Gkv * dn : dr, nv = Gkv * dv;
   void* keys = ws;
   const size_t off_v = al((size_t)rows * nk * 2), off_s = off_v + al((size_t)rows * std::max(nv, rkv) * 2);
   void* vals = at(ws, off_v);
-  // split-K partials of the products: the rest of that region
+  // split-K partials of the products: the rest below off_o
   const Scratch sk = {(float*)at(ws, off_s), off_o > off_s ? (off_o - off_s) / 4 : 0};
   // (an o that the vector stores cannot take is filled from ws at the end)
   const bool o_direct = o && (uintptr_t)o % 16 == 0;

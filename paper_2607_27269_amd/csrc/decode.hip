@@ -498,6 +498,9 @@ bool decode_supported(int DK, int DVL) {
   return false;
 }
 
+// (The last term, a latent per sequence and head, is used by nothing since the merge and W_UV
+// share a launch.  It stays: callers keep workspaces of this size, the call without a workspace
+// holds it against its static buffer, and what that refused it refuses still.)
 size_t decode_ws_bytes(int B, int H, int DK, int DVL, int Lmax) {
   const int HP = (H + 31) / 32 * 32;
   const int nsplit = (Lmax + decode_chunk(Lmax, B) - 1) / decode_chunk(Lmax, B);

@@ -181,8 +181,6 @@ hipError_t step_prepare(const RopeTable& a, const RopeTable& b, int T, const uin
 // rope group i / rdiv), written in storage dtype with row stride H*dqk.
 hipError_t dq_finish(const float* dq_acc, void* dq, DType t, int N, int T, int H, int dqk,
                      int dnope, int rdiv, const float* cos_t, const float* sin_t, hipStream_t s);
-// dk^PE of rope group r = R^T sum of the partials of Ka groups r*per .. r*per+per-1,
-// written to out[n*out_tok + r*drope + e] in storage dtype.
 // bf16, one launch: R^T on dq (null: not), dkpe_finish (dkpe null: not) and, with dot, Eq. 11
 // from the ndot partials of sum dO . (o_s - o_t) left by the delta pass: with
 // dO = 2 M Y / (D sum M), L = sum(dO . (o_s - o_t)) / 2 (fixed order); loss[1] = NaN, the
@@ -190,6 +188,8 @@ hipError_t dq_finish(const float* dq_acc, void* dq, DType t, int N, int T, int H
 hipError_t bwd_finish(const RopeArgs* dq, const float* dkpe, void* dkpe_out, int64_t dkpe_tok, int N, int T,
                       int Gr, int per, int dr, const float* cos_t, const float* sin_t, const double* dot,
                       int64_t ndot, int D, void* scratch, float* loss, hipStream_t s);
+// dk^PE of rope group r = R^T sum of the partials of Ka groups r*per .. r*per+per-1,
+// written to out[n*out_tok + r*drope + e] in storage dtype.
 hipError_t dkpe_finish(const float* part, void* out, DType t, int64_t out_tok, int N, int T,
                        int Gr, int per, int drope, const float* cos_t, const float* sin_t,
                        hipStream_t s);
