@@ -263,9 +263,9 @@ int mla_recon_decode_noalloc(const mla_recon_cfg *cfg, const void *q, const void
  * o = W_UV[g] (weighted latent) and/or its post-W_O output A (the student side of Eq. 11),
  * computed either as o W_O^T or, given the folded weights of mla_recon_fold_uv_into_o, as
  * (weighted latent) W_O'^T.  The keys W_UK c_j (and, without folded weights, the values
- * W_UV c_j) are expanded into ws once per call, bf16.  A cache row that is not finite makes
- * the outputs of the tokens that see it NaN and leaves all others as they are.  Same shape
- * requirements as mla_recon_decode, and at most 65535 tokens (batch * seq) per call.
+ * W_UV c_j) are expanded into ws once per call, bf16.  A cache row that is not finite
+ * (or, without folded weights, whose values are not) makes the outputs of the tokens that see
+ * it NaN and leaves all others as they are.  Same shape requirements as mla_recon_decode, and at most 65535 tokens (batch * seq) per call.
  *   q     [B, T, H, d_nope + d_rope] bf16 (q^rope rotated by R_t)
  *   cache [B, T, r_kv + d_rope] bf16
  *   Wuk [G_kv d_nope, r_kv], Wuv [G_kv d_k, r_kv], Wo [D, H d_k] bf16; Wo_folded

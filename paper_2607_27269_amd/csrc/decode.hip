@@ -586,7 +586,10 @@ hipError_t uv_project(const void* lat, const void* Wuv, void* o, int rows, int H
 }
 
 // One wavefront per cache row: 16 bytes of the latent per lane (rkv <= 512).  Reads the
-// latents once; rows are rewritten only where they are not finite.
+// latents once; rows are rewritten only where they are not finite.  Finite latents can have
+// values beyond bf16 (a cache row past the tokens in use may hold anything): where a latent
+// reaches 2^64 the row's values are read too.  (Below that it would take weights of 2^55: a
+// sum has at most 512 terms.)
 __global__ __launch_bounds__(256) void prefill_guard_kernel(const bf16_t* __restrict__ cache,
                                                             int64_t rows, int rkv, int dr,
                                                             bf16_t* __restrict__ keys, int nk,
@@ -599,11 +602,15 @@ __global__ __launch_bounds__(256) void prefill_guard_kernel(const bf16_t* __rest
   const bool in = 8 * lane < rkv;
   u32x4 w = {0u, 0u, 0u, 0u};
   if (in) w = *(const u32x4*)(src + 8 * lane);
-  bool bad = false;
+  uint32_t top = 0u;  // the lane's largest exponent field, in place of the upper half's
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    bad |= (w[q] & 0x7f80u) == 0x7f80u || (w[q] & 0x7f800000u) == 0x7f800000u;
-  const bool any = __ballot(bad) != 0;  // wave-uniform
+  for (int q = 0; q < 4; ++q) top = max(top, max(w[q] << 16 & 0x7f800000u, w[q] & 0x7f800000u));
+  bool any = __ballot(top == 0x7f800000u) != 0;  // wave-uniform
+  if (!any && v && __ballot(top >= (127u + 64u) << 23) != 0) {
+    bool bad = false;
+    for (int c = lane; c < nv; c += 64) bad |= (v[row * nv + c] & 0x7f80u) == 0x7f80u;
+    any = __ballot(bad) != 0;
+  }
   if (lat_copy && in) *(u32x4*)(lat_copy + row * rkv + 8 * lane) = any ? u32x4{0u, 0u, 0u, 0u} : w;
   if (copy_pe)
     for (int c = lane; c < nk; c += 64) keys[row * nk + c] = any ? (bf16_t)0x7fc0 : src[rkv + c];

@@ -267,7 +267,7 @@ hipError_t uv_project(const void* lat, const void* Wuv, void* o, int rows, int H
                       int dv, hipStream_t s);
 // Prefill's guard against non-finite cache rows.  Attention multiplies masked values by
 // P = 0, which keeps a masked row out of earlier outputs only where it is finite.  For every
-// cache row whose latent has a NaN or an infinity: its values (v [rows][nv], or null) become
+// cache row whose latent, or whose values, have a NaN or an infinity: its values (v [rows][nv], or null) become
 // 0 and its keys (keys [rows][nk]) NaN, so that exactly the queries that see the row get NaN.
 // lat_copy (or null) receives the latents [rows][rkv], such rows as 0; copy_pe: the keys are
 // the cache's positional columns, copied (nk = dr; no non-positional keys).

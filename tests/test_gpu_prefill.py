@@ -120,3 +120,27 @@ def test_prefill_nonfinite_rows(idx, form, row):
                 continue
             assert torch.equal(y[0], y2[0]) and torch.equal(y[1, :row], y2[1, :row])
             assert not torch.isfinite(y2[1, row:].float()).any()
+
+
+@pytest.mark.parametrize("idx,form", [(1, "o+A"), (3, "A"), (2, "o+folded"), (1, "folded")])
+def test_prefill_huge_finite_rows(idx, form):
+    """Cache rows past the tokens in use may hold any finite bytes, whose values W_UV c lie
+    beyond bf16: the tokens before them are as with zeros there.  (Not bitwise: the softmax
+    reference of a wavefront's queries moves together.)"""
+    import torch
+    B, T, n = 2, 200, 70
+    cfg, c, x = _setup(idx, B, T)
+    x["cache"][:, n:] = 0
+    o, A = _run(cfg, c, x, form)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    sign = torch.randint(0, 2, x["cache"][:, n:].shape, device="cuda", generator=g) * 2 - 1
+    for big in (3e38, 2.0 ** 70):
+        print(f"[prefill] cfg{idx} {form} rows of {big}", flush=True)
+        x2 = dict(x, cache=x["cache"].clone(), Wuv=x["Wuv"] * (1.0 if big > 1e38 else 2.0 ** 57))
+        x2["cache"][:, n:] = (sign * big).to(torch.bfloat16)
+        x1 = dict(x, Wuv=x2["Wuv"])
+        y1 = (o, A) if big > 1e38 else _run(cfg, c, x1, form)
+        for y, y2 in zip(y1, _run(cfg, c, x2, form)):
+            if y is not None:
+                assert torch.isfinite(y2[:, :n].float()).all()
+                assert _rel(y2[:, :n], y[:, :n].double()) <= TOL
