@@ -64,6 +64,7 @@ struct GemmDev {
   float alpha, beta;
   int kchunk;         // K elements per split (multiple of BK)
   int nsplit;         // split-K chunks (persistent launch)
+  int aligned;        // rows of A and B 16-byte aligned (gemm_tile)
   int ktotal;
   int mstore;         // rows of C written (M is the row count operand A may be read at)
   // batched causal mode (causal != 0): workgroup z of nbatch works on A + z sA,
@@ -99,6 +100,8 @@ __device__ __forceinline__ int64_t tile32_off(int64_t r, int64_t c, int64_t tq) 
 }
 
 // ---- global -> register staging -------------------------------------------------------
+// (rows of the caller's arrays need no more than their elements' alignment here)
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
 template <bool KMAJOR, int ROWS, int NTHR, int BK, bool TILED = false>
 struct Loader;
 
@@ -132,7 +135,7 @@ struct Loader<true, ROWS, NTHR, BK, false> {
       const int row = c / NCH, kc = (c % NCH) * 8;
       u32x4 v = {0u, 0u, 0u, 0u};
       if ((CHUNKS % NTHR == 0 || c < CHUNKS) && row < rows_valid && k0 + kc < kend)
-        v = *(const u32x4*)(p + (int64_t)(row0 + row) * ld + k0 + kc);
+        v = *(const u32x4_any*)(p + (int64_t)(row0 + row) * ld + k0 + kc);
       r[i] = v;
     }
   }
@@ -202,7 +205,7 @@ struct Loader<false, ROWS, NTHR, BK, false> {
       const int kr = c / CPR, rc = (c % CPR) * 8;
       u32x4 v = {0u, 0u, 0u, 0u};
       if ((CHUNKS % NTHR == 0 || c < CHUNKS) && rc < rows_valid && k0 + kr < kend)
-        v = *(const u32x4*)(p + (int64_t)(k0 + kr) * ld + row0 + rc);
+        v = *(const u32x4_any*)(p + (int64_t)(k0 + kr) * ld + row0 + rc);
       r[i] = v;
     }
   }
@@ -489,13 +492,14 @@ __device__ __forceinline__ void gemm_tile(const GemmDev& g, int wg, int split) {
   const int nkg = (kend - kbeg + BK - 1) / BK;  // slices per operand group
   const int nk = nkg * (g.causal ? g.kgroups : 1);
   // slices copied straight to LDS (small tiles: also in a matrix smaller than the tile, with
-  // clamped rows); a
-  // ragged last slice, and every slice of a tile whose operand rows are too far apart for
-  // 32-bit offsets, goes through registers with zero fill
+  // clamped rows); a ragged last slice, and every slice of a tile whose operand rows are too far
+  // apart for 32-bit offsets, goes through registers with zero fill.  So does every slice of
+  // operands that are not 16-byte aligned, which the copies are not known to take: a product
+  // of few tokens must not depend on how its caller's arrays lie.
   const int mvalid = edge_rows<ATILE>(g) - m0, nvalid = g.N - n0;
   constexpr bool EDGE = BM <= 128 && !ATILE;  // (larger tiles are not used below their size)
   const bool edge = mvalid < BM || nvalid < BN;  // uniform
-  const bool dma_ok = (EDGE || !edge) && (AK ? (int64_t)BM * g.lda : (int64_t)BK * g.lda) < (1ll << 30) &&
+  const bool dma_ok = (ATILE || g.aligned) && (EDGE || !edge) && (AK ? (int64_t)BM * g.lda : (int64_t)BK * g.lda) < (1ll << 30) &&
                       (BKM ? (int64_t)BN * g.ldb : (int64_t)BK * g.ldb) < (1ll << 30);
   const int nfull = dma_ok ? (kend - kbeg) / BK : 0;
   // rev: slices are walked from the top of the K range down, so that all row tiles of a
@@ -1641,6 +1645,7 @@ static GemmDev dev_of(const Gemm& g) {
   d.M = g.M; d.N = g.N; d.ktotal = g.K; d.nsplit = 1;
   d.A = (const bf16_t*)g.A; d.lda = g.lda;
   d.B = (const bf16_t*)g.B; d.ldb = g.ldb;
+  d.aligned = ((uintptr_t)g.A | (uintptr_t)g.B) % 16 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0;
   d.C = g.C; d.ldc = g.ldc; d.alpha = g.alpha; d.beta = g.beta;
   d.mstore = g.M; d.part = nullptr; d.kchunk = 0;
   d.lscale = nullptr; d.lmask = nullptr; d.lpart = nullptr; d.lref = nullptr; d.ldref = 0;
@@ -2028,6 +2033,7 @@ hipError_t gemm_mfma_causal(const Gemm& g, const GemmBatch& bt, hipStream_t s) {
   d.M = g.M; d.N = g.N; d.ktotal = g.K; d.nsplit = 1;
   d.A = (const bf16_t*)g.A; d.lda = g.lda;
   d.B = (const bf16_t*)g.B; d.ldb = g.ldb;
+  d.aligned = 1;  // (checked above)
   d.C = g.C; d.ldc = g.ldc; d.alpha = g.alpha; d.beta = 0.f;
   d.part = nullptr;
   d.lscale = nullptr; d.lmask = nullptr; d.lpart = nullptr; d.lref = nullptr; d.ldref = 0;

@@ -101,6 +101,23 @@ def test_prefill_unaligned_o():
         assert torch.equal(o, o1) and torch.equal(A, A1)
 
 
+def test_prefill_unaligned_weights():
+    """A prefill of few tokens takes W_UK and W_O (or W_O') at any element: the same bits."""
+    import torch
+    cfg, c, x = _setup(1, 2, 30)
+    for form in ("o+A", "o+folded"):
+        o, A = _run(cfg, c, x, form)
+        for shift in (1, 2, 4):
+            y = dict(x)
+            for n in ("Wuk", "Wo", "fold"):
+                b = torch.empty(x[n].numel() + 8, dtype=x[n].dtype, device="cuda")
+                y[n] = b[shift:shift + x[n].numel()]
+                y[n].copy_(x[n].reshape(-1))
+            print(f"[prefill] {form} weights moved by {shift}", flush=True)
+            o1, A1 = _run(cfg, c, y, form)
+            assert torch.equal(o, o1) and torch.equal(A, A1)
+
+
 @pytest.mark.parametrize("idx,form", [(1, "o+A"), (1, "folded"), (3, "o+A"), (2, "o+folded")])
 @pytest.mark.parametrize("row", [0, 37, 66, 99])
 def test_prefill_nonfinite_rows(idx, form, row):

@@ -75,6 +75,41 @@ def test_unaligned_mask_matches_aligned():
             assert err <= 1e-2, (g, err)
 
 
+@pytest.mark.parametrize("idx,T", [(1, 90), (2, 33), (4, 65)])
+def test_unaligned_forward_arrays_match_aligned(idx, T):
+    """The forwards of few tokens take h and weights at any element: their products are
+    smaller than the tiles that are copied straight to LDS whole, and unaligned operands go
+    through registers in the same order, to the same bits."""
+    import torch
+    from paper_2607_27269_amd import _lib as L
+    from paper_2607_27269_amd.step import DeviceStep
+    print(f"[robust] unaligned h and weights cfg{idx} T={T}", flush=True)
+    cfg, wl = _case(idx, 1, T, None)
+    dev = DeviceStep(wl)
+    names = [n for n in ("h", "Wq", "Wk", "Wv", "Wo", "Wdq", "Wuq", "Wdkv_kr", "Wuk", "Wuv")
+             if getattr(dev, n) is not None]
+    outs = []
+    for shift in (0, 1, 2, 4):
+        x = {}
+        for n in names:
+            t = getattr(dev, n)
+            b = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)
+            x[n] = b[shift:shift + t.numel()]
+            x[n].copy_(t.reshape(-1))
+        p = lambda n: x[n].data_ptr() if n in x else None
+        A = torch.full((2,) + tuple(dev.A_t.shape), float("nan"), device=dev.A_t.device)
+        dev.ws.fill_(255)
+        tw = L.TeacherW(p("Wq"), p("Wk"), p("Wv"), p("Wo"), dev.inv_freq_t.data_ptr())
+        sw = L.StudentW(p("Wdq"), p("Wuq"), p("Wdkv_kr"), p("Wuk"), p("Wuv"), dev.inv_freq_s.data_ptr())
+        L.mla_recon_teacher_fwd(dev.ccfg, p("h"), tw, A[0].data_ptr(), dev.ws.data_ptr(), dev.ws_bytes, dev.stream)
+        L.mla_recon_student_fwd(dev.ccfg, p("h"), sw, p("Wo"), A[1].data_ptr(), dev.ws.data_ptr(), dev.ws_bytes,
+                                dev.stream)
+        torch.cuda.synchronize()
+        outs.append(A)
+    assert torch.isfinite(outs[0]).all()
+    for A in outs[1:]:
+        assert torch.equal(A, outs[0])
+
 def test_nan_in_valid_token_reaches_loss_and_gradients():
     import torch
     from paper_2607_27269_amd.step import DeviceStep
