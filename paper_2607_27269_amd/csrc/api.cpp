@@ -174,7 +174,9 @@ static Layout layout_of(const Dims& d, int chunk) {
   L.s_lse = take(N * d.H * 4);
   L.b_do = take(N * d.H * d.dv * ts);
   L.b_delta = take(N * d.H * 4);
-  L.b_dqacc = take(d.t == DT_F32 ? N * d.H * d.dqk * 4 : 0);
+  // (the vector-ALU attention's dQ, also in bf16)
+  const bool simt = d.t == DT_F32 || !attn_mfma_supported((int)d.dqk, (int)d.dv);
+  L.b_dqacc = take(simt ? N * d.H * d.dqk * 4 : 0);
   L.b_dkv = take(N * d.Gkv * (d.dn + d.dv) * ts);
   L.b_dkpe = take(d.Gkv * N * d.dr * 4);
   // dq .. split, side by side: before dQ is written, everything from a chunk's first dq row to

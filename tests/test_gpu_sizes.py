@@ -52,6 +52,30 @@ def test_step_sizes(idx, B, T):
         assert abs(out["loss"] - ref["loss"]) <= LOSS_TOL * ref["loss"]
 
 
+@pytest.mark.parametrize("dv,dn,dr,Gr,B,T", [(32, 32, 32, 1, 2, 200), (32, 16, 16, 2, 1, 130),
+                                             (16, 8, 8, 2, 3, 77)])
+def test_step_narrow_heads_bf16(dv, dn, dr, Gr, B, T):
+    """Head widths that only the vector-ALU attention has, in bf16 (its dQ is summed in an
+    fp32 region of its own)."""
+    from paper_2607_27269_amd.step import DeviceStep
+    print(f"[sizes] d_k={dv} d_nope={dn} d_rope={dr} B={B} T={T}", flush=True)
+    cfg = configs.shrink(configs.get(1), batch=B, seq=T, hidden=512, n_heads=8, n_kv_groups=2, head_dim=dv,
+                         q_rank=128, kv_rank=64, nope_dim=dn, rope_dim=dr, s_kv_groups=2, s_rope_groups=Gr,
+                         outlier_channels=0)
+    wl = synth.make_workload(cfg)
+    ref = oracle_step(wl)
+    tol = _tol(wl, ref)
+    dev = DeviceStep(wl)
+    for label, step in (("four calls: ", dev.step), ("single call: ", lambda: dev.fused_step(with_dA=False))):
+        for g in dev.grads.values():
+            g.fill_(float("nan"))
+        dev.ws.fill_(255)  # NaN patterns
+        step()
+        out = dev.results()
+        compare(out, ref, [g for g in GRADS if g in dev.grads], tol, label=label, cfg=cfg)
+        assert abs(out["loss"] - ref["loss"]) <= LOSS_TOL * ref["loss"]
+
+
 @pytest.mark.parametrize("B,T", [(2, 640), (3, 130), (5, 333)])
 def test_step_workspace_does_not_change_results(B, T):
     """Neither the split of a product nor that of a group's heads (and with them the rounding)
