@@ -1317,7 +1317,8 @@ __device__ __forceinline__ void gemm_nt4(const GemmDev& g, const Nt4Group& gr) {
         // byte: the block's nine dwords are shifted down to it (each holds a byte of the block).
         // (dO of 6002 tokens, 4096 x 4096: 189 us; on 256-wide tiles of the kernel that lets
         // the compiler place the copies, 250 us)
-        u32x8 mk = {1u, 1u, 1u, 1u, 1u, 1u, 1u, 1u};
+        constexpr uint32_t ALL = 0x01010101u;  // (a byte per row; no mask: every row kept)
+        u32x8 mk = {ALL, ALL, ALL, ALL, ALL, ALL, ALL, ALL};
         if (LS && g.lmask) {  // uniform
           const int r0 = m0 + wrow0 + i * 32, sh = SHIFT ? r0 & 3 : 0;
           const uint64_t pa = uniform_ptr(g.lmask + r0 - sh);

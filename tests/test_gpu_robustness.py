@@ -75,6 +75,28 @@ def test_unaligned_mask_matches_aligned():
             assert err <= 1e-2, (g, err)
 
 
+@pytest.mark.parametrize("idx,B,T", [(3, 1, 2048), (4, 2, 3001), (1, 1, 300)])
+def test_no_mask_matches_all_ones(idx, B, T):
+    """A null mask is a mask of ones: the same bits, on the four-wavefront product's whole and
+    moved tiles (the first two) as on the small tiles."""
+    import torch
+    from paper_2607_27269_amd import _lib as L
+    from paper_2607_27269_amd.step import DeviceStep
+    print(f"[robust] no mask cfg{idx} B={B} T={T}", flush=True)
+    cfg, wl = _case(idx, B, T, None)
+    dev = DeviceStep(wl)
+    outs = []
+    for m in (dev.mask.fill_(1).data_ptr(), None):
+        for g in dev.grads.values():
+            g.fill_(float("nan"))
+        L.mla_recon_step(dev.ccfg, dev.h.data_ptr(), dev.tw, dev.sw, m, dev.loss_buf.data_ptr(), None, dev.sg,
+                         dev.ws.data_ptr(), dev.ws_bytes, dev.stream)
+        torch.cuda.synchronize()
+        outs.append({"loss": dev.loss_buf[:1].clone(), **{k: v.clone() for k, v in dev.grads.items()}})
+    for k in outs[0]:
+        assert torch.isfinite(outs[0][k]).all() and torch.equal(outs[0][k], outs[1][k]), k
+
+
 @pytest.mark.parametrize("idx,T", [(1, 90), (2, 33), (4, 65)])
 def test_unaligned_forward_arrays_match_aligned(idx, T):
     """The forwards of few tokens take h and weights at any element: their products are
